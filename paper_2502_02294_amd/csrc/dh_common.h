@@ -113,41 +113,78 @@ __device__ __forceinline__ float pow_approx(float x, float y) {
   return __builtin_amdgcn_exp2f(y * __builtin_amdgcn_logf(x));
 }
 
-template <int D, int NQ = 5>
+// How F^R = (c Q + F)/2 or F^L = (c Q - F)/2 of a component whose flux is itself a product,
+// F = x y (density, energy, entropy; the momenta's flux is a sum), is rounded.  Every FMA
+// of a split is spelled out, so a cell's fluxes do not depend on where the compiler sees it.
+enum SplitRound {
+  kFluxRounded = 0,    // c Q exact: fma(c, Q, +-round(x y))
+  kSpeedRounded = 1,   // x y exact: fma(+-x, y, round(c Q))
+  kBothRounded = 2     // round(c Q) +- round(F), for the momenta too
+};
+
+// The specific internal energy before the floor, E - |U|^2/2, from et = Et / a^2: with
+// E = et / rho exact inside the FMA, or (ROUNDED) rounded first.  The latter with the
+// dual-energy entropy, which compares against E, and in the x adjoint (ETOT of the splits:
+// there H = Et/a^2 + p, too, takes the rounded et), as those have always been rounded: in cold
+// gas e is a small difference, and the last bit of it is seen in the adjoint.
+template <bool ROUNDED>
+__device__ __forceinline__ float total_minus_kinetic(float et, float ir, float uu) {
+  return ROUNDED ? fmaf(-0.5f, uu, et * ir) : fmaf(et, ir, -0.5f * uu);
+}
+
+// a + b with both operands already rounded (never contracted with the product behind one)
+__device__ __forceinline__ float add_rounded(float a, float b) {
+#pragma clang fp contract(off)
+  return a + b;
+}
+
+// (c q + s x y) / 2, s = +-1, with f = x y rounded
+template <int ROUND>
+__device__ __forceinline__ float half_split(float c, float q, float s, float f, float x, float y) {
+  if (ROUND == kFluxRounded) return 0.5f * fmaf(c, q, s * f);
+  if (ROUND == kSpeedRounded) return 0.5f * fmaf(s * x, y, c * q);
+  return 0.5f * add_rounded(c * q, s * f);
+}
+
+template <int D, int NQ = 5, int RR = kFluxRounded, int RL = kFluxRounded, bool ETOT = false>
 __device__ __forceinline__ void split_flux(const float* q, const HydroK& h, float* fr,
                                            float* fl) {
   const float rho = q[0];
   const float ir = rcp_approx(rho);
   const float u0 = q[1] * h.ia * ir, u1 = q[2] * h.ia * ir, u2 = q[3] * h.ia * ir;
-  const float ke = 0.5f * (u0 * u0 + u1 * u1 + u2 * u2);
-  float e;
-  if (NQ == 6) {
-    const float big = q[4] * h.ia2 * ir;
-    const float e_tot = big - ke;
-    e = e_tot > kDualEta1 * big ? e_tot : q[5] * h.ia2 * pow_approx(rho, h.gm2);
-  } else {
-    e = q[4] * h.ia2 * ir - ke;
-  }
+  const float uu = fmaf(u2, u2, fmaf(u0, u0, u1 * u1));
+  const float et = q[4] * h.ia2;
+  float e = total_minus_kinetic<NQ == 6 || ETOT>(et, ir, uu);
+  if (NQ == 6 && !(e > kDualEta1 * (et * ir))) e = q[5] * h.ia2 * pow_approx(rho, h.gm2);
   e = fmaxf(e, h.efloor);
-  const float p = h.gm1 * rho * e;
+  const float pe = h.gm1 * rho;
+  const float p = pe * e;
   const float cs = sqrt_approx(h.gg1 * e);
   const float ud = D == 0 ? u0 : (D == 1 ? u1 : u2);
   const float c = (fabsf(ud) + cs) * h.ia;
-  float f[5];
-  f[0] = rho * ud * h.ia;
-  f[1] = rho * ud * u0 + (D == 0 ? p : 0.0f);
-  f[2] = rho * ud * u1 + (D == 1 ? p : 0.0f);
-  f[3] = rho * ud * u2 + (D == 2 ? p : 0.0f);
-  f[4] = h.a * ud * (q[4] * h.ia2 + p);
+  const float m = rho * ud;
+  // F_rho = m / a, F_E = (a U_d) H with H = Et/a^2 + p, F_S = (S U_d) / a
+  const float f0 = m * h.ia;
+  fr[0] = half_split<RR>(c, rho, 1.0f, f0, h.ia, m);
+  fl[0] = half_split<RL>(c, rho, -1.0f, f0, h.ia, m);
+  const float u[3] = {u0, u1, u2};
 #pragma unroll
-  for (int k = 0; k < 5; ++k) {
-    fr[k] = 0.5f * (c * q[k] + f[k]);
-    fl[k] = 0.5f * (c * q[k] - f[k]);
+  for (int k = 0; k < 3; ++k) {
+    const float f = fmaf(m, u[k], D == k ? p : 0.0f);
+    constexpr int mr = RR == kBothRounded ? kBothRounded : kFluxRounded;
+    constexpr int ml = RL == kBothRounded ? kBothRounded : kFluxRounded;
+    fr[1 + k] = half_split<mr>(c, q[1 + k], 1.0f, f, 0.0f, 0.0f);
+    fl[1 + k] = half_split<ml>(c, q[1 + k], -1.0f, f, 0.0f, 0.0f);
   }
+  const float au = h.a * ud, H = ETOT ? fmaf(pe, e, et) : fmaf(q[4], h.ia2, p);
+  const float f4 = au * H;
+  fr[4] = half_split<RR>(c, q[4], 1.0f, f4, au, H);
+  fl[4] = half_split<RL>(c, q[4], -1.0f, f4, au, H);
   if (NQ == 6) {
-    const float f5 = q[5] * ud * h.ia;
-    fr[5] = 0.5f * (c * q[5] + f5);
-    fl[5] = 0.5f * (c * q[5] - f5);
+    const float su = q[5] * ud;
+    const float f5 = su * h.ia;
+    fr[5] = half_split<RR>(c, q[5], 1.0f, f5, h.ia, su);
+    fl[5] = half_split<RL>(c, q[5], -1.0f, f5, h.ia, su);
   }
 }
 
@@ -157,23 +194,22 @@ __device__ __forceinline__ void split_flux(const float* q, const HydroK& h, floa
 // Derivatives are those of the floored EOS (zero through e where the floor is active), of
 // the branch of the dual-energy selection that the state takes, and of |U_d| with
 // sign(0) = 0.
-template <int D, int NQ = 5>
+template <int D, int NQ = 5, bool ETOT = false>
 __device__ __forceinline__ void split_flux_vjp(const float* q, const HydroK& h, const float* s,
                                                const float* dv, float* out) {
   const float rho = q[0];
   const float ir = rcp_approx(rho);
   const float iar = h.ia * ir;
   const float u[3] = {q[1] * iar, q[2] * iar, q[3] * iar};
-  const float ke = 0.5f * (u[0] * u[0] + u[1] * u[1] + u[2] * u[2]);
-  float eraw, tot = 1.0f, rs = 0.0f;   // tot: the total energy's branch; rs = rho^(gamma-2)
+  const float uu = fmaf(u[2], u[2], fmaf(u[0], u[0], u[1] * u[1]));
+  const float ke = 0.5f * uu;
+  const float et = q[4] * h.ia2;
+  float eraw = total_minus_kinetic<NQ == 6 || ETOT>(et, ir, uu);
+  float tot = 1.0f, rs = 0.0f;   // tot: the total energy's branch; rs = rho^(gamma-2)
   if (NQ == 6) {
-    const float big = q[4] * h.ia2 * ir;
-    const float e_tot = big - ke;
-    tot = e_tot > kDualEta1 * big ? 1.0f : 0.0f;
+    tot = eraw > kDualEta1 * (et * ir) ? 1.0f : 0.0f;
     rs = pow_approx(rho, h.gm2);
-    eraw = tot > 0.0f ? e_tot : q[5] * h.ia2 * rs;
-  } else {
-    eraw = q[4] * h.ia2 * ir - ke;
+    eraw = tot > 0.0f ? eraw : q[5] * h.ia2 * rs;
   }
   // 0 where the floor is active (its derivative), 1 elsewhere; every term is computed and
   // masked, so the function has no branches

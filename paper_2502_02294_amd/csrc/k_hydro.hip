@@ -17,9 +17,7 @@
 //                cells along the pencil with a register pipeline (loads coalesced across x,
 //                two cells prefetched, 3-cell halos re-read from cache).
 //   sweep_x_vjp  adjoint along x in LDS.
-//   vjp_walk_h + vjp_finish   adjoint along y/z in two passes: the first walks the pencil
-//                and writes lambda_h = dL/dUh, the second applies the stage-1 transpose
-//                with a +-1 stencil.
+//   sweep_walk_vjp   adjoint along y/z: one walk per segment with the same pipeline.
 #include "dh_kernels.h"
 
 namespace dh {
@@ -110,7 +108,7 @@ __global__ void __launch_bounds__(kRowThreads) sweep_x_kernel(const float* __res
   float qh[NQ];
 #pragma unroll
   for (int c = 0; c < NQ; ++c)
-    qh[c] = u[c] - hdt * ((fr[c] - FL[c][jp]) - (FR[c][jm] - fl[c]));
+    qh[c] = fmaf(-hdt, (fr[c] - FL[c][jp]) - (FR[c][jm] - fl[c]), u[c]);
   split_flux<0, NQ>(qh, h2, fr, fl);
   __syncthreads();
 #pragma unroll
@@ -131,7 +129,7 @@ __global__ void __launch_bounds__(kRowThreads) sweep_x_kernel(const float* __res
   for (int c = 0; c < NQ; ++c) FR[c][j] = f2[c];
   __syncthreads();
 #pragma unroll
-  for (int c = 0; c < NQ; ++c) qout[c * nc + base + j] = u[c] - dt * (f2[c] - FR[c][jm]);
+  for (int c = 0; c < NQ; ++c) qout[c * nc + base + j] = fmaf(-dt, f2[c] - FR[c][jm], u[c]);
 }
 
 // ---------------------------------------------------------------------- forward y / z walk
@@ -155,6 +153,25 @@ __device__ __forceinline__ void kick_loaded(float (&u)[NQ], const float (&g)[3],
   u[1] = m[0];
   u[2] = m[1];
   u[3] = m[2];
+}
+
+// The splits of the cells with which a pipeline is filled at every kHead-th cell of a pencil
+// (a head) are rounded as SplitRound says per visit, not as in the steady state: the way a
+// walk of kHead cells per segment has always rounded them.  So a sweep's results, and the half
+// step and the branches its adjoint recomputes, are the same to the last bit however many
+// segments a launch cuts a pencil into (a last bit there can move a limiter to its other side,
+// and a gradient by 1e-4).
+constexpr int kHead = 64;
+__device__ __forceinline__ bool walk_head(int s) { return (s & (kHead - 1)) == 0; }
+
+// Column (x, other) and segment of a thread.  n is a power of two and n^2 a multiple of the
+// block, so the segment is the same over a wave.
+__device__ __forceinline__ void walk_thread(int n, int& x, int& other, int& seg) {
+  const unsigned t = blockIdx.x * blockDim.x + threadIdx.x;
+  const unsigned lg = 31u - __builtin_clz(static_cast<unsigned>(n));
+  x = static_cast<int>(t & (n - 1));
+  other = static_cast<int>((t >> lg) & (n - 1));
+  seg = __builtin_amdgcn_readfirstlane(static_cast<int>(t >> (2 * lg)));
 }
 
 template <int D, int NQ>
@@ -208,10 +225,14 @@ __device__ __forceinline__ void walk_load_g(const WalkPtr<NQ>& p, int kk, float 
   g[2] = v.z;
 }
 
-template <int D, int I, int STAGE, bool KICK, int NQ>
+template <int D, int I, int STAGE, bool HEAD, bool KICK, int NQ>
 __device__ __forceinline__ void walk_fwd_visit(WalkFwd<D, NQ>& w, const WalkPtr<NQ>& p, int k,
                                                const HydroK& h1, const HydroK& h2, float dt,
                                                float hdt) {
+  // rounding of the splits where a head fills its pipeline (see kHead)
+  constexpr bool fill = HEAD && STAGE < 4;
+  constexpr int q1 = fill && (I == 0 || I >= 3) ? kSpeedRounded : kFluxRounded;
+  constexpr int q2 = fill && (I == 2 || I == 5) ? kSpeedRounded : kFluxRounded;
   constexpr int s0 = I & 7, s1 = (I + 7) & 7, s3 = (I + 5) & 7, sa = (I + kAhead) & 7;
   constexpr int t0 = I & 3, t1 = (I + 3) & 3, t2 = (I + 2) & 3, t3 = (I + 1) & 3;
   constexpr int p0 = I & 1, p1 = (I + 1) & 1;
@@ -222,15 +243,15 @@ __device__ __forceinline__ void walk_fwd_visit(WalkFwd<D, NQ>& w, const WalkPtr<
     kick_loaded(w.u[s0], w.g[I & 3], p.h);
   }
   float l1[NQ];
-  split_flux<D, NQ>(w.u[s0], h1, w.r1[p0], l1);
+  split_flux<D, NQ, q1, q1>(w.u[s0], h1, w.r1[p0], l1);
   if (STAGE < 1) return;
 #pragma unroll
   for (int c = 0; c < NQ; ++c) w.f1[p0][c] = w.r1[p1][c] - l1[c];   // face k-1/2
   if (STAGE < 2) return;
   float qh[NQ];   // half step of cell k-1 from faces (k-1) -+ 1/2
 #pragma unroll
-  for (int c = 0; c < NQ; ++c) qh[c] = w.u[s1][c] - hdt * (w.f1[p0][c] - w.f1[p1][c]);
-  split_flux<D, NQ>(qh, h2, w.r2[t0], w.l2[t0]);
+  for (int c = 0; c < NQ; ++c) qh[c] = fmaf(-hdt, w.f1[p0][c] - w.f1[p1][c], w.u[s1][c]);
+  split_flux<D, NQ, q2, q2>(qh, h2, w.r2[t0], w.l2[t0]);
   if (STAGE < 3) return;
   // face (k-3)+1/2: F^R at cells k-4, k-3, k-2 (slots t3, t2, t1), F^L at k-3, k-2, k-1; the
   // lower slopes are the previous face's upper ones
@@ -248,7 +269,21 @@ __device__ __forceinline__ void walk_fwd_visit(WalkFwd<D, NQ>& w, const WalkPtr<
   if (STAGE < 4) return;
   const unsigned off = p.at(k - 3);
 #pragma unroll
-  for (int c = 0; c < NQ; ++c) p.st(c, off, w.u[s3][c] - dt * (w.f2[p0][c] - w.f2[p1][c]));
+  for (int c = 0; c < NQ; ++c) p.st(c, off, fmaf(-dt, w.f2[p0][c] - w.f2[p1][c], w.u[s3][c]));
+}
+
+// Visits 0..5 of a segment from cell s on fill the pipeline; from visit 6 on every visit
+// writes a cell.
+template <int D, bool HEAD, bool KICK, int NQ>
+__device__ __forceinline__ void walk_fwd_fill(WalkFwd<D, NQ>& w, const WalkPtr<NQ>& p, int s,
+                                              const HydroK& h1, const HydroK& h2, float dt,
+                                              float hdt) {
+  walk_fwd_visit<D, 0, 0, HEAD, KICK, NQ>(w, p, s - 3, h1, h2, dt, hdt);
+  walk_fwd_visit<D, 1, 1, HEAD, KICK, NQ>(w, p, s - 2, h1, h2, dt, hdt);
+  walk_fwd_visit<D, 2, 2, HEAD, KICK, NQ>(w, p, s - 1, h1, h2, dt, hdt);
+  walk_fwd_visit<D, 3, 2, HEAD, KICK, NQ>(w, p, s, h1, h2, dt, hdt);
+  walk_fwd_visit<D, 4, 2, HEAD, KICK, NQ>(w, p, s + 1, h1, h2, dt, hdt);
+  walk_fwd_visit<D, 5, 3, HEAD, KICK, NQ>(w, p, s + 2, h1, h2, dt, hdt);
 }
 
 template <int D, bool KICK, int NQ>
@@ -257,11 +292,9 @@ __global__ void __launch_bounds__(256) sweep_walk_kernel(const float* __restrict
                                                          long long nc, int seg_len, int nseg,
                                                          const StepScal* __restrict__ tab,
                                                          const float4* __restrict__ g4) {
-  const long long t = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (t >= static_cast<long long>(n) * n * nseg) return;
-  const int x = static_cast<int>(t % n);
-  const int other = static_cast<int>((t / n) % n);
-  const int seg = static_cast<int>(t / (static_cast<long long>(n) * n));
+  int x, other, seg;
+  walk_thread(n, x, other, seg);
+  if (seg >= nseg) return;
   WalkPtr<NQ> p;
   p.n = n;
   p.base = 4u * (D == 1 ? static_cast<unsigned>(other) * n * n + x
@@ -294,23 +327,20 @@ __global__ void __launch_bounds__(256) sweep_walk_kernel(const float* __restrict
     walk_load_g<NQ>(p, s - 3, w.g[0]);
     walk_load_g<NQ>(p, s - 2, w.g[1]);
   }
-  // visits 0..5 fill the pipeline; from visit 6 on every visit writes a cell
-  walk_fwd_visit<D, 0, 0, KICK, NQ>(w, p, s - 3, h1, h2, dt, hdt);
-  walk_fwd_visit<D, 1, 1, KICK, NQ>(w, p, s - 2, h1, h2, dt, hdt);
-  walk_fwd_visit<D, 2, 2, KICK, NQ>(w, p, s - 1, h1, h2, dt, hdt);
-  walk_fwd_visit<D, 3, 2, KICK, NQ>(w, p, s, h1, h2, dt, hdt);
-  walk_fwd_visit<D, 4, 2, KICK, NQ>(w, p, s + 1, h1, h2, dt, hdt);
-  walk_fwd_visit<D, 5, 3, KICK, NQ>(w, p, s + 2, h1, h2, dt, hdt);
+  if (walk_head(s))
+    walk_fwd_fill<D, true, KICK, NQ>(w, p, s, h1, h2, dt, hdt);
+  else
+    walk_fwd_fill<D, false, KICK, NQ>(w, p, s, h1, h2, dt, hdt);
   // seg_len is a multiple of 8: visits 6 + 8m .. 13 + 8m have ring phases 6, 7, 0, .., 5
   for (int k = s + 3; k < s + 3 + seg_len; k += 8) {
-    walk_fwd_visit<D, 6, 4, KICK, NQ>(w, p, k, h1, h2, dt, hdt);
-    walk_fwd_visit<D, 7, 4, KICK, NQ>(w, p, k + 1, h1, h2, dt, hdt);
-    walk_fwd_visit<D, 0, 4, KICK, NQ>(w, p, k + 2, h1, h2, dt, hdt);
-    walk_fwd_visit<D, 1, 4, KICK, NQ>(w, p, k + 3, h1, h2, dt, hdt);
-    walk_fwd_visit<D, 2, 4, KICK, NQ>(w, p, k + 4, h1, h2, dt, hdt);
-    walk_fwd_visit<D, 3, 4, KICK, NQ>(w, p, k + 5, h1, h2, dt, hdt);
-    walk_fwd_visit<D, 4, 4, KICK, NQ>(w, p, k + 6, h1, h2, dt, hdt);
-    walk_fwd_visit<D, 5, 4, KICK, NQ>(w, p, k + 7, h1, h2, dt, hdt);
+    walk_fwd_visit<D, 6, 4, false, KICK, NQ>(w, p, k, h1, h2, dt, hdt);
+    walk_fwd_visit<D, 7, 4, false, KICK, NQ>(w, p, k + 1, h1, h2, dt, hdt);
+    walk_fwd_visit<D, 0, 4, false, KICK, NQ>(w, p, k + 2, h1, h2, dt, hdt);
+    walk_fwd_visit<D, 1, 4, false, KICK, NQ>(w, p, k + 3, h1, h2, dt, hdt);
+    walk_fwd_visit<D, 2, 4, false, KICK, NQ>(w, p, k + 4, h1, h2, dt, hdt);
+    walk_fwd_visit<D, 3, 4, false, KICK, NQ>(w, p, k + 5, h1, h2, dt, hdt);
+    walk_fwd_visit<D, 4, 4, false, KICK, NQ>(w, p, k + 6, h1, h2, dt, hdt);
+    walk_fwd_visit<D, 5, 4, false, KICK, NQ>(w, p, k + 7, h1, h2, dt, hdt);
   }
 }
 
@@ -362,7 +392,7 @@ __global__ void __launch_bounds__(kRowThreads) sweep_x_vjp_kernel(
       u[2] = m[1];
       u[3] = m[2];
     }
-    split_flux<0, NQ>(u, h1, fr, fl);
+    split_flux<0, NQ, kFluxRounded, kFluxRounded, true>(u, h1, fr, fl);
 #pragma unroll
     for (int c = 0; c < NQ; ++c) {
       S[0][c][j] = lm[c];
@@ -376,8 +406,8 @@ __global__ void __launch_bounds__(kRowThreads) sweep_x_vjp_kernel(
     float fr[NQ], fl[NQ];
 #pragma unroll
     for (int c = 0; c < NQ; ++c)
-      qh[c] = u[c] - hdt * ((S[1][c][j] - S[2][c][jp]) - (S[1][c][jm] - S[2][c][j]));
-    split_flux<0, NQ>(qh, h2, fr, fl);
+      qh[c] = fmaf(-hdt, (S[1][c][j] - S[2][c][jp]) - (S[1][c][jm] - S[2][c][j]), u[c]);
+    split_flux<0, NQ, kFluxRounded, kFluxRounded, true>(qh, h2, fr, fl);
 #pragma unroll
     for (int c = 0; c < NQ; ++c) {
       S[3][c][j] = fr[c];
@@ -416,7 +446,7 @@ __global__ void __launch_bounds__(kRowThreads) sweep_x_vjp_kernel(
       sv[c] = gR + gL;
       dv[c] = gR - gL;
     }
-    split_flux_vjp<0, NQ>(qh, h2, sv, dv, gr);
+    split_flux_vjp<0, NQ, true>(qh, h2, sv, dv, gr);
 #pragma unroll
     for (int c = 0; c < NQ; ++c) S[0][c][j] = gr[c];
   }
@@ -430,7 +460,7 @@ __global__ void __launch_bounds__(kRowThreads) sweep_x_vjp_kernel(
       sv[c] = gp - gm;
       dv[c] = gp + gm;
     }
-    split_flux_vjp<0, NQ>(u, h1, sv, dv, out);
+    split_flux_vjp<0, NQ, true>(u, h1, sv, dv, out);
 #pragma unroll
     for (int c = 0; c < NQ; ++c) lam_in[c * nc + base + j] = lm[c] + gr[c] + out[c];
   }
@@ -503,10 +533,20 @@ struct WalkVjpPtr {
 
 // STAGE: 0 split only, 1 + F1, 2 + half step and stage-2 split, 3 + first faces (every
 // adjoint assigned), 4 + faces, 5 + lambda_h, 6 + G1, 7 + output
-template <int D, int I, int STAGE, bool KICK, int NQ>
+template <int D, int I, int STAGE, bool HEAD, bool KICK, int NQ>
 __device__ __forceinline__ void walk_vjp_visit(WalkVjp<NQ>& w, const WalkVjpPtr<NQ>& p, int k,
                                                const HydroK& h1, const HydroK& h2, float dt,
                                                float hdt) {
+  // rounding of the stage-1 splits where a head fills its pipeline (see kHead)
+  constexpr bool fill = HEAD && STAGE < 7;
+  constexpr int q1r = !fill                               ? kFluxRounded
+                      : I == 0 || I == 2 || I >= 6 ? kSpeedRounded
+                      : I == 5                            ? kBothRounded
+                                                          : kFluxRounded;
+  constexpr int q1l = !fill    ? kFluxRounded
+                      : I >= 6 ? kSpeedRounded
+                      : I == 2 ? kBothRounded
+                               : kFluxRounded;
   constexpr int u0 = I & 7, u1 = (I + 7) & 7, u4 = (I + 4) & 7;
   constexpr int ua = (I + kAheadU) & 7, la = (I + kAheadL) & 7;
   constexpr int l1s = (I + 7) & 7, l2s = (I + 6) & 7, l3s = (I + 5) & 7;
@@ -525,13 +565,13 @@ __device__ __forceinline__ void walk_vjp_visit(WalkVjp<NQ>& w, const WalkVjpPtr<
   }
   if (KICK) kick_loaded(w.u[u0], w.g[I & 1], p.h);
   float l1[NQ];
-  split_flux<D, NQ>(w.u[u0], h1, w.r1[p0], l1);
+  split_flux<D, NQ, q1r, q1l>(w.u[u0], h1, w.r1[p0], l1);
   if (STAGE < 1) return;
 #pragma unroll
   for (int c = 0; c < NQ; ++c) w.f1[p0][c] = w.r1[p1][c] - l1[c];
   if (STAGE < 2) return;
 #pragma unroll
-  for (int c = 0; c < NQ; ++c) w.uh[t0][c] = w.u[u1][c] - hdt * (w.f1[p0][c] - w.f1[p1][c]);
+  for (int c = 0; c < NQ; ++c) w.uh[t0][c] = fmaf(-hdt, w.f1[p0][c] - w.f1[p1][c], w.u[u1][c]);
   split_flux<D, NQ>(w.uh[t0], h2, w.r2[t0], w.l2[t0]);
   if (STAGE < 3) return;
   // R face k-2 (F^R at k-3, k-2, k-1), L face k-3 (F^L at k-3, k-2, k-1)
@@ -587,6 +627,21 @@ __device__ __forceinline__ void walk_vjp_visit(WalkVjp<NQ>& w, const WalkVjpPtr<
   }
 }
 
+// Visits 0..7 of a segment from cell s on; from visit 8 on every visit writes a cell.
+template <int D, bool HEAD, bool KICK, int NQ>
+__device__ __forceinline__ void walk_vjp_fill(WalkVjp<NQ>& w, const WalkVjpPtr<NQ>& p, int s,
+                                              const HydroK& h1, const HydroK& h2, float dt,
+                                              float hdt) {
+  walk_vjp_visit<D, 0, 0, HEAD, KICK, NQ>(w, p, s - 4, h1, h2, dt, hdt);
+  walk_vjp_visit<D, 1, 1, HEAD, KICK, NQ>(w, p, s - 3, h1, h2, dt, hdt);
+  walk_vjp_visit<D, 2, 2, HEAD, KICK, NQ>(w, p, s - 2, h1, h2, dt, hdt);
+  walk_vjp_visit<D, 3, 2, HEAD, KICK, NQ>(w, p, s - 1, h1, h2, dt, hdt);
+  walk_vjp_visit<D, 4, 3, HEAD, KICK, NQ>(w, p, s, h1, h2, dt, hdt);
+  walk_vjp_visit<D, 5, 4, HEAD, KICK, NQ>(w, p, s + 1, h1, h2, dt, hdt);
+  walk_vjp_visit<D, 6, 5, HEAD, KICK, NQ>(w, p, s + 2, h1, h2, dt, hdt);
+  walk_vjp_visit<D, 7, 6, HEAD, KICK, NQ>(w, p, s + 3, h1, h2, dt, hdt);
+}
+
 template <int D, bool KICK, int NQ>
 __global__ void __launch_bounds__(256) sweep_walk_vjp_kernel(const float* __restrict__ qin,
                                                              const float* __restrict__ lam_out,
@@ -594,11 +649,9 @@ __global__ void __launch_bounds__(256) sweep_walk_vjp_kernel(const float* __rest
                                                              long long nc, int seg_len, int nseg,
                                                              const StepScal* __restrict__ tab,
                                                              const float4* __restrict__ g4) {
-  const long long t = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (t >= static_cast<long long>(n) * n * nseg) return;
-  const int x = static_cast<int>(t % n);
-  const int other = static_cast<int>((t / n) % n);
-  const int seg = static_cast<int>(t / (static_cast<long long>(n) * n));
+  int x, other, seg;
+  walk_thread(n, x, other, seg);
+  if (seg >= nseg) return;
   WalkVjpPtr<NQ> p;
   p.n = n;
   p.base = 4u * (D == 1 ? static_cast<unsigned>(other) * n * n + x
@@ -639,28 +692,36 @@ __global__ void __launch_bounds__(256) sweep_walk_vjp_kernel(const float* __rest
 #pragma unroll
     for (int c = 0; c < NQ; ++c) w.lm[j][c] = WalkVjpPtr<NQ>::ld(p.l[c], off);
   }
-  walk_vjp_visit<D, 0, 0, KICK, NQ>(w, p, s - 4, h1, h2, dt, hdt);
-  walk_vjp_visit<D, 1, 1, KICK, NQ>(w, p, s - 3, h1, h2, dt, hdt);
-  walk_vjp_visit<D, 2, 2, KICK, NQ>(w, p, s - 2, h1, h2, dt, hdt);
-  walk_vjp_visit<D, 3, 2, KICK, NQ>(w, p, s - 1, h1, h2, dt, hdt);
-  walk_vjp_visit<D, 4, 3, KICK, NQ>(w, p, s, h1, h2, dt, hdt);
-  walk_vjp_visit<D, 5, 4, KICK, NQ>(w, p, s + 1, h1, h2, dt, hdt);
-  walk_vjp_visit<D, 6, 5, KICK, NQ>(w, p, s + 2, h1, h2, dt, hdt);
-  walk_vjp_visit<D, 7, 6, KICK, NQ>(w, p, s + 3, h1, h2, dt, hdt);
+  if (walk_head(s))
+    walk_vjp_fill<D, true, KICK, NQ>(w, p, s, h1, h2, dt, hdt);
+  else
+    walk_vjp_fill<D, false, KICK, NQ>(w, p, s, h1, h2, dt, hdt);
   // seg_len is a multiple of 8: visits 8 + 8m .. 15 + 8m have ring phases 0 .. 7
   for (int k = s + 4; k < s + 4 + seg_len; k += 8) {
-    walk_vjp_visit<D, 0, 7, KICK, NQ>(w, p, k, h1, h2, dt, hdt);
-    walk_vjp_visit<D, 1, 7, KICK, NQ>(w, p, k + 1, h1, h2, dt, hdt);
-    walk_vjp_visit<D, 2, 7, KICK, NQ>(w, p, k + 2, h1, h2, dt, hdt);
-    walk_vjp_visit<D, 3, 7, KICK, NQ>(w, p, k + 3, h1, h2, dt, hdt);
-    walk_vjp_visit<D, 4, 7, KICK, NQ>(w, p, k + 4, h1, h2, dt, hdt);
-    walk_vjp_visit<D, 5, 7, KICK, NQ>(w, p, k + 5, h1, h2, dt, hdt);
-    walk_vjp_visit<D, 6, 7, KICK, NQ>(w, p, k + 6, h1, h2, dt, hdt);
-    walk_vjp_visit<D, 7, 7, KICK, NQ>(w, p, k + 7, h1, h2, dt, hdt);
+    walk_vjp_visit<D, 0, 7, false, KICK, NQ>(w, p, k, h1, h2, dt, hdt);
+    walk_vjp_visit<D, 1, 7, false, KICK, NQ>(w, p, k + 1, h1, h2, dt, hdt);
+    walk_vjp_visit<D, 2, 7, false, KICK, NQ>(w, p, k + 2, h1, h2, dt, hdt);
+    walk_vjp_visit<D, 3, 7, false, KICK, NQ>(w, p, k + 3, h1, h2, dt, hdt);
+    walk_vjp_visit<D, 4, 7, false, KICK, NQ>(w, p, k + 4, h1, h2, dt, hdt);
+    walk_vjp_visit<D, 5, 7, false, KICK, NQ>(w, p, k + 5, h1, h2, dt, hdt);
+    walk_vjp_visit<D, 6, 7, false, KICK, NQ>(w, p, k + 6, h1, h2, dt, hdt);
+    walk_vjp_visit<D, 7, 7, false, KICK, NQ>(w, p, k + 7, h1, h2, dt, hdt);
   }
 }
 
-int pick_segment(int n) { return n >= 64 ? 64 : n; }
+// Cells per segment of a walk: at most kHead, halved (down to 8) until the launch has 2048
+// waves, two per SIMD, which is what the adjoint's registers allow at a time.  Each halving
+// costs 6 (adjoint 8) more visits per segment, so a launch with enough waves keeps long
+// segments: at 256^3 (4096 waves) z takes 143 us forward and 265 us in the adjoint, 144 and
+// 295 us with 16 cells.  With one segment per pencil small boxes leave the chip idle, and a
+// walk takes the latency of its visits: 64^3 32.4 -> 9.2 us (adjoint 73.5 -> 15.7 us), 128^3
+// 36.8 -> 21.8 us (75 -> 40 us).
+int pick_segment(const Batch& b) {
+  int seg = b.n < kHead ? b.n : kHead;
+  const long long columns = static_cast<long long>(b.n) * b.n * b.S;
+  while (seg > 8 && columns * (b.n / seg) < 2048 * 64) seg /= 2;
+  return seg;
+}
 
 }  // namespace
 
@@ -680,7 +741,7 @@ void sweep_nq(hipStream_t st, const float* qin, float* qout, const Batch& b, int
       hipLaunchKernelGGL((sweep_x_kernel<false, NQ>), grid, dim3(kRowThreads), 0, st, qin, qout,
                          n, nc, b.tab, nullptr);
   } else {
-    const int seg = pick_segment(n);
+    const int seg = pick_segment(b);
     const int nseg = n / seg;
     const long long threads = static_cast<long long>(n) * n * nseg;
     const dim3 grid(blocks_for(threads, 256), b.S);
@@ -712,7 +773,7 @@ void sweep_vjp_nq(hipStream_t st, const float* qin, const float* lam_out, float*
       hipLaunchKernelGGL((sweep_x_vjp_kernel<false, NQ>), grid, dim3(kRowThreads), 0, st, qin,
                          lam_out, lam_in, n, nc, b.tab, nullptr);
   } else {
-    const int seg = pick_segment(n);
+    const int seg = pick_segment(b);
     const int nseg = n / seg;
     const long long threads = static_cast<long long>(n) * n * nseg;
     const dim3 grid(blocks_for(threads, 256), b.S);
