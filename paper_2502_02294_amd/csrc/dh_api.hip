@@ -895,7 +895,7 @@ void power_spectrum(dh_sim* s, int nbins, std::vector<double>& pk) {
   density_spectrum(s, b);
   dh::launch_pk_bin(s->st, s->spec, nbins, s->pk_part, b);
   std::vector<double> sums(static_cast<size_t>(S) * nbins);
-  double* d_sums = s->red;   // S nbins <= 8 red_blocks S + 8 doubles
+  double* d_sums = s->red;   // S nbins doubles
   dh::launch_reduce_sum(s->st, s->pk_part, nblk, nblk, S * nbins, d_sums);
   DH_HIP(hipMemcpyAsync(sums.data(), d_sums, sums.size() * sizeof(double), hipMemcpyDeviceToHost,
                         s->st));
@@ -1499,7 +1499,8 @@ int dh_create(const dh_config* cfg, dh_sim** out) {
     s->g4b = s->alloc<float4>(nc);
     s->cfl_red = s->alloc<double>(static_cast<long long>(dh::cfl_blocks(n)) * S + 1);
     s->red_blocks = dh::sum_blocks(s->nc);
-    s->red = s->alloc<double>(8LL * s->red_blocks * S + 8);
+    // 8 conservation sums, 2 loss or source sums, or up to n / 2 spectrum sums per sample
+    s->red = s->alloc<double>(std::max({8LL * s->red_blocks, 2LL * dh::cfl_blocks(n), n / 2LL}) * S + 8);
     s->red_out = s->alloc<double>(8LL * S + 16);
     s->d_acur = s->alloc<double>(S);
     s->cur_tab = s->alloc<StepScal>(S);
@@ -1877,7 +1878,7 @@ int dh_forward(dh_sim* s, const float* d_white, double a_final, int32_t* nsteps_
 int dh_loss(dh_sim* s, const float* d_target, double* loss_out) {
   if (!s || !d_target || !loss_out) return DH_E_INVAL;
   return guarded(s, [&]() -> int {
-    const int nb = s->red_blocks;
+    const int nb = dh::cfl_blocks(s->n);
     dh::launch_loss_partial(s->st, s->q, d_target, s->prm.A, s->prm.beta,
                             static_cast<float>(1.0 / s->f_b), s->red, batch(s, nullptr));
     dh::launch_reduce_sum(s->st, s->red, nb, nb, s->S, s->red_out);
@@ -1956,7 +1957,7 @@ int dh_backward(dh_sim* s, const float* d_grad_rho, float* d_grad_white, double*
                      1.0 / s->f_b, s->e_floor, s->t_per_e, s->cfg.gamma, nullptr, s->lq,
                      batch(s, nullptr));
     } else {
-      const int nb = s->red_blocks;
+      const int nb = dh::cfl_blocks(s->n);
       dh::launch_loss_vjp(s->st, s->q, s->loss_target, s->prm.A, s->prm.beta,
                           static_cast<float>(1.0 / s->f_b), s->lq, s->red, batch(s, nullptr));
       dh::launch_reduce_sum(s->st, s->red, nb, nb, 2 * S, s->red_out);

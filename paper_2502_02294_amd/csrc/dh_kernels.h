@@ -239,7 +239,7 @@ int sum_blocks(long long count);
 // FP64 block sums of several fields of one sample: partial[v * nblocks + b]
 void launch_conservation_partial(hipStream_t st, const float* q, const float* mom,
                                  double* partial, int nblocks, long long nc);
-// flux-field loss: partial[s nb + block], nb = sum_blocks(nc)
+// flux-field loss: partial[s nb + block], nb = cfl_blocks(n)
 void launch_loss_partial(hipStream_t st, const float* rho, const float* target, double A,
                          double beta, float inv_rho_mean, double* partial, const Batch& b);
 // lam_rho = dL/drho (per sample, mean over the sample's cells); dL/d(A, beta) partials

@@ -13,37 +13,47 @@ namespace dh {
 namespace {
 
 constexpr int kRedThreads = 256;
-constexpr int kRedPer = 8;   // cells per thread in reduction kernels
+constexpr int kRedPer = 8;   // cells per thread of the conservation sums
 
 __device__ __forceinline__ int wrapi(int j, int n) { return j & (n - 1); }
 
-// block reduction of nv doubles per thread into out[v * stride + blockIdx.x], through the
-// LDS scratch sh (NV kRedThreads doubles; the caller synchronises before handing in memory
-// that other waves may still read)
+// Sum or maximum of v over the 64 lanes of the wave, a butterfly in a fixed order
+template <bool MAX>
+__device__ __forceinline__ double wave_reduce(double v) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    const double o = __shfl_xor(v, off, 64);
+    v = MAX ? fmax(v, o) : v + o;
+  }
+  return v;
+}
+
+// block reduction of NV doubles per thread into out[v * stride + blockIdx.x]: the waves by
+// shuffles, then the waves' values in order through the LDS scratch sh (the caller
+// synchronises before handing in memory that other waves may still read)
 template <int NV, bool MAX>
-__device__ void block_reduce_in(double (*sh)[kRedThreads], double (&v)[NV], double* out,
+__device__ void block_reduce_in(double (*sh)[kRedThreads / 64], double (&v)[NV], double* out,
                                 long long stride) {
 #pragma unroll
-  for (int k = 0; k < NV; ++k) sh[k][threadIdx.x] = v[k];
-  __syncthreads();
-  for (int off = kRedThreads / 2; off > 0; off >>= 1) {
-    if (threadIdx.x < off) {
-#pragma unroll
-      for (int k = 0; k < NV; ++k)
-        sh[k][threadIdx.x] = MAX ? fmax(sh[k][threadIdx.x], sh[k][threadIdx.x + off])
-                                 : sh[k][threadIdx.x] + sh[k][threadIdx.x + off];
-    }
-    __syncthreads();
+  for (int k = 0; k < NV; ++k) {
+    const double w = wave_reduce<MAX>(v[k]);
+    if ((threadIdx.x & 63) == 0) sh[k][threadIdx.x >> 6] = w;
   }
+  __syncthreads();
   if (threadIdx.x == 0) {
 #pragma unroll
-    for (int k = 0; k < NV; ++k) out[k * stride + blockIdx.x] = sh[k][0];
+    for (int k = 0; k < NV; ++k) {
+      double r = sh[k][0];
+#pragma unroll
+      for (int w = 1; w < kRedThreads / 64; ++w) r = MAX ? fmax(r, sh[k][w]) : r + sh[k][w];
+      out[k * stride + blockIdx.x] = r;
+    }
   }
 }
 
 template <int NV, bool MAX>
 __device__ void block_reduce_store(double (&v)[NV], double* out, long long stride) {
-  __shared__ double sh[NV][kRedThreads];
+  __shared__ double sh[NV][kRedThreads / 64];
   block_reduce_in<NV, MAX>(sh, v, out, stride);
 }
 
@@ -294,7 +304,7 @@ template <bool FULL, int NQ>
 __global__ void __launch_bounds__(kRedThreads) close_step_kernel(
     const float* q_in, float* q, const float4* __restrict__ g4, float* __restrict__ star,
     float* __restrict__ q_kicked, double gg1, double* partial, long long nc,
-    const StepScal* __restrict__ tab, float* __restrict__ znew, float* __restrict__ sn_out) {
+    const StepScal* __restrict__ tab, float* __restrict__ znew, float* __restrict__ sn_out, int per) {
   const StepScal& sc = tab[blockIdx.y];
   const bool do_max = FULL && partial != nullptr;
   if (!sc.active) {
@@ -312,8 +322,8 @@ __global__ void __launch_bounds__(kRedThreads) close_step_kernel(
   if (sn_out) sn_out += blockIdx.y * nc;
   const float gm2 = static_cast<float>(a.gamma - 2.0), g1m = static_cast<float>(1.0 - a.gamma);
   double vmax[1] = {0.0};
-  const long long base = static_cast<long long>(blockIdx.x) * kRedThreads * kRedPer;
-  for (int r = 0; r < kRedPer; ++r) {
+  const long long base = static_cast<long long>(blockIdx.x) * kRedThreads * per;
+  for (int r = 0; r < per; ++r) {
     const long long c = base + r * kRedThreads + threadIdx.x;
     if (c >= nc) break;
     float q5[NQ];
@@ -386,7 +396,7 @@ __device__ __forceinline__ float smooth27(const float* __restrict__ f, unsigned 
 template <int NQ>
 __global__ void __launch_bounds__(kRedThreads) sn_inject_kernel(
     const float* __restrict__ sn, float* __restrict__ q, double gg1, double* partial, int n,
-    int lgn, const StepScal* __restrict__ tab) {
+    int lgn, const StepScal* __restrict__ tab, int per) {
   const StepScal& sc = tab[blockIdx.y];
   const long long nc = 1LL << (3 * lgn);
   if (!sc.active) {
@@ -399,8 +409,8 @@ __global__ void __launch_bounds__(kRedThreads) sn_inject_kernel(
   const float gm2 = static_cast<float>(a.gamma - 2.0), g1m = static_cast<float>(1.0 - a.gamma);
   const unsigned n1 = static_cast<unsigned>(n - 1);
   double vmax[1] = {0.0};
-  const long long base = static_cast<long long>(blockIdx.x) * kRedThreads * kRedPer;
-  for (int r = 0; r < kRedPer; ++r) {
+  const long long base = static_cast<long long>(blockIdx.x) * kRedThreads * per;
+  for (int r = 0; r < per; ++r) {
     const long long c = base + r * kRedThreads + threadIdx.x;
     if (c >= nc) break;
     const unsigned uc = static_cast<unsigned>(c);
@@ -616,7 +626,7 @@ __global__ void __launch_bounds__(kRedThreads) source_kick_vjp_kernel(
     const float* __restrict__ q_kick, const float4* __restrict__ g4, float* __restrict__ lam,
     float* __restrict__ lam_g, double* partial, long long nc, const StepScal* __restrict__ tab,
     const float* __restrict__ q_open, float* __restrict__ lam_g_open,
-    const StepScal* __restrict__ tab_open, const float* __restrict__ lam_inj) {
+    const StepScal* __restrict__ tab_open, const float* __restrict__ lam_inj, int per) {
   const StepScal& sc = tab[blockIdx.y];
   if (!sc.active) {
     zero_partials<2>(partial);
@@ -636,8 +646,8 @@ __global__ void __launch_bounds__(kRedThreads) source_kick_vjp_kernel(
     h_open = tab_open[blockIdx.y].h;
   }
   double acc[2] = {0.0, 0.0};
-  const long long base = static_cast<long long>(blockIdx.x) * kRedThreads * kRedPer;
-  for (int r = 0; r < kRedPer; ++r) {
+  const long long base = static_cast<long long>(blockIdx.x) * kRedThreads * per;
+  for (int r = 0; r < per; ++r) {
     const long long c = base + r * kRedThreads + threadIdx.x;
     if (c >= nc) break;
     float q5[NQ], l5[NQ];
@@ -793,7 +803,7 @@ template <int NQ>
 __global__ void __launch_bounds__(kRedThreads) close_step_mlp_kernel(
     const float* q_in, float* q, const float4* __restrict__ g4, float* __restrict__ star,
     float* __restrict__ q_kicked, double gg1, double* partial, long long nc,
-    const StepScal* __restrict__ tab, float* __restrict__ znew, float* __restrict__ sn_out) {
+    const StepScal* __restrict__ tab, float* __restrict__ znew, float* __restrict__ sn_out, int per) {
   const StepScal& sc = tab[blockIdx.y];
   if (!sc.active) {
     if (partial) zero_partials<1>(partial);
@@ -817,8 +827,8 @@ __global__ void __launch_bounds__(kRedThreads) close_step_mlp_kernel(
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int g = lane >> 4, cl = lane & 15;
   double vmax[1] = {0.0};
-  const long long base = static_cast<long long>(blockIdx.x) * kRedThreads * kRedPer;
-  for (int r = 0; r < kRedPer; ++r) {
+  const long long base = static_cast<long long>(blockIdx.x) * kRedThreads * per;
+  for (int r = 0; r < per; ++r) {
     const long long c = base + r * kRedThreads + threadIdx.x;
     const bool valid = c < nc;
     float q5[NQ];
@@ -886,7 +896,7 @@ __global__ void __launch_bounds__(kRedThreads) close_step_mlp_kernel(
     // the stage, free once every wave is done, holds the reduction (no LDS of its own, so
     // more blocks share a CU)
     __syncthreads();
-    block_reduce_in<1, true>(reinterpret_cast<double (*)[kRedThreads]>(&stage[0][0][0]), vmax,
+    block_reduce_in<1, true>(reinterpret_cast<double (*)[kRedThreads / 64]>(&stage[0][0][0]), vmax,
                              sample_partials(partial), partial_stride());
   }
 }
@@ -902,7 +912,7 @@ __global__ void __launch_bounds__(kRedThreads) close_step_mlp_kernel(
 template <int NQ>
 __global__ void __launch_bounds__(kRedThreads, 2) source_vjp_mlp_kernel(
     const float* __restrict__ q, float* __restrict__ lam, double* partial, long long nc,
-    const StepScal* __restrict__ tab, const float* __restrict__ lam_inj) {
+    const StepScal* __restrict__ tab, const float* __restrict__ lam_inj, int per) {
   const StepScal& sc = tab[blockIdx.y];
   if (!sc.active) {
     zero_partials<2>(partial);
@@ -922,8 +932,8 @@ __global__ void __launch_bounds__(kRedThreads, 2) source_vjp_mlp_kernel(
   const int g = lane >> 4, cl = lane & 15;
   const double K = a.a * a.a * a.e0_code;
   double acc[2] = {0.0, 0.0};
-  const long long base = static_cast<long long>(blockIdx.x) * kRedThreads * kRedPer;
-  for (int r = 0; r < kRedPer; ++r) {
+  const long long base = static_cast<long long>(blockIdx.x) * kRedThreads * per;
+  for (int r = 0; r < per; ++r) {
     const long long c = base + r * kRedThreads + threadIdx.x;
     const bool valid = c < nc;
     float q5[NQ];
@@ -1117,9 +1127,9 @@ __global__ void __launch_bounds__(kRedThreads, 2) source_vjp_mlp_kernel(
   }
   // the stage, free once every wave is done, holds the reduction: 54 KB of LDS per block, so
   // three blocks (three waves per SIMD) share a CU
-  static_assert(sizeof(stage) >= 2 * kRedThreads * sizeof(double), "stage too small");
+  static_assert(sizeof(stage) >= 2 * kRedThreads / 64 * sizeof(double), "stage too small");
   __syncthreads();
-  block_reduce_in<2, false>(reinterpret_cast<double (*)[kRedThreads]>(&stage[0][0][0]), acc,
+  block_reduce_in<2, false>(reinterpret_cast<double (*)[kRedThreads / 64]>(&stage[0][0][0]), acc,
                             sample_partials(partial), partial_stride());
 }
 
@@ -1129,12 +1139,12 @@ __global__ void __launch_bounds__(kRedThreads) cfl_partial_kernel(const float* _
                                                                   const double* __restrict__ a_cur,
                                                                   double gg1, double efloor,
                                                                   float gm2, double* partial,
-                                                                  long long nc) {
+                                                                  long long nc, int per) {
   const double a = a_cur[blockIdx.y];
   q += blockIdx.y * NQ * nc;
   double v[1] = {0.0};
-  const long long base = static_cast<long long>(blockIdx.x) * kRedThreads * kRedPer;
-  for (int r = 0; r < kRedPer; ++r) {
+  const long long base = static_cast<long long>(blockIdx.x) * kRedThreads * per;
+  for (int r = 0; r < per; ++r) {
     const long long c = base + r * kRedThreads + threadIdx.x;
     if (c >= nc) break;
     float q5[NQ];
@@ -1144,26 +1154,34 @@ __global__ void __launch_bounds__(kRedThreads) cfl_partial_kernel(const float* _
   block_reduce_store<1, true>(v, sample_partials(partial), partial_stride());
 }
 
-// single block: out[v] = reduce over in[v * stride + 0..count)
-__global__ void __launch_bounds__(kRedThreads) reduce_kernel(const double* __restrict__ in,
-                                                             int count, int stride, int is_max,
-                                                             double* out) {
-  __shared__ double sh[kRedThreads];
-  const int v = blockIdx.x;
-  double acc = is_max ? -INFINITY : 0.0;
-  for (int i = threadIdx.x; i < count; i += kRedThreads) {
-    const double x = in[static_cast<long long>(v) * stride + i];
-    acc = is_max ? fmax(acc, x) : acc + x;
+// one block per vector: out[v] = reduce over in[v * stride + 0..count)
+constexpr int kReduceThreads = 1024;
+template <bool MAX>
+__global__ void __launch_bounds__(kReduceThreads) reduce_kernel(const double* __restrict__ in,
+                                                                int count, int stride,
+                                                                double* out) {
+  __shared__ double sh[kReduceThreads / 64];
+  const double* x = in + static_cast<long long>(blockIdx.x) * stride;
+  const double none = MAX ? -INFINITY : 0.0;
+  double acc = none;
+  // four independent loads a round (a missing one changes neither a sum nor a maximum)
+  for (int i = threadIdx.x; i < count; i += 4 * kReduceThreads) {
+    double y[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      y[k] = i + k * kReduceThreads < count ? x[i + k * kReduceThreads] : none;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) acc = MAX ? fmax(acc, y[k]) : acc + y[k];
   }
-  sh[threadIdx.x] = acc;
+  acc = wave_reduce<MAX>(acc);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = acc;
   __syncthreads();
-  for (int off = kRedThreads / 2; off > 0; off >>= 1) {
-    if (threadIdx.x < off)
-      sh[threadIdx.x] = is_max ? fmax(sh[threadIdx.x], sh[threadIdx.x + off])
-                               : sh[threadIdx.x] + sh[threadIdx.x + off];
-    __syncthreads();
+  if (threadIdx.x == 0) {
+    double r = sh[0];
+#pragma unroll
+    for (int w = 1; w < kReduceThreads / 64; ++w) r = MAX ? fmax(r, sh[w]) : r + sh[w];
+    out[blockIdx.x] = r;
   }
-  if (threadIdx.x == 0) out[v] = sh[0];
 }
 
 // ------------------------------------------------------------------------- sums
@@ -1187,12 +1205,12 @@ __global__ void __launch_bounds__(kRedThreads) loss_kernel(const float* __restri
                                                            const float* __restrict__ target,
                                                            double A, double beta, double irm,
                                                            double* partial, long long nc,
-                                                           long long qs) {
+                                                           long long qs, int per) {
   rho += blockIdx.y * qs;   // density row of the sample's Q
   target += blockIdx.y * nc;
   double v[1] = {0.0};
-  const long long base = static_cast<long long>(blockIdx.x) * kRedThreads * kRedPer;
-  for (int r = 0; r < kRedPer; ++r) {
+  const long long base = static_cast<long long>(blockIdx.x) * kRedThreads * per;
+  for (int r = 0; r < per; ++r) {
     const long long c = base + r * kRedThreads + threadIdx.x;
     if (c >= nc) break;
     const double f = exp(-A * pow(rho[c] * irm, beta));
@@ -1208,14 +1226,14 @@ __global__ void __launch_bounds__(kRedThreads) loss_vjp_kernel(const float* __re
                                                                double A, double beta, double irm,
                                                                float* __restrict__ lam_rho,
                                                                double* partial, long long nc,
-                                                               long long qs) {
+                                                               long long qs, int per) {
   rho += blockIdx.y * qs;
   target += blockIdx.y * nc;
   lam_rho += blockIdx.y * qs;
   double v[2] = {0.0, 0.0};
-  const long long base = static_cast<long long>(blockIdx.x) * kRedThreads * kRedPer;
+  const long long base = static_cast<long long>(blockIdx.x) * kRedThreads * per;
   const double w = 2.0 / static_cast<double>(nc);
-  for (int r = 0; r < kRedPer; ++r) {
+  for (int r = 0; r < per; ++r) {
     const long long c = base + r * kRedThreads + threadIdx.x;
     if (c >= nc) break;
     const double dl = rho[c] * irm;
@@ -1389,7 +1407,22 @@ __global__ void fill_kernel(float* p, float v, long long count) {
   if (i < count) p[i] = v;
 }
 
+// Cells per thread of the closing pass, the source adjoint, the CFL and the loss passes: up to
+// 8, so that a block's reduction is a small part of its work, but no more than leaves 2048
+// blocks (8 per CU) of one sample.  Chosen by the box alone, so that the order of the FP64
+// sums, and with it every sample's gradient, does not depend on the batch.
+int cells_per_thread(int n) {
+  const long long per = static_cast<long long>(n) * n * n / (2048LL * kRedThreads);
+  return static_cast<int>(per < 1 ? 1 : (per > 8 ? 8 : per));
+}
+
 }  // namespace
+
+int cfl_blocks(int n) {
+  const long long nc = static_cast<long long>(n) * n * n;
+  return static_cast<int>(nc / (kRedThreads * cells_per_thread(n)));
+}
+int source_vjp_blocks(int n) { return cfl_blocks(n); }
 
 void launch_gas_kick_vjp(hipStream_t st, const float* q_before, const float4* g4, float* lam_q,
                          float* lam_g, const Batch& b) {
@@ -1409,17 +1442,18 @@ void launch_close_step(hipStream_t st, const float* q_in, float* q, const float4
   if ((star == nullptr && znew != nullptr) || (block_max != nullptr && sn_out != nullptr))
     throw ArgError("closing pass: new stars need the star field; a smoothed injection takes "
                    "the CFL maxima to the injection pass");
-  const dim3 grid(sum_blocks(b.nc()), b.S);
+  const int per = cells_per_thread(b.n);
+  const dim3 grid(cfl_blocks(b.n), b.S);
   const double gg1 = gamma * (gamma - 1.0);
 #define DH_CLOSE(FULL, NQ)                                                                      \
   hipLaunchKernelGGL((close_step_kernel<FULL, NQ>), grid, dim3(kRedThreads), 0, st, q_in, q, g4, \
-                     star, q_kicked, gg1, block_max, b.nc(), b.tab, znew, sn_out)
+                     star, q_kicked, gg1, block_max, b.nc(), b.tab, znew, sn_out, per)
   if (closure && b.nq == 6)
     hipLaunchKernelGGL(close_step_mlp_kernel<6>, grid, dim3(kRedThreads), 0, st, q_in, q, g4, star,
-                       q_kicked, gg1, block_max, b.nc(), b.tab, znew, sn_out);
+                       q_kicked, gg1, block_max, b.nc(), b.tab, znew, sn_out, per);
   else if (closure)
     hipLaunchKernelGGL(close_step_mlp_kernel<5>, grid, dim3(kRedThreads), 0, st, q_in, q, g4, star,
-                       q_kicked, gg1, block_max, b.nc(), b.tab, znew, sn_out);
+                       q_kicked, gg1, block_max, b.nc(), b.tab, znew, sn_out, per);
   else if (b.nq == 6) {
     if (star) DH_CLOSE(true, 6);
     else DH_CLOSE(false, 6);
@@ -1441,11 +1475,13 @@ void launch_sn_inject(hipStream_t st, const float* sn, float* q, double gamma, d
                       const Batch& b) {
   if (!b.tab) throw ArgError("supernova injection: step table required");
   if (b.nq == 6)
-    hipLaunchKernelGGL(sn_inject_kernel<6>, dim3(sum_blocks(b.nc()), b.S), dim3(kRedThreads), 0,
-                       st, sn, q, gamma * (gamma - 1.0), block_max, b.n, log2_int(b.n), b.tab);
+    hipLaunchKernelGGL(sn_inject_kernel<6>, dim3(cfl_blocks(b.n), b.S), dim3(kRedThreads), 0, st, sn,
+                       q, gamma * (gamma - 1.0), block_max, b.n, log2_int(b.n), b.tab,
+                       cells_per_thread(b.n));
   else
-    hipLaunchKernelGGL(sn_inject_kernel<5>, dim3(sum_blocks(b.nc()), b.S), dim3(kRedThreads), 0,
-                       st, sn, q, gamma * (gamma - 1.0), block_max, b.n, log2_int(b.n), b.tab);
+    hipLaunchKernelGGL(sn_inject_kernel<5>, dim3(cfl_blocks(b.n), b.S), dim3(kRedThreads), 0, st, sn,
+                       q, gamma * (gamma - 1.0), block_max, b.n, log2_int(b.n), b.tab,
+                       cells_per_thread(b.n));
   DH_LAUNCH_CHECK();
 }
 
@@ -1469,8 +1505,6 @@ void launch_smooth27(hipStream_t st, const float* in, long long in_stride, float
 int sum_blocks(long long count) {
   return static_cast<int>((count + kRedThreads * kRedPer - 1) / (kRedThreads * kRedPer));
 }
-int source_vjp_blocks(int n) { return sum_blocks(static_cast<long long>(n) * n * n); }
-int cfl_blocks(int n) { return sum_blocks(static_cast<long long>(n) * n * n); }
 
 void launch_source_vjp(hipStream_t st, const float* q_before, float* lam_q, double* partials,
                        const Batch& b, const float* lam_inj) {
@@ -1478,10 +1512,10 @@ void launch_source_vjp(hipStream_t st, const float* q_before, float* lam_q, doub
   const dim3 grid(source_vjp_blocks(b.n), b.S);
   if (b.nq == 6)
     hipLaunchKernelGGL(source_vjp_mlp_kernel<6>, grid, dim3(kRedThreads), 0, st, q_before, lam_q,
-                       partials, b.nc(), b.tab, lam_inj);
+                       partials, b.nc(), b.tab, lam_inj, cells_per_thread(b.n));
   else
     hipLaunchKernelGGL(source_vjp_mlp_kernel<5>, grid, dim3(kRedThreads), 0, st, q_before, lam_q,
-                       partials, b.nc(), b.tab, lam_inj);
+                       partials, b.nc(), b.tab, lam_inj, cells_per_thread(b.n));
   DH_LAUNCH_CHECK();
 }
 
@@ -1496,7 +1530,7 @@ void launch_source_kick_vjp(hipStream_t st, const float* q_kick, const float4* g
 #define DH_SKV(OPEN, NQ)                                                                      \
   hipLaunchKernelGGL((source_kick_vjp_kernel<OPEN, NQ>), grid, dim3(kRedThreads), 0, st, q_kick, \
                      g4, lam_q, lam_g, partials, b.nc(), b.tab, q_open, lam_g_open, tab_open,    \
-                     lam_inj)
+                     lam_inj, cells_per_thread(b.n))
   if (b.nq == 6) {
     if (q_open) DH_SKV(true, 6);
     else DH_SKV(false, 6);
@@ -1513,23 +1547,26 @@ void launch_cfl_partial(hipStream_t st, const float* q, const double* a_cur, dou
   const float gm2 = static_cast<float>(gamma - 2.0);
   if (b.nq == 6)
     hipLaunchKernelGGL(cfl_partial_kernel<6>, dim3(cfl_blocks(b.n), b.S), dim3(kRedThreads), 0, st,
-                       q, a_cur, gamma * (gamma - 1.0), efloor, gm2, block_max, b.nc());
+                       q, a_cur, gamma * (gamma - 1.0), efloor, gm2, block_max, b.nc(),
+                       cells_per_thread(b.n));
   else
     hipLaunchKernelGGL(cfl_partial_kernel<5>, dim3(cfl_blocks(b.n), b.S), dim3(kRedThreads), 0, st,
-                       q, a_cur, gamma * (gamma - 1.0), efloor, gm2, block_max, b.nc());
+                       q, a_cur, gamma * (gamma - 1.0), efloor, gm2, block_max, b.nc(),
+                       cells_per_thread(b.n));
   DH_LAUNCH_CHECK();
 }
 
 void launch_reduce_max(hipStream_t st, const double* in, int count, int stride, int nvec,
                        double* out) {
-  hipLaunchKernelGGL(reduce_kernel, dim3(nvec), dim3(kRedThreads), 0, st, in, count, stride, 1,
-                     out);
+  hipLaunchKernelGGL(reduce_kernel<true>, dim3(nvec), dim3(kReduceThreads), 0, st, in, count,
+                     stride, out);
   DH_LAUNCH_CHECK();
 }
 
 void launch_reduce_sum(hipStream_t st, const double* in, int count, int stride, int nvec,
                        double* out) {
-  hipLaunchKernelGGL(reduce_kernel, dim3(nvec), dim3(kRedThreads), 0, st, in, count, stride, 0, out);
+  hipLaunchKernelGGL(reduce_kernel<false>, dim3(nvec), dim3(kReduceThreads), 0, st, in, count,
+                     stride, out);
   DH_LAUNCH_CHECK();
 }
 
@@ -1542,16 +1579,17 @@ void launch_conservation_partial(hipStream_t st, const float* q, const float* mo
 
 void launch_loss_partial(hipStream_t st, const float* rho, const float* target, double A,
                          double beta, float inv_rho_mean, double* partial, const Batch& b) {
-  hipLaunchKernelGGL(loss_kernel, dim3(sum_blocks(b.nc()), b.S), dim3(kRedThreads), 0, st, rho,
-                     target, A, beta, static_cast<double>(inv_rho_mean), partial, b.nc(), b.qs());
+  hipLaunchKernelGGL(loss_kernel, dim3(cfl_blocks(b.n), b.S), dim3(kRedThreads), 0, st, rho,
+                     target, A, beta, static_cast<double>(inv_rho_mean), partial, b.nc(), b.qs(),
+                     cells_per_thread(b.n));
   DH_LAUNCH_CHECK();
 }
 
 void launch_loss_vjp(hipStream_t st, const float* rho, const float* target, double A, double beta,
                      float inv_rho_mean, float* lam_rho, double* partial, const Batch& b) {
-  hipLaunchKernelGGL(loss_vjp_kernel, dim3(sum_blocks(b.nc()), b.S), dim3(kRedThreads), 0, st, rho,
+  hipLaunchKernelGGL(loss_vjp_kernel, dim3(cfl_blocks(b.n), b.S), dim3(kRedThreads), 0, st, rho,
                      target, A, beta, static_cast<double>(inv_rho_mean), lam_rho, partial, b.nc(),
-                     b.qs());
+                     b.qs(), cells_per_thread(b.n));
   DH_LAUNCH_CHECK();
 }
 
