@@ -551,9 +551,9 @@ bool keep_step(dh_sim* s, int k) {
 }
 
 // bins of the particle positions pos (all samples of b)
-void sort_particles(dh_sim* s, const float* pos, const Batch& b) {
+void sort_particles(dh_sim* s, const float* pos, const Batch& b, bool keep_ids = false) {
   dh::launch_keys(s->st, pos, s->bins.key, b);
-  dh::launch_sort(s->st, s->bins, pos, b);
+  dh::launch_sort(s->st, s->bins, pos, b, false, keep_ids);
 }
 
 // phi_out = Poisson solve of delta with the Green's factor of each sample's table entry
@@ -679,7 +679,7 @@ void do_step(dh_sim* s, const StepPlan& sp, TapeStep* tp, bool defer, int store_
       tp->vsorted = e.sorted;
       tp->vspos = e.spos;
     } else {
-      dh::launch_sort(s->st, s->bins, s->pos, b, true);
+      dh::launch_sort(s->st, s->bins, s->pos, b, true, true);
       potential_from_bins(s, tp->q[4], s->phi, s->g4, b);
       // the tape keeps this sort of x1 for the reverse pass; the next sort writes the tape's
       // former buffers
@@ -706,7 +706,7 @@ void do_step(dh_sim* s, const StepPlan& sp, TapeStep* tp, bool defer, int store_
       std::swap(s->q, s->q2);
     }
     // Poisson at a(t + dt) from gas + DM (keys and their histogram were made by the drift)
-    dh::launch_sort(s->st, s->bins, s->pos, b, true);
+    dh::launch_sort(s->st, s->bins, s->pos, b, true, store_k >= 0 || s->aux);
     potential_from_bins(s, s->q, s->phi, s->g4, b);
     // closing gas half kick with g_{n+1}, source term and the CFL maxima: one pass
     close_pass(s, s->q, nullptr, true, true, s->bins.spos, s->bins.sorted, b, closure);
@@ -1279,7 +1279,7 @@ void finish_first_kick(dh_sim* s, const TapeStep& T) {
   dh::launch_grad(st, T.phi0, s->g4b, b);
   s->g4b_phi0_of = -1;
   dh::launch_fill(st, s->lg, 0.0f, 3 * s->nc * s->S);
-  sort_particles(s, T.x0, b);
+  sort_particles(s, T.x0, b, true);
   dh::launch_gather_sorted(st, s->bins, s->lp, b);
   dh::launch_deposit_vec(st, s->bins, false, s->lg, b);
   dh::launch_kick_vjp_pos(st, s->g4b, T.x0, s->lp, false, s->lx, b);
@@ -1491,7 +1491,8 @@ int dh_create(const dh_config* cfg, dh_sim** out) {
     s->bins.count = s->alloc<uint32_t>(nc);
     s->bins.start = s->alloc<uint32_t>(nc + 1);
     s->bins.sorted = s->alloc<uint32_t>(np);
-    s->bins.block_sums = s->alloc<uint32_t>(static_cast<long long>(dh::scan_block_count(nc)) + 1);
+    s->bins.block_sums = s->alloc<uint32_t>(static_cast<long long>(dh::scan_block_count(nc)));
+    DH_HIP(hipMemset(s->bins.count, 0, static_cast<size_t>(nc) * sizeof(uint32_t)));
     s->bins.large = s->alloc<uint32_t>(1 + dh::large_bin_capacity(np));
     s->bins.spos = s->alloc<float4>(np);
     s->bins.sval = s->alloc<float4>(np);

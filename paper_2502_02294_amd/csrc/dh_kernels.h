@@ -67,7 +67,7 @@ void launch_sweep_vjp(hipStream_t st, const float* qin, const float* lam_out, fl
 struct Bins {          // counting sort of particles by CIC base cell
   uint32_t* key;       // [S np] bin of each particle
   uint32_t* rank;      // [S np] scratch: arrival rank inside its bin
-  uint32_t* count;     // [S nc]
+  uint32_t* count;     // [S nc], zero between sorts (a histogram starts from zeros)
   uint32_t* start;     // [S nc + 1] exclusive prefix sum of count
   uint32_t* sorted;    // [S np] particle ids, bins in order, ids ascending inside a bin
   uint32_t* block_sums;  // [scan blocks]
@@ -76,7 +76,7 @@ struct Bins {          // counting sort of particles by CIC base cell
   float4* sval;        // [S np] a particle vector field in bin order (adjoint deposits)
 };
 size_t scan_block_count(long long nbins);
-// entries of Bins::large for `total` particles (bins of more than 32 particles)
+// entries of Bins::large for `total` particles (bins of more than 256 particles)
 long long large_bin_capacity(long long total);
 void launch_keys(hipStream_t st, const float* pos, uint32_t* key, const Batch& b);
 // aux[id] += CIC read-out of znew at each particle (bin order: spos, sorted of the positions
@@ -84,9 +84,10 @@ void launch_keys(hipStream_t st, const float* pos, uint32_t* key, const Batch& b
 void launch_star_readout(hipStream_t st, const float* znew, const float4* spos,
                          const uint32_t* sorted, float* aux, const Batch& b);
 // sort by bins.key (already computed for pos) and gather pos into bin order; counted: the
-// histogram was made by launch_kick_drift (count_into)
+// histogram was made by launch_kick_drift (count_into); keep_ids: the ids, too, are wanted in
+// bin order (bins.sorted, for launch_gather_sorted and launch_star_readout)
 void launch_sort(hipStream_t st, const Bins& bins, const float* pos, const Batch& b,
-                 bool counted = false);
+                 bool counted, bool keep_ids);
 // bins.sval = v[3][np] (per sample) in bin order
 void launch_gather_sorted(hipStream_t st, const Bins& bins, const float* v, const Batch& b);
 // out = rho_gas + m_dm * CIC(sorted positions) + offset; rho_gas (sample s at
@@ -106,7 +107,7 @@ void launch_readout_g(hipStream_t st, const float4* g4, const float* pos, float*
 // (the same array for an update in place); optional copies of the new momenta and positions.
 // prev: first the previous step's closing kick (h_prev of the table), as launch_kick would.
 // count_into (optional, key == count_into->key): also the histogram of the following
-// launch_sort(..., counted = true) (count zeroed here, arrival ranks)
+// launch_sort(..., counted = true) (arrival ranks)
 void launch_kick_drift(hipStream_t st, const float4* g4, const float* pos_in, float* pos,
                        float* mom, uint32_t* key, float* mom_copy, float* pos_copy, bool prev,
                        const Batch& b, const Bins* count_into = nullptr);

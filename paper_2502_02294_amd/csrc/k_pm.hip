@@ -17,7 +17,7 @@ namespace dh {
 namespace {
 
 constexpr int kScanThreads = 256;
-constexpr int kLargeSortBlocks = 1024;
+constexpr int kLargeSortBlocks = 512;   // two blocks of 64 KB of LDS per CU
 constexpr int kScanPer = 16;
 constexpr int kScanTile = kScanThreads * kScanPer;
 
@@ -74,11 +74,6 @@ __global__ void keys_kernel(const float* __restrict__ pos, uint32_t* __restrict_
   key[blockIdx.y * np + i] = bin_of(c, n, blockIdx.y, np);
 }
 
-__global__ void fill_u32_kernel(uint32_t* p, uint32_t v, long long count) {
-  const long long i = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i < count) p[i] = v;
-}
-
 __global__ void hist_kernel(const uint32_t* __restrict__ key, uint32_t* count,
                             uint32_t* __restrict__ rank, long long np) {
   const long long i = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -121,72 +116,75 @@ __device__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* sh, uint32_t& tot
 // tile element e lives at LDS word e + e / kScanPer (padding breaks the 16-word stride)
 __device__ __forceinline__ int tile_slot(int e) { return e + e / kScanPer; }
 
-__global__ void __launch_bounds__(kScanThreads) scan_reduce_kernel(
-    const uint32_t* __restrict__ in, uint32_t* __restrict__ block_sums, long long count) {
-  __shared__ uint32_t sh[4];
-  const long long base = static_cast<long long>(blockIdx.x) * kScanTile;
-  uint32_t s = 0;
-  if (base + kScanTile <= count) {
-    // whole tile: 16-byte loads, consecutive threads on consecutive vectors
-    const uint4* in4 = reinterpret_cast<const uint4*>(in + base);
+__device__ __forceinline__ uint32_t wave_add(uint32_t v) {
 #pragma unroll
-    for (int k = 0; k < kScanPer / 4; ++k) {
-      const uint4 v = in4[k * kScanThreads + threadIdx.x];
-      s += v.x + v.y + v.z + v.w;
-    }
-  } else {
-    for (int k = 0; k < kScanPer; ++k) {
-      const long long e = base + k * kScanThreads + threadIdx.x;
-      if (e < count) s += in[e];
-    }
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  return v;
+}
+
+// sum of v over the block (every thread receives it); sh holds the four wave sums
+__device__ __forceinline__ uint32_t block_add(uint32_t v, uint32_t* sh) {
+  v = wave_add(v);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
   __syncthreads();
-  if (threadIdx.x == 0) block_sums[blockIdx.x] = sh[0] + sh[1] + sh[2] + sh[3];
+  const uint32_t t = sh[0] + sh[1] + sh[2] + sh[3];
+  __syncthreads();   // sh is free again on return
+  return t;
 }
 
-// Exclusive scan of the nb block sums in place, one workgroup: each thread takes kScanPer
-// consecutive sums per round of kScanTile.
-__global__ void __launch_bounds__(kScanThreads) scan_block_sums_kernel(uint32_t* sums, int nb) {
+// sums[t] = sum of the counts of tile t
+__global__ void __launch_bounds__(kScanThreads) scan_sums_kernel(const uint32_t* __restrict__ in,
+                                                                 uint32_t* __restrict__ sums) {
   __shared__ uint32_t sh[4];
-  uint32_t carry = 0;
-  for (int b0 = 0; b0 < nb; b0 += kScanTile) {
-    const int i0 = b0 + threadIdx.x * kScanPer;
-    uint32_t v[kScanPer];
-    uint32_t s = 0;
+  // 16-byte loads, consecutive threads on consecutive vectors
+  const uint4* in4 =
+      reinterpret_cast<const uint4*>(in + static_cast<long long>(blockIdx.x) * kScanTile);
+  uint32_t s = 0;
 #pragma unroll
-    for (int k = 0; k < kScanPer; ++k) {
-      v[k] = i0 + k < nb ? sums[i0 + k] : 0u;
-      s += v[k];
-    }
-    uint32_t total;
-    uint32_t run = carry + block_exclusive_scan(s, sh, total);
-#pragma unroll
-    for (int k = 0; k < kScanPer; ++k) {
-      if (i0 + k < nb) sums[i0 + k] = run;
-      run += v[k];
-    }
-    carry += total;
+  for (int k = 0; k < kScanPer / 4; ++k) {
+    const uint4 v = in4[k * kScanThreads + threadIdx.x];
+    s += v.x + v.y + v.z + v.w;
   }
+  const uint32_t t = block_add(s, sh);
+  if (threadIdx.x == 0) sums[blockIdx.x] = t;
 }
 
-__global__ void __launch_bounds__(kScanThreads) scan_final_kernel(
-    const uint32_t* __restrict__ in, const uint32_t* __restrict__ block_off,
-    uint32_t* __restrict__ out, long long count) {
+// Exclusive scan of the bin counts, one block per tile: out[0..tiles kScanTile] = prefix sums
+// and total.  What lies before its tile each block adds up itself: the tile sums (at most 4 of
+// 2^31 / 2^12 a thread at 256^3, from L2) or, for up to kScanDirect tiles (32^3), where another
+// launch would cost more than it saves, the counts.  Against a separate scan of the tile sums
+// that is one launch less and 256^3 takes 17 + 24 us instead of 17 + 5.5 + 24; a single pass
+// with look-back between the blocks took 79 us there (its polls cross the XCDs).
+// Also clears the list of large bins for the sort that follows.
+constexpr int kScanDirect = 8;
+
+__global__ void __launch_bounds__(kScanThreads) scan_kernel(const uint32_t* __restrict__ in,
+                                                            const uint32_t* __restrict__ sums,
+                                                            uint32_t* __restrict__ out, int tiles,
+                                                            uint32_t* __restrict__ large) {
   __shared__ uint32_t tile[kScanTile + kScanTile / kScanPer];
   __shared__ uint32_t sh[4];
-  const long long base = static_cast<long long>(blockIdx.x) * kScanTile;
+  const int t = blockIdx.x;
+  const long long base = static_cast<long long>(t) * kScanTile;
+  uint32_t part = 0;
+  if (sums) {
+    for (int i = threadIdx.x; i < t; i += kScanThreads) part += sums[i];
+  } else {
+    const uint4* all4 = reinterpret_cast<const uint4*>(in);
+    for (int i = threadIdx.x; i < t * (kScanTile / 4); i += kScanThreads) {
+      const uint4 v = all4[i];
+      part += v.x + v.y + v.z + v.w;
+    }
+  }
   for (int k = 0; k < kScanPer; ++k) {
     const int e = k * kScanThreads + threadIdx.x;
-    tile[tile_slot(e)] = base + e < count ? in[base + e] : 0u;
+    tile[tile_slot(e)] = in[base + e];
   }
-  __syncthreads();
+  const uint32_t before = block_add(part, sh);   // also orders the tile's LDS writes
   uint32_t s = 0;
   for (int k = 0; k < kScanPer; ++k) s += tile[tile_slot(threadIdx.x * kScanPer + k)];
   uint32_t total;
-  uint32_t run = block_exclusive_scan(s, sh, total) + block_off[blockIdx.x];
+  uint32_t run = block_exclusive_scan(s, sh, total) + before;
   for (int k = 0; k < kScanPer; ++k) {
     const int sl = tile_slot(threadIdx.x * kScanPer + k);
     const uint32_t v = tile[sl];
@@ -196,9 +194,12 @@ __global__ void __launch_bounds__(kScanThreads) scan_final_kernel(
   __syncthreads();
   for (int k = 0; k < kScanPer; ++k) {
     const int e = k * kScanThreads + threadIdx.x;
-    if (base + e < count) out[base + e] = tile[tile_slot(e)];
+    out[base + e] = tile[tile_slot(e)];
   }
-  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[count] = block_off[blockIdx.x] + total;
+  if (threadIdx.x == 0) {
+    if (t == tiles - 1) out[static_cast<long long>(tiles) * kScanTile] = before + total;
+    if (t == 0) large[0] = 0u;
+  }
 }
 
 __global__ void scatter_kernel(const uint32_t* __restrict__ key, const uint32_t* __restrict__ rank,
@@ -210,12 +211,19 @@ __global__ void scatter_kernel(const uint32_t* __restrict__ key, const uint32_t*
 }
 
 // The atomics above fix each bin's size but not the order inside it; sorting each bin's ids
-// ascending makes the layout a pure function of the keys.  A thread sorts a bin of up to 8
-// ids with a sorting network in registers, of up to kSmallBin ids by insertion; larger bins (dense halos gather thousands of particles in a
-// cell) go to a list that bin_sort_large_kernel sorts one workgroup per bin.  (Moving the
-// positions along with the ids, in place of the gather pass after the sort, was slower: the
-// scattered 16-byte writes cost more than the gather's scattered reads.)
-constexpr uint32_t kSmallBin = 32;
+// ascending makes the layout a pure function of the keys.  A wave takes 64 consecutive bins,
+// whose ids are one run of the list: it brings them to LDS, sorts every bin there (up to 8 ids
+// by a lane in registers, more by all lanes, counting for each id the smaller ones), writes
+// them back and gathers the positions, both coalesced over the run.  At 256^3 that is one pass
+// of 100 us early on, where a pass per bin and a gather after it took 45 + 101 us; in a
+// clustered state a lane alone sorted up to 32 ids through global memory (128^3 run to
+// a = 0.29: 54 + 21 us a step on average).  Runs longer than kWaveIds go in several parts;
+// bins of more than kWaveBin ids (dense halos gather thousands of particles in a cell) go to
+// a list that bin_sort_large_kernel sorts one workgroup per bin.  (Moving the positions along
+// with the ids in the scatter was slower: the scattered 16-byte writes cost more than the
+// gather's scattered reads.)
+constexpr uint32_t kWaveBin = 256;
+constexpr uint32_t kWaveIds = 512;
 constexpr int kLdsSort = 16384;   // ids a workgroup sorts in LDS (64 KB)
 
 // Batcher's odd-even merge network for 8 keys (19 compare-exchanges)
@@ -231,37 +239,108 @@ __device__ __forceinline__ void sort8(uint32_t (&v)[8]) {
   }
 }
 
-__global__ void bin_sort_kernel(const uint32_t* __restrict__ start, uint32_t* sorted,
-                                long long nbins, uint32_t* __restrict__ large) {
-  const long long b = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (b >= nbins) return;
+// position of particle id (global: sample id >> lnp) of per-sample [3][np] arrays
+__device__ __forceinline__ float4 gather3(const float* __restrict__ v, uint32_t id, int lnp) {
+  const long long np = 1LL << lnp;
+  const float* vs = v + (id >> lnp) * 3 * np;
+  const long long loc = id & (np - 1);
+  return make_float4(vs[loc], vs[np + loc], vs[2 * np + loc], 0.0f);
+}
+
+// orders the wave's LDS accesses (its lanes exchange ids through its own part of the LDS)
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// sorts the k <= 64 R ids at s ascending, all lanes of the wave: an id's place is the number
+// of smaller ones (ids are distinct)
+template <int R>
+__device__ __forceinline__ void wave_rank_sort(uint32_t* s, uint32_t k, int lane) {
+  uint32_t v[R], rank[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const uint32_t i = lane + 64 * r;
+    v[r] = i < k ? s[i] : 0u;
+    rank[r] = 0;
+  }
+#pragma unroll
+  for (int q = 0; q < R; ++q) {
+    const uint32_t n = k > 64u * q ? min(k - 64u * q, 64u) : 0u;
+    for (uint32_t j = 0; j < n; ++j) {
+      const uint32_t u = __builtin_amdgcn_readlane(v[q], j);
+#pragma unroll
+      for (int r = 0; r < R; ++r) rank[r] += u < v[r] ? 1u : 0u;
+    }
+  }
+  wave_sync();
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    if (lane + 64 * r < k) s[rank[r]] = v[r];
+}
+
+// (nbins is a multiple of 256.)  The counts are cleared for the next histogram.
+__global__ void __launch_bounds__(256) bin_sort_gather_kernel(const uint32_t* __restrict__ start,
+                                                              uint32_t* sorted,
+                                                              const float* __restrict__ pos,
+                                                              float4* __restrict__ spos, int lnp,
+                                                              uint32_t* __restrict__ count,
+                                                              uint32_t* __restrict__ large,
+                                                              bool keep_ids) {
+  __shared__ uint32_t ids[4][kWaveIds];
+  const int lane = threadIdx.x & 63;
+  uint32_t* my = ids[threadIdx.x >> 6];
+  const uint32_t b = blockIdx.x * 256u + threadIdx.x;
   const uint32_t lo = start[b], hi = start[b + 1];
   const uint32_t cnt = hi - lo;
-  if (cnt > kSmallBin) {
-    // large[0] counts the entries large[1..]; the list order does not affect the result
-    large[1 + atomicAdd(&large[0], 1u)] = static_cast<uint32_t>(b);
-    return;
-  }
-  if (cnt < 2) return;
-  if (cnt <= 8) {
-    // independent loads, a sorting network in registers (the padding sorts last)
-    uint32_t v[8];
-#pragma unroll
-    for (uint32_t i = 0; i < 8; ++i) v[i] = i < cnt ? sorted[lo + i] : 0xFFFFFFFFu;
-    sort8(v);
-#pragma unroll
-    for (uint32_t i = 0; i < 8; ++i)
-      if (i < cnt) sorted[lo + i] = v[i];
-    return;
-  }
-  for (uint32_t i = lo + 1; i < hi; ++i) {
-    const uint32_t v = sorted[i];
-    uint32_t j = i;
-    while (j > lo && sorted[j - 1] > v) {
-      sorted[j] = sorted[j - 1];
-      --j;
+  count[b] = 0;
+  uint32_t run = __builtin_amdgcn_readfirstlane(lo);   // ids before it are done
+  for (int first = 0; first < 64;) {
+    // the bins from `first` on that fit into LDS together
+    const uint64_t stop =
+        __ballot(lane >= first && (hi - run > kWaveIds || cnt > kWaveBin)) >> first;
+    const int fit = stop ? __builtin_ctzll(stop) : 64 - first;
+    if (fit == 0) {
+      // large[0] counts the entries large[1..]; the list order does not affect the result
+      if (lane == first) large[1 + atomicAdd(&large[0], 1u)] = b;
+      run = __shfl(hi, first, 64);
+      ++first;
+      continue;
     }
-    sorted[j] = v;
+    const uint32_t end = __shfl(hi, first + fit - 1, 64);
+    const uint32_t total = end - run;
+    for (uint32_t i = lane; i < total; i += 64) my[i] = sorted[run + i];
+    wave_sync();
+    const bool mine = lane >= first && lane < first + fit;
+    const uint32_t off = lo - run;
+    if (mine && cnt >= 2 && cnt <= 8) {
+      uint32_t v[8];
+#pragma unroll
+      for (uint32_t i = 0; i < 8; ++i) v[i] = i < cnt ? my[off + i] : 0xFFFFFFFFu;
+      sort8(v);
+#pragma unroll
+      for (uint32_t i = 0; i < 8; ++i)
+        if (i < cnt) my[off + i] = v[i];
+    }
+    for (uint64_t m = __ballot(mine && cnt > 8); m; m &= m - 1) {
+      const int l = __builtin_ctzll(m);
+      const uint32_t k = __shfl(cnt, l, 64);
+      uint32_t* s = my + __shfl(off, l, 64);
+      if (k <= 64)
+        wave_rank_sort<1>(s, k, lane);
+      else
+        wave_rank_sort<4>(s, k, lane);
+    }
+    wave_sync();
+    for (uint32_t i = lane; i < total; i += 64) {
+      const uint32_t id = my[i];
+      if (keep_ids) sorted[run + i] = id;
+      spos[run + i] = gather3(pos, id, lnp);
+    }
+    wave_sync();
+    run = end;
+    first += fit;
   }
 }
 
@@ -289,7 +368,9 @@ __device__ void bitonic_ascending(uint32_t k, uint32_t p, Get get, Put put) {
 
 __global__ void __launch_bounds__(256) bin_sort_large_kernel(const uint32_t* __restrict__ start,
                                                              uint32_t* sorted,
-                                                             const uint32_t* __restrict__ large) {
+                                                             const uint32_t* __restrict__ large,
+                                                             const float* __restrict__ pos,
+                                                             float4* __restrict__ spos, int lnp) {
   __shared__ uint32_t sh[kLdsSort];
   const uint32_t count = large[0];
   for (uint32_t e = blockIdx.x; e < count; e += gridDim.x) {
@@ -309,6 +390,8 @@ __global__ void __launch_bounds__(256) bin_sort_large_kernel(const uint32_t* __r
                         [&](uint32_t i, uint32_t v) { g[i] = v; });
     }
     __syncthreads();
+    for (uint32_t i = threadIdx.x; i < k; i += blockDim.x) spos[lo + i] = gather3(pos, g[i], lnp);
+    __syncthreads();
   }
 }
 
@@ -319,11 +402,7 @@ __global__ void gather_sorted_kernel(const uint32_t* __restrict__ sorted,
                                      long long total, int lnp) {
   const long long j = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (j >= total) return;
-  const uint32_t id = sorted[j];
-  const long long np = 1LL << lnp;
-  const long long smp = id >> lnp, loc = id & (np - 1);
-  const float* vs = v + smp * 3 * np;
-  out[j] = make_float4(vs[loc], vs[np + loc], vs[2 * np + loc], 0.0f);
+  out[j] = gather3(v, sorted[j], lnp);
 }
 
 // ---------------------------------------------------------------------------- deposit
@@ -942,7 +1021,7 @@ __global__ void __launch_bounds__(256) grad_vjp_kernel(const float* __restrict__
 
 }  // namespace
 
-long long large_bin_capacity(long long total) { return total / (kSmallBin + 1) + 1; }
+long long large_bin_capacity(long long total) { return total / (kWaveBin + 1) + 1; }
 
 size_t scan_block_count(long long nbins) {
   return static_cast<size_t>((nbins + kScanTile - 1) / kScanTile);
@@ -964,39 +1043,34 @@ void launch_keys(hipStream_t st, const float* pos, uint32_t* key, const Batch& b
 }
 
 void launch_sort(hipStream_t st, const Bins& bins, const float* pos, const Batch& b,
-                 bool counted) {
+                 bool counted, bool keep_ids) {
   const long long nbins = b.nc() * b.S, total = nbins;
+  const int lnp = log2_ll(b.nc());
   if (!counted) {
-    hipLaunchKernelGGL(fill_u32_kernel, dim3(blocks_for(nbins, 256)), dim3(256), 0, st,
-                       bins.count, 0u, nbins);
-    DH_LAUNCH_CHECK();
     hipLaunchKernelGGL(hist_kernel, dim3(blocks_for(total, 256)), dim3(256), 0, st, bins.key,
                        bins.count, bins.rank, total);
     DH_LAUNCH_CHECK();
   }
-  const int nb = static_cast<int>(scan_block_count(nbins));
-  hipLaunchKernelGGL(scan_reduce_kernel, dim3(nb), dim3(kScanThreads), 0, st, bins.count,
-                     bins.block_sums, nbins);
-  DH_LAUNCH_CHECK();
-  hipLaunchKernelGGL(scan_block_sums_kernel, dim3(1), dim3(kScanThreads), 0, st, bins.block_sums,
-                     nb);
-  DH_LAUNCH_CHECK();
-  hipLaunchKernelGGL(scan_final_kernel, dim3(nb), dim3(kScanThreads), 0, st, bins.count,
-                     bins.block_sums, bins.start, nbins);
+  // (n is a power of two, 16 or more: whole tiles)
+  const int tiles = static_cast<int>(scan_block_count(nbins));
+  const bool direct = tiles <= kScanDirect;
+  if (!direct) {
+    hipLaunchKernelGGL(scan_sums_kernel, dim3(tiles), dim3(kScanThreads), 0, st, bins.count,
+                       bins.block_sums);
+    DH_LAUNCH_CHECK();
+  }
+  hipLaunchKernelGGL(scan_kernel, dim3(tiles), dim3(kScanThreads), 0, st, bins.count,
+                     direct ? nullptr : bins.block_sums, bins.start, tiles, bins.large);
   DH_LAUNCH_CHECK();
   hipLaunchKernelGGL(scatter_kernel, dim3(blocks_for(total, 256)), dim3(256), 0, st, bins.key,
                      bins.rank, bins.start, bins.sorted, total);
   DH_LAUNCH_CHECK();
-  hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(256), 0, st, bins.large, 0u, 1LL);
-  DH_LAUNCH_CHECK();
-  hipLaunchKernelGGL(bin_sort_kernel, dim3(blocks_for(nbins, 256)), dim3(256), 0, st, bins.start,
-                     bins.sorted, nbins, bins.large);
+  hipLaunchKernelGGL(bin_sort_gather_kernel, dim3(static_cast<unsigned>(nbins / 256)), dim3(256), 0,
+                     st, bins.start, bins.sorted, pos, bins.spos, lnp, bins.count, bins.large,
+                     keep_ids);
   DH_LAUNCH_CHECK();
   hipLaunchKernelGGL(bin_sort_large_kernel, dim3(kLargeSortBlocks), dim3(256), 0, st, bins.start,
-                     bins.sorted, bins.large);
-  DH_LAUNCH_CHECK();
-  hipLaunchKernelGGL(gather_sorted_kernel, dim3(blocks_for(total, 256)), dim3(256), 0, st,
-                     bins.sorted, pos, bins.spos, total, log2_ll(b.nc()));
+                     bins.sorted, bins.large, pos, bins.spos, lnp);
   DH_LAUNCH_CHECK();
 }
 
@@ -1067,12 +1141,6 @@ void launch_kick_drift(hipStream_t st, const float4* g4, const float* pos_in, fl
   if (count_into && key != count_into->key) throw ArgError("kick_drift: keys of another sort");
   uint32_t* count = count_into ? count_into->count : nullptr;
   uint32_t* rank = count_into ? count_into->rank : nullptr;
-  if (count) {
-    const long long nbins = b.nc() * b.S;
-    hipLaunchKernelGGL(fill_u32_kernel, dim3(blocks_for(nbins, 256)), dim3(256), 0, st, count, 0u,
-                       nbins);
-    DH_LAUNCH_CHECK();
-  }
   hipLaunchKernelGGL(kick_drift_kernel, per_sample(b.nc(), b), dim3(256), 0, st, g4, pos_in, pos,
                      mom, key, mom_copy, pos_copy, b.n, b.nc(), prev ? 1 : 0, b.tab, count, rank);
   DH_LAUNCH_CHECK();
