@@ -4,11 +4,12 @@
 // Half spectrum layout: spec[(kz * n + ky) * nh + kx], nh = n/2 + 1, kx = 0..n/2.
 // Forward transforms are unnormalised; every spectral operator carries the 1/N^3 of the
 // inverse.  Passes:
-//   x_r2c     rows of n reals -> n/2+1 complex
-//   pencil<1> y lines (all (z, kx) lines of a sample, tk consecutive ones per block)
+//   plane_forward, plane_inverse   x and y lines of a z plane (n <= 128)
+//   x_r2c     rows of n reals -> n/2+1 complex (n = 256)
+//   pencil<1> y lines (all (z, kx) lines of a sample, tk consecutive ones per block; n = 256)
 //   pencil<2> z lines ((ky, kx) lines): forward, spectral operator, inverse, each optional,
 //             and optional accumulation into the output
-//   x_c2r     Hermitian extension of each row, inverse FFT, real part times a scale.
+//   x_c2r     Hermitian extension of each row, inverse FFT, real part times a scale (n = 256).
 //
 // Each n-point line transform is the four-step factorisation n = N1 * N2 with both factors
 // done in registers and one transpose through LDS:
@@ -97,31 +98,32 @@ __device__ __forceinline__ float2 tw_full(const float2* tw, int m, int n) {
 // The transpose of a line transform through this line's exchange buffer ex (n floats): the
 // writer thread q puts v[i] (i < NW) at [i WS + q], the reader thread q takes v[j] (j < NR)
 // from [q RS + j]; real parts first, then imaginary parts, so the buffer is half the size
-// of a complex one (more blocks per CU).  A caller that writes ex again needs a barrier first.
-template <int NW, int WS, int NR, int RS>
+// of a complex one (more blocks per CU).  Element e of the buffer is at ex[e ES].  A caller
+// that writes ex again needs a barrier first.
+template <int NW, int WS, int NR, int RS, int ES>
 __device__ __forceinline__ void exchange(float2 (&v)[kMaxR], float* ex, int q, bool writer,
                                          bool reader) {
   float re[kMaxR];
   if (writer)
 #pragma unroll
-    for (int i = 0; i < NW; ++i) ex[i * WS + q] = v[i].x;
+    for (int i = 0; i < NW; ++i) ex[(i * WS + q) * ES] = v[i].x;
   __syncthreads();
   if (reader)
 #pragma unroll
-    for (int j = 0; j < NR; ++j) re[j] = ex[q * RS + j];
+    for (int j = 0; j < NR; ++j) re[j] = ex[(q * RS + j) * ES];
   __syncthreads();
   if (writer)
 #pragma unroll
-    for (int i = 0; i < NW; ++i) ex[i * WS + q] = v[i].y;
+    for (int i = 0; i < NW; ++i) ex[(i * WS + q) * ES] = v[i].y;
   __syncthreads();
   if (reader)
 #pragma unroll
-    for (int j = 0; j < NR; ++j) v[j] = make_float2(re[j], ex[q * RS + j]);
+    for (int j = 0; j < NR; ++j) v[j] = make_float2(re[j], ex[(q * RS + j) * ES]);
 }
 
 // Forward line transform: D_x (thread q < N2 of the line) -> D_k (thread q < N1).
-// ex: this line's exchange buffer (n floats), tw: twiddle half table in LDS.
-template <int N1, int N2>
+// ex: this line's exchange buffer (n floats, ES apart), tw: twiddle half table in LDS.
+template <int N1, int N2, int ES = 1>
 __device__ __forceinline__ void line_forward(float2 (&v)[kMaxR], float* ex, const float2* tw,
                                              int q, bool in_x, bool in_k) {
   constexpr int n = N1 * N2;
@@ -130,12 +132,12 @@ __device__ __forceinline__ void line_forward(float2 (&v)[kMaxR], float* ex, cons
 #pragma unroll
     for (int k1 = 0; k1 < N1; ++k1) v[k1] = cmul(v[k1], tw_full(tw, q * k1, n));
   }
-  exchange<N1, N2, N2, N2>(v, ex, q, in_x, in_k);
+  exchange<N1, N2, N2, N2, ES>(v, ex, q, in_x, in_k);
   if (in_k) dft_reg<N2, false>(v);   // q = k1: DFT over j2 gives X[k1 + N1 k2]
 }
 
 // Inverse line transform: D_k (thread q < N1) -> D_x (thread q < N2), unnormalised.
-template <int N1, int N2>
+template <int N1, int N2, int ES = 1>
 __device__ __forceinline__ void line_inverse(float2 (&v)[kMaxR], float* ex, const float2* tw,
                                              int q, bool in_x, bool in_k) {
   constexpr int n = N1 * N2;
@@ -147,7 +149,7 @@ __device__ __forceinline__ void line_inverse(float2 (&v)[kMaxR], float* ex, cons
       v[a] = cmul(v[a], make_float2(w.x, -w.y));
     }
   }
-  exchange<N2, N1, N1, N1>(v, ex, q, in_k, in_x);
+  exchange<N2, N1, N1, N1, ES>(v, ex, q, in_k, in_x);
   if (in_x) dft_reg<N1, true>(v);   // q = a: inverse DFT over k1 gives x[a + N2 b]
 }
 
@@ -232,6 +234,130 @@ __global__ void __launch_bounds__(kFftThreads) x_c2r_kernel(const float2* __rest
     float* dst = out + smp * out_stride + (row - smp * nn) * n;
 #pragma unroll
     for (int b = 0; b < N1; ++b) dst[q + N2 * b] = v[b].x * scale;
+  }
+}
+
+// -------------------------------------------------------------------------- plane passes
+// The x and y passes of one z plane in one block (n <= 128): the half spectrum of the plane (up
+// to 66 KB) stays in LDS between them, and each line's exchange buffer is its own row (or the
+// real parts of its own column) of it.  The transforms and their values are those of separate
+// x and y passes.  Rounds of the block cover the lines; 1024 threads, since a single sample has
+// only n blocks.  Latency binds it (64 of 256 CUs at 64^3), and 128^3 has half the chip; the
+// gain is a launch and a round trip of the spectrum per direction.  us, forward and inverse,
+// against the separate passes: 32^3 3.8 + 3.5 (6.7 + 6.4), 64^3 5.2 + 5.2 (7.5 + 7.5), 128^3
+// 17.2 + 14.2 (18.1 + 15.0; 18.6 + 15.9 with 512 threads).
+template <int N1, int N2>
+struct Plane {
+  static constexpr int n = N1 * N2, nh = n / 2 + 1;
+  static constexpr int R = N1 > N2 ? N1 : N2;
+  static constexpr int threads = n * R < 1024 ? n * R : 1024;
+  static constexpr int tk = threads / R;                  // lines per round
+  static constexpr int xrounds = n / tk;                  // n is a multiple of tk
+  static constexpr int yrounds = (nh + tk - 1) / tk;
+};
+
+template <int N1, int N2>
+__global__ void __launch_bounds__((Plane<N1, N2>::threads)) plane_forward_kernel(
+    const float* __restrict__ in, float2* __restrict__ spec, const float2* __restrict__ tw,
+    const StepScal* __restrict__ tab, long long in_stride) {
+  using P = Plane<N1, N2>;
+  constexpr int n = P::n, nh = P::nh;
+  __shared__ float2 H[n * nh];
+  __shared__ float2 TW[n / 2];
+  if (!sample_active(tab, blockIdx.y)) return;
+  load_tw(TW, tw, n);
+  const float* src = in + blockIdx.y * in_stride + static_cast<long long>(blockIdx.x) * n * n;
+  float2 v[kMaxR];
+  {
+    const int q = threadIdx.x % P::R, r = threadIdx.x / P::R;
+    const bool in_x = q < N2, in_k = q < N1;
+#pragma unroll 1
+    for (int k = 0; k < P::xrounds; ++k) {
+      const int row = k * P::tk + r;
+      if (in_x)
+#pragma unroll
+        for (int j1 = 0; j1 < N1; ++j1) v[j1] = make_float2(src[row * n + q + N2 * j1], 0.0f);
+      __syncthreads();
+      line_forward<N1, N2>(v, reinterpret_cast<float*>(H + row * nh), TW, q, in_x, in_k);
+      __syncthreads();   // the row has been read: it takes the spectrum now
+      if (in_k)
+#pragma unroll
+        for (int k2 = 0; k2 < N2; ++k2) {
+          const int kx = q + N1 * k2;
+          if (kx < nh) H[row * nh + kx] = v[k2];
+        }
+    }
+  }
+  __syncthreads();
+  float2* dst = spec + (static_cast<long long>(blockIdx.y) * n + blockIdx.x) * n * nh;
+  {
+    const int li = threadIdx.x % P::tk, q = threadIdx.x / P::tk;
+#pragma unroll 1
+    for (int k = 0; k < P::yrounds; ++k) {
+      const int kx = k * P::tk + li;
+      const bool in_x = kx < nh && q < N2, in_k = kx < nh && q < N1;
+      if (in_x)
+#pragma unroll
+        for (int r = 0; r < N1; ++r) v[r] = H[(q + N2 * r) * nh + kx];
+      __syncthreads();
+      line_forward<N1, N2, 2 * nh>(v, reinterpret_cast<float*>(H + kx), TW, q, in_x, in_k);
+      if (in_k)
+#pragma unroll
+        for (int r = 0; r < N2; ++r) dst[(q + N1 * r) * nh + kx] = v[r];
+    }
+  }
+}
+
+template <int N1, int N2>
+__global__ void __launch_bounds__((Plane<N1, N2>::threads)) plane_inverse_kernel(
+    const float2* __restrict__ spec, float* __restrict__ out, const float2* __restrict__ tw,
+    float scale, const StepScal* __restrict__ tab, long long out_stride) {
+  using P = Plane<N1, N2>;
+  constexpr int n = P::n, nh = P::nh;
+  __shared__ float2 H[n * nh];
+  __shared__ float2 TW[n / 2];
+  if (!sample_active(tab, blockIdx.y)) return;
+  load_tw(TW, tw, n);
+  const float2* src = spec + (static_cast<long long>(blockIdx.y) * n + blockIdx.x) * n * nh;
+  float2 v[kMaxR];
+  {
+    const int li = threadIdx.x % P::tk, q = threadIdx.x / P::tk;
+#pragma unroll 1
+    for (int k = 0; k < P::yrounds; ++k) {
+      const int kx = k * P::tk + li;
+      const bool in_x = kx < nh && q < N2, in_k = kx < nh && q < N1;
+      if (in_k)
+#pragma unroll
+        for (int r = 0; r < N2; ++r) v[r] = src[(q + N1 * r) * nh + kx];
+      __syncthreads();
+      line_inverse<N1, N2, 2 * nh>(v, reinterpret_cast<float*>(H + kx), TW, q, in_x, in_k);
+      __syncthreads();
+      if (in_x)
+#pragma unroll
+        for (int r = 0; r < N1; ++r) H[(q + N2 * r) * nh + kx] = v[r];
+    }
+  }
+  __syncthreads();
+  {
+    const int q = threadIdx.x % P::R, r = threadIdx.x / P::R;
+    const bool in_x = q < N2, in_k = q < N1;
+    float* dst = out + blockIdx.y * out_stride + static_cast<long long>(blockIdx.x) * n * n;
+#pragma unroll 1
+    for (int k = 0; k < P::xrounds; ++k) {
+      const int row = k * P::tk + r;
+      if (in_k)
+#pragma unroll
+        for (int k2 = 0; k2 < N2; ++k2) {   // Hermitian extension X[n - k] = conj(X[k])
+          const int kx = q + N1 * k2;
+          const float2 w = H[row * nh + (kx < nh ? kx : n - kx)];
+          v[k2] = kx < nh ? w : make_float2(w.x, -w.y);
+        }
+      __syncthreads();
+      line_inverse<N1, N2>(v, reinterpret_cast<float*>(H + row * nh), TW, q, in_x, in_k);
+      if (in_x)
+#pragma unroll
+        for (int b = 0; b < N1; ++b) dst[row * n + q + N2 * b] = v[b].x * scale;
+    }
   }
 }
 
@@ -401,29 +527,26 @@ __global__ void __launch_bounds__(kFftThreads) pencil_kernel(const float2* in, f
   }
 }
 
-template <int N1, int N2, int OPK>
-void pencil_op(hipStream_t st, int ax, const float2* in, float2* out, const float2* tw,
-               int flags, const OpArgs& op, const Batch& b) {
+template <int AX, int N1, int N2, int OPK>
+void pencil_op(hipStream_t st, const float2* in, float2* out, const float2* tw, int flags,
+               const OpArgs& op, const Batch& b) {
   using L = Lines<N1, N2>;
   constexpr int n = L::n, nh = n / 2 + 1;
   const dim3 grid((n * nh + L::tk - 1) / L::tk, b.S);
-  if (ax == 1)
-    hipLaunchKernelGGL((pencil_kernel<1, N1, N2, OPK>), grid, dim3(kFftThreads), 0, st, in, out,
-                       tw, flags, op, b.tab);
-  else
-    hipLaunchKernelGGL((pencil_kernel<2, N1, N2, OPK>), grid, dim3(kFftThreads), 0, st, in, out,
-                       tw, flags, op, b.tab);
+  hipLaunchKernelGGL((pencil_kernel<AX, N1, N2, OPK>), grid, dim3(kFftThreads), 0, st, in, out, tw,
+                     flags, op, b.tab);
 }
 
+// z pass
 template <int N1, int N2>
-void pencil_n(hipStream_t st, int ax, const float2* in, float2* out, const float2* tw, int flags,
+void pencil_n(hipStream_t st, const float2* in, float2* out, const float2* tw, int flags,
               const OpArgs& op, const Batch& b) {
   if (!(flags & 2) || op.op < 0)
-    pencil_op<N1, N2, 0>(st, ax, in, out, tw, flags & ~2, op, b);
+    pencil_op<2, N1, N2, 0>(st, in, out, tw, flags & ~2, op, b);
   else if (op.op == kOpGreen)
-    pencil_op<N1, N2, 1>(st, ax, in, out, tw, flags, op, b);
+    pencil_op<2, N1, N2, 1>(st, in, out, tw, flags, op, b);
   else
-    pencil_op<N1, N2, 2>(st, ax, in, out, tw, flags, op, b);
+    pencil_op<2, N1, N2, 2>(st, in, out, tw, flags, op, b);
 }
 
 template <int N1, int N2>
@@ -444,23 +567,46 @@ void c2r_n(hipStream_t st, const float2* spec, float* out, const float2* tw, flo
                      dim3(kFftThreads), 0, st, spec, out, tw, scale, b.tab, out_stride);
 }
 
-// n = N1 * N2 with N1 >= N2, both at most 16
-#define DH_FFT_DISPATCH(n, CALL)                                  \
+template <int N1, int N2>
+void plane_forward_n(hipStream_t st, const float* in, float2* spec, const float2* tw,
+                     const Batch& b, long long in_stride) {
+  hipLaunchKernelGGL((plane_forward_kernel<N1, N2>), dim3(N1 * N2, b.S),
+                     dim3(Plane<N1, N2>::threads), 0, st, in, spec, tw, b.tab, in_stride);
+}
+
+template <int N1, int N2>
+void plane_inverse_n(hipStream_t st, const float2* spec, float* out, const float2* tw, float scale,
+                     const Batch& b, long long out_stride) {
+  hipLaunchKernelGGL((plane_inverse_kernel<N1, N2>), dim3(N1 * N2, b.S),
+                     dim3(Plane<N1, N2>::threads), 0, st, spec, out, tw, scale, b.tab, out_stride);
+}
+
+// n = N1 * N2 with N1 >= N2, both at most 16.  BIG: n = 256, whose planes (264 KB of half
+// spectrum) exceed the LDS, so its x and y passes are separate.
+#define DH_FFT_DISPATCH(n, CALL, BIG)                             \
   switch (n) {                                                    \
     case 16: CALL(4, 4); break;                                   \
     case 32: CALL(8, 4); break;                                   \
     case 64: CALL(8, 8); break;                                   \
     case 128: CALL(16, 8); break;                                 \
-    case 256: CALL(16, 16); break;                                \
+    case 256: BIG(16, 16); break;                                 \
     default: throw ArgError("fft: n must be a power of two in [16, 256]"); \
   }
 
-void pencil(hipStream_t st, int ax, const float2* in, float2* out, const float2* tw, int flags,
+void pencil(hipStream_t st, const float2* in, float2* out, const float2* tw, int flags,
             const OpArgs& op, const Batch& b) {
-#define DH_CALL(a, c) pencil_n<a, c>(st, ax, in, out, tw, flags, op, b)
-  DH_FFT_DISPATCH(b.n, DH_CALL)
+#define DH_CALL(a, c) pencil_n<a, c>(st, in, out, tw, flags, op, b)
+  DH_FFT_DISPATCH(b.n, DH_CALL, DH_CALL)
 #undef DH_CALL
   DH_LAUNCH_CHECK();
+}
+
+// y pass in place (flags 1 forward, 4 inverse)
+template <int N1, int N2>
+void y_pass(hipStream_t st, float2* spec, const float2* tw, int flags, const Batch& b) {
+  OpArgs none{};
+  none.op = -1;
+  pencil_op<1, N1, N2, 0>(st, spec, spec, tw, flags, none, b);
 }
 
 }  // namespace
@@ -476,24 +622,28 @@ void fft_make_twiddles(int n, std::vector<float2>& tw) {
 void fft_forward_xy(hipStream_t st, const float* in, float2* spec, const float2* tw,
                     const Batch& b, long long in_stride) {
   const long long is = in_stride < 0 ? b.nc() : in_stride;
-#define DH_CALL(a, c) r2c_n<a, c>(st, in, spec, tw, b, is)
-  DH_FFT_DISPATCH(b.n, DH_CALL)
-#undef DH_CALL
+#define DH_PLANE(a, c) plane_forward_n<a, c>(st, in, spec, tw, b, is)
+#define DH_PASSES(a, c)                 \
+  r2c_n<a, c>(st, in, spec, tw, b, is); \
+  DH_LAUNCH_CHECK();                    \
+  y_pass<a, c>(st, spec, tw, 1, b)
+  DH_FFT_DISPATCH(b.n, DH_PLANE, DH_PASSES)
+#undef DH_PASSES
+#undef DH_PLANE
   DH_LAUNCH_CHECK();
-  OpArgs none{};
-  none.op = -1;
-  pencil(st, 1, spec, spec, tw, 1, none, b);
 }
 
 void fft_inverse_yx(hipStream_t st, float2* spec, float* out, const float2* tw, float scale,
                     const Batch& b, long long out_stride) {
-  OpArgs none{};
-  none.op = -1;
-  pencil(st, 1, spec, spec, tw, 4, none, b);
   const long long os = out_stride < 0 ? b.nc() : out_stride;
-#define DH_CALL(a, c) c2r_n<a, c>(st, spec, out, tw, scale, b, os)
-  DH_FFT_DISPATCH(b.n, DH_CALL)
-#undef DH_CALL
+#define DH_PLANE(a, c) plane_inverse_n<a, c>(st, spec, out, tw, scale, b, os)
+#define DH_PASSES(a, c)           \
+  y_pass<a, c>(st, spec, tw, 4, b); \
+  DH_LAUNCH_CHECK();              \
+  c2r_n<a, c>(st, spec, out, tw, scale, b, os)
+  DH_FFT_DISPATCH(b.n, DH_PLANE, DH_PASSES)
+#undef DH_PASSES
+#undef DH_PLANE
   DH_LAUNCH_CHECK();
 }
 
@@ -501,20 +651,20 @@ void fft_zpass_green(hipStream_t st, float2* spec, const float2* tw, const Batch
   if (!b.tab) throw ArgError("Poisson pass: step table required");
   OpArgs o{};
   o.op = kOpGreen;
-  pencil(st, 2, spec, spec, tw, 1 | 2 | 4, o, b);
+  pencil(st, spec, spec, tw, 1 | 2 | 4, o, b);
 }
 
 void fft_zpass_forward(hipStream_t st, const float2* in, float2* out, const float2* tw,
                        const Batch& b) {
   OpArgs none{};
   none.op = -1;
-  pencil(st, 2, in, out, tw, 1, none, b);
+  pencil(st, in, out, tw, 1, none, b);
 }
 
 void fft_zpass_inverse(hipStream_t st, float2* spec, const float2* tw, const Batch& b) {
   OpArgs none{};
   none.op = -1;
-  pencil(st, 2, spec, spec, tw, 4, none, b);
+  pencil(st, spec, spec, tw, 4, none, b);
 }
 
 // IC operators on the z pass (see apply_op): out = op(in), forward z transform first and
@@ -537,7 +687,7 @@ void fft_zpass_ic(hipStream_t st, const float2* in, float2* out, const float2* t
   o.eh_alpha = static_cast<float>(op.eh_alpha);
   o.eh_ks = static_cast<float>(op.eh_ks);
   const int flags = (forward_first ? 1 : 0) | 2 | (inverse_after ? 4 : 0) | (accumulate ? 8 : 0);
-  pencil(st, 2, in, out, tw, flags, o, b);
+  pencil(st, in, out, tw, flags, o, b);
 }
 
 }  // namespace dh
