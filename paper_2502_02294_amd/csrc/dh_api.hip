@@ -142,7 +142,8 @@ struct dh_sim {
   std::vector<double> speed;
   double* red = nullptr;       // block partials
   double* red_out = nullptr;   // reduced values
-  double* host_out = nullptr;  // pinned
+  dh::HostValue* host_out = nullptr;  // pinned: values the device hands to the waiting host
+  uint64_t host_seq = 0;              // sequence number of the last hand-over
   double* d_acur = nullptr;    // scale factor of each sample (CFL recomputation)
   int red_blocks = 0;
 
@@ -152,6 +153,7 @@ struct dh_sim {
   // (device [tab_cap][S]), which (slot, sample) pairs were replayed, and the first slot not
   // yet checked
   double* speed_log = nullptr;
+  double* host_log = nullptr;   // pinned [tab_cap][S]
   std::vector<double> replayed;   // [tab_cap][S]: the replayed dt, 0 for a CFL step
   int checked_slots = 0;
   StepScal* htabs = nullptr;   // pinned mirror
@@ -161,7 +163,7 @@ struct dh_sim {
   StepScal* stage_tab = nullptr;  // single entry for the stage calls
   StepScal stage_last{};          // what stage_tab holds (valid once uploaded)
   bool stage_valid = false;
-  StepScal* hstage = nullptr;     // pinned staging of cur_tab / stage_tab
+  StepScal* hstage = nullptr;     // pinned staging of uploads too large for a launch
 
   // adjoint buffers
   float *lq = nullptr, *lq2 = nullptr, *lx = nullptr, *lp = nullptr,
@@ -173,6 +175,7 @@ struct dh_sim {
   const float* open_q0 = nullptr;
   const StepScal* open_tab = nullptr;
   double* param_steps = nullptr;   // [cap][2 S] per-step dL/d(eps_sf, delta_c)
+  double* host_params = nullptr;   // pinned: the loss's 2 S sums, then the steps used
   int param_cap = 0;
 
   // learned closure: flat weights and their packed matrix-core form
@@ -298,6 +301,40 @@ dh::HydroK hydro_at(const dh_sim* s, double a) {
 
 void sync(dh_sim* s) { DH_HIP(hipStreamSynchronize(s->st)); }
 
+// Small uploads from ordinary host memory, on the stream; staged through pinned memory (which
+// must be free again first) where they exceed a launch's arguments.
+void upload(dh_sim* s, void* dst, const void* src, size_t bytes) {
+  if (dh::launch_upload(s->st, dst, src, bytes)) return;
+  sync(s);
+  std::memcpy(s->hstage, src, bytes);
+  DH_HIP(hipMemcpyAsync(dst, s->hstage, bytes, hipMemcpyHostToDevice, s->st));
+}
+
+// out[v] = reduction over in[v * stride + 0..count), v < nvec <= 2 S + 16, returned to the host.  The
+// kernel writes the values into pinned memory and the host watches for them, which returns a
+// few us after the kernel, where a copy and a wait for the stream take some 20 us more (a CFL
+// step needs its speed before the next one can be planned).  Everything enqueued before has
+// finished when this returns.
+void reduce_to_host(dh_sim* s, const double* in, int count, int stride, int nvec, bool max,
+                    double* out) {
+  const uint64_t seq = ++s->host_seq;
+  dh::launch_reduce_to_host(s->st, in, count, stride, nvec, max, s->host_out, seq);
+  for (int v = 0; v < nvec; ++v) {
+    const dh::HostValue* h = s->host_out + v;
+    for (int spin = 1; __atomic_load_n(&h->seq, __ATOMIC_ACQUIRE) != seq; ++spin) {
+      if (spin % (1 << 16) != 0) continue;
+      // still not there: has the stream failed, or drained without it?
+      const hipError_t e = hipStreamQuery(s->st);
+      (void)hipGetLastError();
+      if (e == hipErrorNotReady) continue;
+      if (e != hipSuccess) throw HipError(std::string("reduction: ") + hipGetErrorString(e));
+      if (__atomic_load_n(&h->seq, __ATOMIC_ACQUIRE) != seq)
+        throw HipError("reduction: the device's value did not arrive");
+    }
+    out[v] = h->value;
+  }
+}
+
 Batch batch(const dh_sim* s, const StepScal* tab) { return Batch{s->n, s->S, tab, s->nq}; }
 
 float green_at(const dh_sim* s, double a) {
@@ -370,6 +407,11 @@ void ensure_tab_slots(dh_sim* s, int slots) {
   DH_HIP(hipHostMalloc(&hp, static_cast<size_t>(cap) * s->S * sizeof(StepScal),
                        hipHostMallocDefault));
   StepScal* h = static_cast<StepScal*>(hp);
+  if (s->host_log) (void)hipHostFree(s->host_log);
+  s->host_log = nullptr;
+  DH_HIP(hipHostMalloc(&hp, static_cast<size_t>(cap) * s->S * sizeof(double),
+                       hipHostMallocDefault));
+  s->host_log = static_cast<double*>(hp);
   if (s->tabs) {
     const size_t bytes = static_cast<size_t>(s->tab_cap) * s->S * sizeof(StepScal);
     DH_HIP(hipMemcpy(d, s->tabs, bytes, hipMemcpyDeviceToDevice));
@@ -393,9 +435,10 @@ void upload_plan(dh_sim* s, const StepPlan& sp) {
   ensure_tab_slots(s, sp.slot + 1);
   StepScal* h = s->htabs + static_cast<size_t>(sp.slot) * s->S;
   for (int i = 0; i < s->S; ++i) h[i] = entry_of(s, i, sp.smp[i], sp.step);
-  DH_HIP(hipMemcpyAsync(s->tabs + static_cast<size_t>(sp.slot) * s->S, h,
-                        static_cast<size_t>(s->S) * sizeof(StepScal), hipMemcpyHostToDevice,
-                        s->st));
+  StepScal* d = s->tabs + static_cast<size_t>(sp.slot) * s->S;
+  const size_t bytes = static_cast<size_t>(s->S) * sizeof(StepScal);
+  if (!dh::launch_upload(s->st, d, h, bytes))
+    DH_HIP(hipMemcpyAsync(d, h, bytes, hipMemcpyHostToDevice, s->st));
 }
 
 const StepScal* tab_of(const dh_sim* s, const StepPlan& sp) {
@@ -403,30 +446,26 @@ const StepScal* tab_of(const dh_sim* s, const StepPlan& sp) {
 }
 
 // Table of the current state: every sample active at its own scale factor (Poisson green).
-// The staging buffer is reused only after the stream has drained.
 const StepScal* state_table(dh_sim* s) {
-  sync(s);
+  std::vector<StepScal> tab(s->S);
   for (int i = 0; i < s->S; ++i) {
     StepScal e{};
     e.active = 1;
     e.green = green_at(s, s->a[i]);
     e.h1 = e.h2 = hydro_at(s, s->a[i]);
     e.src = source_args(s, i, s->a[i], 0.0, s->step);
-    s->hstage[i] = e;
+    tab[i] = e;
   }
-  DH_HIP(hipMemcpyAsync(s->cur_tab, s->hstage, static_cast<size_t>(s->S) * sizeof(StepScal),
-                        hipMemcpyHostToDevice, s->st));
+  upload(s, s->cur_tab, tab.data(), static_cast<size_t>(s->S) * sizeof(StepScal));
   return s->cur_tab;
 }
 
 // Single entry for the stage calls (layout of one sample).  Repeated calls with the same
-// entry reuse the device copy: no drain of the stream and no upload between their launches.
+// entry reuse the device copy: no upload between their launches.
 const StepScal* stage_table(dh_sim* s, const StepScal& e) {
   if (s->stage_valid && std::memcmp(&s->stage_last, &e, sizeof(StepScal)) == 0)
     return s->stage_tab;
-  sync(s);
-  s->hstage[0] = e;
-  DH_HIP(hipMemcpyAsync(s->stage_tab, s->hstage, sizeof(StepScal), hipMemcpyHostToDevice, s->st));
+  upload(s, s->stage_tab, &e, sizeof(StepScal));
   s->stage_last = e;
   s->stage_valid = true;
   return s->stage_tab;
@@ -435,15 +474,14 @@ const StepScal* stage_table(dh_sim* s, const StepScal& e) {
 // Applies the deferred closing kicks (same arithmetic as the kick at the end of a step).
 void flush_kick(dh_sim* s) {
   if (!s->kick_pending) return;
-  sync(s);
+  std::vector<StepScal> tab(s->S);
   for (int i = 0; i < s->S; ++i) {
     StepScal e{};
     e.active = s->kick_due[i] != 0.0f ? 1 : 0;
     e.h_close = s->kick_due[i];
-    s->hstage[i] = e;
+    tab[i] = e;
   }
-  DH_HIP(hipMemcpyAsync(s->cur_tab, s->hstage, static_cast<size_t>(s->S) * sizeof(StepScal),
-                        hipMemcpyHostToDevice, s->st));
+  upload(s, s->cur_tab, tab.data(), static_cast<size_t>(s->S) * sizeof(StepScal));
   dh::launch_kick(s->st, s->g4, s->pos, s->mom, Batch{s->n, s->S, s->cur_tab, s->nq});
   std::fill(s->kick_due.begin(), s->kick_due.end(), 0.0f);
   s->kick_pending = false;
@@ -584,18 +622,12 @@ const std::vector<double>& current_speed(dh_sim* s) {
   if (s->speed_known) return s->speed;
   const int nb = dh::cfl_blocks(s->n);
   if (!s->cfl_partials) {
-    sync(s);
-    std::memcpy(s->host_out, s->a.data(), s->S * sizeof(double));
-    DH_HIP(hipMemcpyAsync(s->d_acur, s->host_out, s->S * sizeof(double), hipMemcpyHostToDevice,
-                          s->st));
+    upload(s, s->d_acur, s->a.data(), s->S * sizeof(double));
     dh::launch_cfl_partial(s->st, s->q, s->d_acur, s->cfg.gamma, s->e_floor, s->cfl_red,
                            batch(s, nullptr));
   }
-  dh::launch_reduce_max(s->st, s->cfl_red, nb, nb, s->S, s->red_out);
-  DH_HIP(hipMemcpyAsync(s->host_out, s->red_out, s->S * sizeof(double), hipMemcpyDeviceToHost,
-                        s->st));
-  sync(s);
-  s->speed.assign(s->host_out, s->host_out + s->S);
+  s->speed.resize(s->S);
+  reduce_to_host(s, s->cfl_red, nb, nb, s->S, true, s->speed.data());
   s->speed_known = true;
   s->cfl_partials = true;
   return s->speed;
@@ -846,10 +878,7 @@ void initial_conditions(dh_sim* s, const float* d_white) {
 // schedule is used up (with stop_at_replay_end), sits out.  *any = whether a sample moves.
 // the current scale factor of every sample into d_acur
 void upload_scale_factors(dh_sim* s) {
-  sync(s);
-  std::memcpy(s->host_out, s->a.data(), s->S * sizeof(double));
-  DH_HIP(hipMemcpyAsync(s->d_acur, s->host_out, s->S * sizeof(double), hipMemcpyHostToDevice,
-                        s->st));
+  upload(s, s->d_acur, s->a.data(), s->S * sizeof(double));
 }
 
 // Mode counts W_b (full spectrum) of bins 1..nbins of the rounded |m|: host, exact, cached.
@@ -994,10 +1023,7 @@ void log_replay_speed(dh_sim* s, const StepPlan& sp) {
   if (!any || !(s->cfg.cfl_forward > 0.0)) return;
   const int nb = dh::cfl_blocks(s->n);
   if (!s->cfl_partials) {
-    sync(s);
-    std::memcpy(s->host_out, s->a.data(), s->S * sizeof(double));
-    DH_HIP(hipMemcpyAsync(s->d_acur, s->host_out, s->S * sizeof(double), hipMemcpyHostToDevice,
-                          s->st));
+    upload(s, s->d_acur, s->a.data(), s->S * sizeof(double));
     dh::launch_cfl_partial(s->st, s->q, s->d_acur, s->cfg.gamma, s->e_floor, s->cfl_red,
                            batch(s, nullptr));
     s->cfl_partials = true;
@@ -1017,8 +1043,8 @@ int check_replay(dh_sim* s) {
   bool any = false;
   for (size_t k = from * S; k < to * S; ++k) any = any || s->replayed[k] > 0.0;
   if (!any) return DH_OK;
-  std::vector<double> v((to - from) * S);
-  DH_HIP(hipMemcpyAsync(v.data(), s->speed_log + from * S, v.size() * sizeof(double),
+  const double* v = s->host_log;
+  DH_HIP(hipMemcpyAsync(s->host_log, s->speed_log + from * S, (to - from) * S * sizeof(double),
                         hipMemcpyDeviceToHost, s->st));
   sync(s);
   for (int k = from; k < to; ++k)
@@ -1511,8 +1537,10 @@ int dh_create(const dh_config* cfg, dh_sim** out) {
       s->mlp_packed = s->alloc<uint4>(static_cast<long long>(dh::mlp::kPackedBytes / sizeof(uint4)));
     }
     void* hp = nullptr;
-    DH_HIP(hipHostMalloc(&hp, (8 * S + 16) * sizeof(double), hipHostMallocDefault));
-    s->host_out = static_cast<double*>(hp);
+    const size_t words = (2 * static_cast<size_t>(S) + 16) * sizeof(dh::HostValue);
+    DH_HIP(hipHostMalloc(&hp, words, hipHostMallocCoherent));
+    std::memset(hp, 0, words);
+    s->host_out = static_cast<dh::HostValue*>(hp);
     DH_HIP(hipHostMalloc(&hp, S * sizeof(StepScal), hipHostMallocDefault));
     s->hstage = static_cast<StepScal*>(hp);
     std::vector<float2> tw;
@@ -1538,6 +1566,8 @@ int dh_destroy(dh_sim* s) {
   for (void* p : s->allocs) (void)hipFree(p);
   if (s->host_out) (void)hipHostFree(s->host_out);
   if (s->hstage) (void)hipHostFree(s->hstage);
+  if (s->host_log) (void)hipHostFree(s->host_log);
+  if (s->host_params) (void)hipHostFree(s->host_params);
   if (s->htabs) (void)hipHostFree(s->htabs);
   delete s;
   return DH_OK;
@@ -1882,11 +1912,8 @@ int dh_loss(dh_sim* s, const float* d_target, double* loss_out) {
     const int nb = dh::cfl_blocks(s->n);
     dh::launch_loss_partial(s->st, s->q, d_target, s->prm.A, s->prm.beta,
                             static_cast<float>(1.0 / s->f_b), s->red, batch(s, nullptr));
-    dh::launch_reduce_sum(s->st, s->red, nb, nb, s->S, s->red_out);
-    DH_HIP(hipMemcpyAsync(s->host_out, s->red_out, s->S * sizeof(double), hipMemcpyDeviceToHost,
-                          s->st));
-    sync(s);
-    for (int i = 0; i < s->S; ++i) loss_out[i] = s->host_out[i] / static_cast<double>(s->nc);
+    reduce_to_host(s, s->red, nb, nb, s->S, false, loss_out);
+    for (int i = 0; i < s->S; ++i) loss_out[i] /= static_cast<double>(s->nc);
     if (!s->loss_target) s->loss_target = s->alloc<float>(s->nc * s->S);
     copy_d2d(s, s->loss_target, d_target, s->nc * s->S);
     s->have_loss = s->have_forward;
@@ -1924,6 +1951,12 @@ int dh_backward(dh_sim* s, const float* d_grad_rho, float* d_grad_white, double*
       s->param_steps = nullptr;
       s->param_cap = nsteps + 2;
       s->param_steps = s->alloc<double>(2LL * S * s->param_cap);
+      if (s->host_params) (void)hipHostFree(s->host_params);
+      s->host_params = nullptr;
+      void* hp = nullptr;
+      DH_HIP(hipHostMalloc(&hp, 2 * static_cast<size_t>(S) * (s->param_cap + 1) * sizeof(double),
+                           hipHostMallocDefault));
+      s->host_params = static_cast<double*>(hp);
     }
     // dark-matter kick factors of the reverse pass: the step's closing kick plus the same
     // sample's next opening kick (0 after its last step)
@@ -1947,7 +1980,7 @@ int dh_backward(dh_sim* s, const float* d_grad_rho, float* d_grad_white, double*
     dh::launch_fill(s->st, s->lx, 0.0f, 3 * np * S);
     dh::launch_fill(s->st, s->lp, 0.0f, 3 * np * S);
     dh::launch_fill(s->st, s->lphi, 0.0f, nc * S);
-    std::vector<double> gA(S, 0.0), gB(S, 0.0);
+    bool flux_loss = false;
     if (d_grad_rho) {
       for (int i = 0; i < S; ++i) copy_d2d(s, s->lq + s->nq * nc * i, d_grad_rho + nc * i, nc);
     } else if (s->loss_kind == dh_sim::kLossPower) {
@@ -1962,13 +1995,7 @@ int dh_backward(dh_sim* s, const float* d_grad_rho, float* d_grad_white, double*
       dh::launch_loss_vjp(s->st, s->q, s->loss_target, s->prm.A, s->prm.beta,
                           static_cast<float>(1.0 / s->f_b), s->lq, s->red, batch(s, nullptr));
       dh::launch_reduce_sum(s->st, s->red, nb, nb, 2 * S, s->red_out);
-      DH_HIP(hipMemcpyAsync(s->host_out, s->red_out, 2 * S * sizeof(double),
-                            hipMemcpyDeviceToHost, s->st));
-      sync(s);
-      for (int i = 0; i < S; ++i) {
-        gA[i] = s->host_out[i];
-        gB[i] = s->host_out[S + i];
-      }
+      flux_loss = true;   // its sums are read with those of the steps, at the end
     }
     // segments in reverse
     const int nseg = (nsteps + K - 1) / K;
@@ -2027,10 +2054,14 @@ int dh_backward(dh_sim* s, const float* d_grad_rho, float* d_grad_white, double*
     // restore the final state of the forward run
     unstash_state(s);
     // parameter gradients: fixed-order host sum of the per-step FP64 partials
-    std::vector<double> ps(2 * static_cast<size_t>(S) * (nsteps > 0 ? nsteps : 1));
+    double* loss_sums = s->host_params;
+    const double* ps = s->host_params + 2 * S;
+    if (flux_loss)
+      DH_HIP(hipMemcpyAsync(loss_sums, s->red_out, 2 * static_cast<size_t>(S) * sizeof(double),
+                            hipMemcpyDeviceToHost, s->st));
     if (nsteps > 0)
-      DH_HIP(hipMemcpyAsync(ps.data(), s->param_steps, 2 * static_cast<size_t>(S) * nsteps *
-                                                           sizeof(double),
+      DH_HIP(hipMemcpyAsync(s->host_params + 2 * S, s->param_steps,
+                            2 * static_cast<size_t>(S) * nsteps * sizeof(double),
                             hipMemcpyDeviceToHost, s->st));
     sync(s);
     for (int i = 0; i < S; ++i) {
@@ -2040,8 +2071,8 @@ int dh_backward(dh_sim* s, const float* d_grad_rho, float* d_grad_white, double*
         ge += ps[2 * S * slot + i];
         gd += ps[2 * S * slot + S + i];
       }
-      grad_params[4 * i + 0] = gA[i];
-      grad_params[4 * i + 1] = gB[i];
+      grad_params[4 * i + 0] = flux_loss ? loss_sums[i] : 0.0;
+      grad_params[4 * i + 1] = flux_loss ? loss_sums[S + i] : 0.0;
       grad_params[4 * i + 2] = ge;
       grad_params[4 * i + 3] = gd;
     }
@@ -2125,11 +2156,7 @@ int dh_fli_loss(dh_sim* s, const float* d_data, const float* d_noise_var, const 
     const int nb = dh::fli_blocks(nc);
     dh::launch_fli(s->st, s->q, s->fli_data, s->fli_nvar, s->fli_white, s->d_acur, 1.0 / s->f_b,
                    s->e_floor, s->t_per_e, s->cfg.gamma, s->fli_part, nullptr, batch(s, nullptr));
-    dh::launch_reduce_sum(s->st, s->fli_part, nb, nb, S, s->red_out);
-    DH_HIP(hipMemcpyAsync(s->host_out, s->red_out, S * sizeof(double), hipMemcpyDeviceToHost,
-                          s->st));
-    sync(s);
-    for (int i = 0; i < S; ++i) loss_out[i] = s->host_out[i];
+    reduce_to_host(s, s->fli_part, nb, nb, S, false, loss_out);
     s->have_loss = s->have_forward;
     s->loss_kind = dh_sim::kLossFli;
     return DH_OK;
@@ -2167,11 +2194,7 @@ int dh_conservation(dh_sim* s, double* out) {
     for (int i = 0; i < s->S; ++i) {
       dh::launch_conservation_partial(s->st, s->q + s->nq * s->nc * i, s->mom + 3 * s->np * i, s->red,
                                       nb, s->nc);
-      dh::launch_reduce_sum(s->st, s->red, nb, nb, 8, s->red_out);
-      DH_HIP(hipMemcpyAsync(s->host_out, s->red_out, 8 * sizeof(double), hipMemcpyDeviceToHost,
-                            s->st));
-      sync(s);
-      for (int k = 0; k < 8; ++k) out[8 * i + k] = s->host_out[k];
+      reduce_to_host(s, s->red, nb, nb, 8, false, out + 8 * i);
       for (int k = 5; k < 8; ++k) out[8 * i + k] *= s->m_dm;
     }
     return DH_OK;

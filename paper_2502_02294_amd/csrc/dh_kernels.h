@@ -236,6 +236,17 @@ void launch_reduce_max(hipStream_t st, const double* in, int count, int stride, 
                        double* out);
 void launch_reduce_sum(hipStream_t st, const double* in, int count, int stride, int nvec,
                        double* out);
+// the same (max or sum) into host memory the device can write (coherent): out[v].value, then
+// out[v].seq = seq
+struct HostValue {
+  double value;
+  uint64_t seq;
+};
+void launch_reduce_to_host(hipStream_t st, const double* in, int count, int stride, int nvec,
+                           bool max, HostValue* out, uint64_t seq);
+// dst = bytes of src, which may be reused when the call returns; false (and nothing done) for
+// more than fits a launch's arguments
+bool launch_upload(hipStream_t st, void* dst, const void* src, size_t bytes);
 int sum_blocks(long long count);
 // FP64 block sums of several fields of one sample: partial[v * nblocks + b]
 void launch_conservation_partial(hipStream_t st, const float* q, const float* mom,

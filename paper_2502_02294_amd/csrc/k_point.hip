@@ -4,6 +4,7 @@
 // initial-condition helpers (Sec. 2.1); with the adjoints of the differentiable ones.
 // All reductions are two-pass with a fixed order, so results are reproducible bit for bit.
 #include <cmath>
+#include <cstring>
 
 #include "dh_kernels.h"
 #include "dh_mlp.h"
@@ -1154,14 +1155,11 @@ __global__ void __launch_bounds__(kRedThreads) cfl_partial_kernel(const float* _
   block_reduce_store<1, true>(v, sample_partials(partial), partial_stride());
 }
 
-// one block per vector: out[v] = reduce over in[v * stride + 0..count)
+// one block per vector: the reduction of x[0..count), valid in thread 0
 constexpr int kReduceThreads = 1024;
 template <bool MAX>
-__global__ void __launch_bounds__(kReduceThreads) reduce_kernel(const double* __restrict__ in,
-                                                                int count, int stride,
-                                                                double* out) {
+__device__ __forceinline__ double block_reduce_vector(const double* __restrict__ x, int count) {
   __shared__ double sh[kReduceThreads / 64];
-  const double* x = in + static_cast<long long>(blockIdx.x) * stride;
   const double none = MAX ? -INFINITY : 0.0;
   double acc = none;
   // four independent loads a round (a missing one changes neither a sum nor a maximum)
@@ -1176,12 +1174,46 @@ __global__ void __launch_bounds__(kReduceThreads) reduce_kernel(const double* __
   acc = wave_reduce<MAX>(acc);
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = acc;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    double r = sh[0];
+  double r = sh[0];
 #pragma unroll
-    for (int w = 1; w < kReduceThreads / 64; ++w) r = MAX ? fmax(r, sh[w]) : r + sh[w];
-    out[blockIdx.x] = r;
+  for (int w = 1; w < kReduceThreads / 64; ++w) r = MAX ? fmax(r, sh[w]) : r + sh[w];
+  return r;
+}
+
+// out[v] = reduce over in[v * stride + 0..count)
+template <bool MAX>
+__global__ void __launch_bounds__(kReduceThreads) reduce_kernel(const double* __restrict__ in,
+                                                                int count, int stride,
+                                                                double* out) {
+  const double r =
+      block_reduce_vector<MAX>(in + static_cast<long long>(blockIdx.x) * stride, count);
+  if (threadIdx.x == 0) out[blockIdx.x] = r;
+}
+
+// The same into host memory: the value, then (system scope) the sequence number the host
+// waits for.
+template <bool MAX>
+__global__ void __launch_bounds__(kReduceThreads) reduce_to_host_kernel(
+    const double* __restrict__ in, int count, int stride, HostValue* out, uint64_t seq) {
+  const double r =
+      block_reduce_vector<MAX>(in + static_cast<long long>(blockIdx.x) * stride, count);
+  if (threadIdx.x == 0) {
+    HostValue* o = out + blockIdx.x;
+    __hip_atomic_store(&o->value, r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&o->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
   }
+}
+
+// Small uploads: the words travel as the kernel's arguments (a copy of a few hundred bytes
+// from pinned memory costs the host twice a launch, and the staging memory a wait).
+template <int N>
+struct Words {
+  uint32_t w[N];
+};
+template <int N>
+__global__ void __launch_bounds__(256) write_words_kernel(Words<N> src, uint32_t* __restrict__ dst,
+                                                          int count) {
+  for (int i = threadIdx.x; i < count; i += 256) dst[i] = src.w[i];
 }
 
 // ------------------------------------------------------------------------- sums
@@ -1568,6 +1600,39 @@ void launch_reduce_sum(hipStream_t st, const double* in, int count, int stride, 
   hipLaunchKernelGGL(reduce_kernel<false>, dim3(nvec), dim3(kReduceThreads), 0, st, in, count,
                      stride, out);
   DH_LAUNCH_CHECK();
+}
+
+void launch_reduce_to_host(hipStream_t st, const double* in, int count, int stride, int nvec,
+                           bool max, HostValue* out, uint64_t seq) {
+  if (max)
+    hipLaunchKernelGGL(reduce_to_host_kernel<true>, dim3(nvec), dim3(kReduceThreads), 0, st, in,
+                       count, stride, out, seq);
+  else
+    hipLaunchKernelGGL(reduce_to_host_kernel<false>, dim3(nvec), dim3(kReduceThreads), 0, st, in,
+                       count, stride, out, seq);
+  DH_LAUNCH_CHECK();
+}
+
+namespace {
+template <int N>
+void write_words(hipStream_t st, void* dst, const void* src, int count) {
+  Words<N> w{};
+  std::memcpy(w.w, src, static_cast<size_t>(count) * 4);
+  hipLaunchKernelGGL(write_words_kernel<N>, dim3(1), dim3(256), 0, st, w,
+                     static_cast<uint32_t*>(dst), count);
+  DH_LAUNCH_CHECK();
+}
+}  // namespace
+
+bool launch_upload(hipStream_t st, void* dst, const void* src, size_t bytes) {
+  // a launch's arguments may take 4 KB
+  if (bytes % 4 != 0 || bytes > 3840) return false;
+  const int count = static_cast<int>(bytes / 4);
+  if (count <= 96)
+    write_words<96>(st, dst, src, count);
+  else
+    write_words<960>(st, dst, src, count);
+  return true;
 }
 
 void launch_conservation_partial(hipStream_t st, const float* q, const float* mom,
