@@ -67,12 +67,12 @@ struct TapeStep {
   const float* phi1;          // not stored either: the next step's phi0, or the state's phi
                               // after a segment's last step; set by the reverse pass
   uint32_t *start, *sorted;   // the step's sort of x1 (bin starts, ids in bin order)
-  float4* spos;               // x1 in that bin order
+  float3* sw1;                // the CIC weights of x1 in that bin order
   float* sn;                  // dual energy with the smoothed injection: the step's per-cell
                               // injected energy before the smoothing (else null)
   // the sort the reverse pass uses: the buffers above, or the forward's stored one
   uint32_t *vstart, *vsorted;
-  float4* vspos;
+  float3* vsw1;
   StepPlan plan;
 };
 
@@ -83,12 +83,12 @@ struct Ckpt {
 };
 
 // What a forward step computed that its recomputation in the reverse pass would compute
-// again, bit for bit: the sort of the post-drift positions (bin starts, ids, positions in
-// bin order) and the end-of-step potential.  Kept per step while memory allows.
+// again, bit for bit: the sort of the post-drift positions (bin starts, ids, CIC weights
+// in bin order) and the end-of-step potential.  Kept per step while memory allows.
 struct StepStore {
   uint32_t* start = nullptr;
   uint32_t* sorted = nullptr;
-  float4* spos = nullptr;
+  float3* sw1 = nullptr;
   float* phi = nullptr;
 };
 
@@ -495,7 +495,7 @@ void drop_kick(dh_sim* s) {
 
 long long store_step_bytes(const dh_sim* s) {
   const long long S = s->S;
-  return (s->nc * S + 1) * 4 + s->np * S * (4 + 16) + s->nc * S * 4;
+  return (s->nc * S + 1) * 4 + s->np * S * (4 + 12) + s->nc * S * 4;
 }
 
 // the dual-energy state with the smoothed injection (its tape keeps the injection field)
@@ -507,7 +507,7 @@ long long tape_entry_bytes(const dh_sim* s) {
   const long long S = s->S, nc = s->nc * S, np = s->np * S;
   const bool closure = s->cfg.closure == DH_CLOSURE_MLP && s->cfg.subgrid != DH_SUBGRID_OFF;
   return (closure ? 5 : 4) * s->nq * nc * 4 + 3 * np * 4 + nc * 4 + (nc + 1) * 4 + np * 4 +
-         np * 16 + (dual_smooth(s) ? nc * 4 : 0);
+         np * 12 + (dual_smooth(s) ? nc * 4 : 0);
 }
 
 // Device memory the first reverse pass still has to allocate (tape entries, adjoint buffers,
@@ -562,7 +562,7 @@ bool keep_step(dh_sim* s, int k) {
     void* p[4] = {nullptr, nullptr, nullptr, nullptr};
     const size_t bytes[4] = {static_cast<size_t>(s->nc * S + 1) * 4,
                              static_cast<size_t>(s->np * S) * 4,
-                             static_cast<size_t>(s->np * S) * 16,
+                             static_cast<size_t>(s->np * S) * 12,
                              static_cast<size_t>(s->nc * S) * 4};
     for (int i = 0; i < 4; ++i) {
       if (hipMalloc(&p[i], bytes[i]) != hipSuccess) {
@@ -575,14 +575,14 @@ bool keep_step(dh_sim* s, int k) {
     }
     e.start = static_cast<uint32_t*>(p[0]);
     e.sorted = static_cast<uint32_t*>(p[1]);
-    e.spos = static_cast<float4*>(p[2]);
+    e.sw1 = static_cast<float3*>(p[2]);
     e.phi = static_cast<float*>(p[3]);
     s->store.push_back(e);
   }
   StepStore& e = s->store[k];
   std::swap(s->bins.start, e.start);
   std::swap(s->bins.sorted, e.sorted);
-  std::swap(s->bins.spos, e.spos);
+  std::swap(s->bins.sw1, e.sw1);
   copy_d2d(s, e.phi, s->phi, s->nc * s->S);
   s->store_valid = k + 1;
   return true;
@@ -642,11 +642,9 @@ bool all_finite(const std::vector<double>& v) {
 // Closing pass of a step from q_in (the state after the sweeps) into s->q: gas half kick,
 // source term (kicked state to q_kicked if given), star field and CFL maxima if `full`; then
 // the smoothed supernova injection (cfg.sn_smooth, with the CFL maxima) and, if `readout`,
-// the step's new stars read out on the particles (cfg.star_dm; spos, sorted: the sort of the
-// end-of-step positions).
+// the step's new stars read out on the particles (cfg.star_dm).
 void close_pass(dh_sim* s, const float* q_in, float* q_kicked, bool full, bool readout,
-                const float4* spos, const uint32_t* sorted, const Batch& b, bool closure,
-                float* sn = nullptr) {
+                const Batch& b, bool closure, float* sn = nullptr) {
   const bool smooth = s->cfg.sn_smooth && s->cfg.subgrid != DH_SUBGRID_OFF;
   const bool stars = readout && full && s->znew && s->cfg.subgrid != DH_SUBGRID_OFF;
   float* snb = sn ? sn : s->sn_buf;   // a tape keeps the injection field where it has room
@@ -654,7 +652,7 @@ void close_pass(dh_sim* s, const float* q_in, float* q_kicked, bool full, bool r
                         s->cfg.gamma, full && !smooth ? s->cfl_red : nullptr, b, closure,
                         stars ? s->znew : nullptr, smooth ? snb : nullptr);
   if (smooth) dh::launch_sn_inject(s->st, snb, s->q, s->cfg.gamma, full ? s->cfl_red : nullptr, b);
-  if (stars) dh::launch_star_readout(s->st, s->znew, spos, sorted, s->aux, b);
+  if (stars) dh::launch_star_readout(s->st, s->znew, s->pos, s->aux, b);
 }
 
 // One step of the method on the handle state.  With a tape entry, keeps its intermediates.
@@ -709,7 +707,7 @@ void do_step(dh_sim* s, const StepPlan& sp, TapeStep* tp, bool defer, int store_
       dh::launch_grad(s->st, s->phi, s->g4, b);
       tp->vstart = e.start;
       tp->vsorted = e.sorted;
-      tp->vspos = e.spos;
+      tp->vsw1 = e.sw1;
     } else {
       dh::launch_sort(s->st, s->bins, s->pos, b, true, true);
       potential_from_bins(s, tp->q[4], s->phi, s->g4, b);
@@ -717,15 +715,15 @@ void do_step(dh_sim* s, const StepPlan& sp, TapeStep* tp, bool defer, int store_
       // former buffers
       std::swap(s->bins.start, tp->start);
       std::swap(s->bins.sorted, tp->sorted);
-      std::swap(s->bins.spos, tp->spos);
+      std::swap(s->bins.sw1, tp->sw1);
       tp->vstart = tp->start;
       tp->vsorted = tp->sorted;
-      tp->vspos = tp->spos;
+      tp->vsw1 = tp->sw1;
     }
     // the recomputation needs neither the star field nor the CFL maxima (plain source)
     const bool full = !recompute || closure;
-    close_pass(s, tp->q[4], closure ? tp->q[5] : nullptr, full, !recompute, tp->vspos,
-               tp->vsorted, b, closure, tp->sn);
+    close_pass(s, tp->q[4], closure ? tp->q[5] : nullptr, full, !recompute, b, closure,
+               tp->sn);
   } else {
     // opening half kicks with g_n (the gas one inside the first sweep), drift with
     // a(t + dt/2)
@@ -738,10 +736,10 @@ void do_step(dh_sim* s, const StepPlan& sp, TapeStep* tp, bool defer, int store_
       std::swap(s->q, s->q2);
     }
     // Poisson at a(t + dt) from gas + DM (keys and their histogram were made by the drift)
-    dh::launch_sort(s->st, s->bins, s->pos, b, true, store_k >= 0 || s->aux);
+    dh::launch_sort(s->st, s->bins, s->pos, b, true, store_k >= 0);
     potential_from_bins(s, s->q, s->phi, s->g4, b);
     // closing gas half kick with g_{n+1}, source term and the CFL maxima: one pass
-    close_pass(s, s->q, nullptr, true, true, s->bins.spos, s->bins.sorted, b, closure);
+    close_pass(s, s->q, nullptr, true, true, b, closure);
     if (store_k >= 0) keep_step(s, store_k);
   }
   // closing dark-matter half kick with g_{n+1} (deferred: the factor the table holds)
@@ -1096,7 +1094,7 @@ void alloc_tape_entry(dh_sim* s, TapeStep& t) {
   t.phi1 = nullptr;
   t.start = s->alloc<uint32_t>(s->nc * S + 1);
   t.sorted = s->alloc<uint32_t>(s->np * S);
-  t.spos = s->alloc<float4>(s->np * S);
+  t.sw1 = s->alloc<float3>(s->np * S);
   t.sn = dual_smooth(s) ? s->alloc<float>(s->nc * S) : nullptr;
 }
 
@@ -1259,9 +1257,8 @@ void step_vjp(dh_sim* s, const TapeStep& T, bool defer_open) {
   dh::Bins tb = s->bins;
   tb.start = T.vstart;
   tb.sorted = T.vsorted;
-  tb.spos = T.vspos;
-  dh::launch_gather_sorted(st, tb, s->lp, b);
-  dh::launch_deposit_vec(st, tb, true, s->lg, b);
+  tb.sw1 = T.vsw1;
+  dh::launch_deposit_vec(st, tb, s->lp, true, s->lg, b);
   // lambda_phi_{n+1}: with the next step's opening kick taken above, its g adjoint (lg2) first
   if (fuse_open)
     dh::launch_grad_vjp2(st, s->lg2, s->lg, s->lphi2, b);
@@ -1306,8 +1303,7 @@ void finish_first_kick(dh_sim* s, const TapeStep& T) {
   s->g4b_phi0_of = -1;
   dh::launch_fill(st, s->lg, 0.0f, 3 * s->nc * s->S);
   sort_particles(s, T.x0, b, true);
-  dh::launch_gather_sorted(st, s->bins, s->lp, b);
-  dh::launch_deposit_vec(st, s->bins, false, s->lg, b);
+  dh::launch_deposit_vec(st, s->bins, s->lp, false, s->lg, b);
   dh::launch_kick_vjp_pos(st, s->g4b, T.x0, s->lp, false, s->lx, b);
   dh::launch_grad_vjp(st, s->lg, s->lphi, s->lphi, b);
 }
@@ -1520,8 +1516,7 @@ int dh_create(const dh_config* cfg, dh_sim** out) {
     s->bins.block_sums = s->alloc<uint32_t>(static_cast<long long>(dh::scan_block_count(nc)));
     DH_HIP(hipMemset(s->bins.count, 0, static_cast<size_t>(nc) * sizeof(uint32_t)));
     s->bins.large = s->alloc<uint32_t>(1 + dh::large_bin_capacity(np));
-    s->bins.spos = s->alloc<float4>(np);
-    s->bins.sval = s->alloc<float4>(np);
+    s->bins.sw1 = s->alloc<float3>(np);
     s->g4 = s->alloc<float4>(nc);
     s->g4b = s->alloc<float4>(nc);
     s->cfl_red = s->alloc<double>(static_cast<long long>(dh::cfl_blocks(n)) * S + 1);

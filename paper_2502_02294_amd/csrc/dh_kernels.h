@@ -72,32 +72,29 @@ struct Bins {          // counting sort of particles by CIC base cell
   uint32_t* sorted;    // [S np] particle ids, bins in order, ids ascending inside a bin
   uint32_t* block_sums;  // [scan blocks]
   uint32_t* large;     // [1 + large_bin_capacity(total)]: count, then bins of many particles
-  float4* spos;        // [S np] positions in bin order
-  float4* sval;        // [S np] a particle vector field in bin order (adjoint deposits)
+  float3* sw1;         // [S np] upper CIC weights of the particles in bin order
 };
 size_t scan_block_count(long long nbins);
 // entries of Bins::large for `total` particles (bins of more than 256 particles)
 long long large_bin_capacity(long long total);
 void launch_keys(hipStream_t st, const float* pos, uint32_t* key, const Batch& b);
-// aux[id] += CIC read-out of znew at each particle (bin order: spos, sorted of the positions
-// at the end of the step; samples that sit the step out are skipped)
-void launch_star_readout(hipStream_t st, const float* znew, const float4* spos,
-                         const uint32_t* sorted, float* aux, const Batch& b);
-// sort by bins.key (already computed for pos) and gather pos into bin order; counted: the
-// histogram was made by launch_kick_drift (count_into); keep_ids: the ids, too, are wanted in
-// bin order (bins.sorted, for launch_gather_sorted and launch_star_readout)
+// aux += CIC read-out of znew at each particle (pos: the positions at the end of the step;
+// samples that sit the step out are skipped)
+void launch_star_readout(hipStream_t st, const float* znew, const float* pos, float* aux,
+                         const Batch& b);
+// sort by bins.key (already computed for pos) and gather the particles' weights into bin order;
+// counted: the histogram was made by launch_kick_drift (count_into); keep_ids: the ids, too,
+// are wanted in bin order (bins.sorted, for launch_deposit_vec)
 void launch_sort(hipStream_t st, const Bins& bins, const float* pos, const Batch& b,
                  bool counted, bool keep_ids);
-// bins.sval = v[3][np] (per sample) in bin order
-void launch_gather_sorted(hipStream_t st, const Bins& bins, const float* v, const Batch& b);
 // out = rho_gas + m_dm * CIC(sorted positions) + offset; rho_gas (sample s at
 // rho_gas + s * rho_stride: 5 n^3 for the density row of Q) may be null (then 0)
 void launch_deposit(hipStream_t st, const Bins& bins, const float* rho_gas,
                     long long rho_stride, float m_dm, float offset, float* out, const Batch& b);
-// out_accum[3][nc] += scale * CIC deposit of bins.sval, scale = h_open (merged: h_dm) of the
-// table
-void launch_deposit_vec(hipStream_t st, const Bins& bins, bool merged, float* out_accum,
-                        const Batch& b);
+// out_accum[3][nc] += scale * CIC deposit of v[3][np] (per sample; bins sorted with keep_ids),
+// scale = h_open (merged: h_dm) of the table
+void launch_deposit_vec(hipStream_t st, const Bins& bins, const float* v, bool merged,
+                        float* out_accum, const Batch& b);
 // g4 = (-grad phi, 0) by two-point central differences
 void launch_grad(hipStream_t st, const float* phi, float4* g4, const Batch& b);
 // g at particles: out[3][np] = CIC read-out of g4

@@ -6,9 +6,9 @@
 //
 // CIC on cell centres: with s = x - 1/2, i0 = floor(s), w1 = s - i0, a particle puts
 // weight (1-w1) in cell i0 and w1 in i0+1 per axis.  Cell c receives from particles whose
-// base cell is c - o, o in {0,1}^3.  After the sort, the positions are gathered into bin
-// order (float4 per particle); the deposit sums each bin's 8 corner weights in LDS and each
-// cell adds its 8 corners, in a fixed order and with ascending particle id inside a bin:
+// base cell is c - o, o in {0,1}^3.  After the sort, the particles' upper weights w1 are gathered
+// into bin order (float3 per particle); the deposit sums each bin's 8 corner weights in LDS and
+// each cell adds its 8 corners, in a fixed order and with ascending particle id inside a bin:
 // every sum is reproducible bit for bit without float atomics.
 #include "dh_kernels.h"
 
@@ -16,10 +16,9 @@ namespace dh {
 
 namespace {
 
-constexpr int kScanThreads = 256;
+constexpr int kScanThreads = 1024;
 constexpr int kLargeSortBlocks = 512;   // two blocks of 64 KB of LDS per CU
-constexpr int kScanPer = 16;
-constexpr int kScanTile = kScanThreads * kScanPer;
+constexpr int kScanTile = kScanThreads * 4;   // one 16-byte vector of counts a thread
 
 __device__ __forceinline__ int wrapi(int j, int n) { return j & (n - 1); }
 
@@ -82,7 +81,7 @@ __global__ void hist_kernel(const uint32_t* __restrict__ key, uint32_t* count,
 }
 
 // Scans of the bin counts: 32-bit integer sums, so the grouping does not change a result.
-static_assert(kScanThreads == 256, "the block scans below assume four waves");
+constexpr int kScanWaves = kScanThreads / 64;
 
 // inclusive scan over the 64 lanes of a wave
 __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v) {
@@ -95,111 +94,62 @@ __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v) {
   return v;
 }
 
-// Block-wide exclusive scan over kScanThreads values; sh holds the four wave totals.
-__device__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* sh, uint32_t& total) {
-  const uint32_t inc = wave_inclusive_scan(v);
-  const int w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 63) sh[w] = inc;
-  __syncthreads();
-  uint32_t below = 0;
-  total = 0;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const uint32_t t = sh[k];
-    below += k < w ? t : 0u;
-    total += t;
-  }
-  __syncthreads();   // sh is free again on return
-  return below + inc - v;
-}
-
-// tile element e lives at LDS word e + e / kScanPer (padding breaks the 16-word stride)
-__device__ __forceinline__ int tile_slot(int e) { return e + e / kScanPer; }
-
-__device__ __forceinline__ uint32_t wave_add(uint32_t v) {
+// sum of v over the block (every thread receives it); sh[kScanWaves] is free before the call
+__device__ __forceinline__ uint32_t block_add(uint32_t v, uint32_t* sh) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-
-// sum of v over the block (every thread receives it); sh holds the four wave sums
-__device__ __forceinline__ uint32_t block_add(uint32_t v, uint32_t* sh) {
-  v = wave_add(v);
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
   __syncthreads();
-  const uint32_t t = sh[0] + sh[1] + sh[2] + sh[3];
-  __syncthreads();   // sh is free again on return
+  uint32_t t = 0;
+#pragma unroll
+  for (int k = 0; k < kScanWaves; ++k) t += sh[k];
   return t;
 }
 
 // sums[t] = sum of the counts of tile t
-__global__ void __launch_bounds__(kScanThreads) scan_sums_kernel(const uint32_t* __restrict__ in,
+__global__ void __launch_bounds__(kScanThreads) scan_sums_kernel(const uint4* __restrict__ in,
                                                                  uint32_t* __restrict__ sums) {
-  __shared__ uint32_t sh[4];
-  // 16-byte loads, consecutive threads on consecutive vectors
-  const uint4* in4 =
-      reinterpret_cast<const uint4*>(in + static_cast<long long>(blockIdx.x) * kScanTile);
-  uint32_t s = 0;
-#pragma unroll
-  for (int k = 0; k < kScanPer / 4; ++k) {
-    const uint4 v = in4[k * kScanThreads + threadIdx.x];
-    s += v.x + v.y + v.z + v.w;
-  }
-  const uint32_t t = block_add(s, sh);
+  __shared__ uint32_t sh[kScanWaves];
+  const uint4 v = in[blockIdx.x * kScanThreads + threadIdx.x];
+  const uint32_t t = block_add(v.x + v.y + v.z + v.w, sh);
   if (threadIdx.x == 0) sums[blockIdx.x] = t;
 }
 
 // Exclusive scan of the bin counts, one block per tile: out[0..tiles kScanTile] = prefix sums
-// and total.  What lies before its tile each block adds up itself: the tile sums (at most 4 of
-// 2^31 / 2^12 a thread at 256^3, from L2) or, for up to kScanDirect tiles (32^3), where another
-// launch would cost more than it saves, the counts.  Against a separate scan of the tile sums
-// that is one launch less and 256^3 takes 17 + 24 us instead of 17 + 5.5 + 24; a single pass
-// with look-back between the blocks took 79 us there (its polls cross the XCDs).
+// and total.  What lies before its tile each block adds up itself: the tile sums (4 a thread at
+// 256^3, from L2) or, for up to kScanDirect tiles (32^3), where another launch would cost more
+// than it saves, the counts (in flight together: 4.6 us; 256 threads of 16 counts took 10.4).
 // Also clears the list of large bins for the sort that follows.
 constexpr int kScanDirect = 8;
 
-__global__ void __launch_bounds__(kScanThreads) scan_kernel(const uint32_t* __restrict__ in,
+__global__ void __launch_bounds__(kScanThreads) scan_kernel(const uint4* __restrict__ in,
                                                             const uint32_t* __restrict__ sums,
-                                                            uint32_t* __restrict__ out, int tiles,
+                                                            uint4* __restrict__ out, int tiles,
                                                             uint32_t* __restrict__ large) {
-  __shared__ uint32_t tile[kScanTile + kScanTile / kScanPer];
-  __shared__ uint32_t sh[4];
-  const int t = blockIdx.x;
-  const long long base = static_cast<long long>(t) * kScanTile;
+  __shared__ uint32_t sh[kScanWaves], shp[kScanWaves];
+  const int t = blockIdx.x, wave = threadIdx.x >> 6;
+  const int at = t * kScanThreads + threadIdx.x;
+  const uint4 v = in[at];
   uint32_t part = 0;
   if (sums) {
     for (int i = threadIdx.x; i < t; i += kScanThreads) part += sums[i];
   } else {
-    const uint4* all4 = reinterpret_cast<const uint4*>(in);
-    for (int i = threadIdx.x; i < t * (kScanTile / 4); i += kScanThreads) {
-      const uint4 v = all4[i];
-      part += v.x + v.y + v.z + v.w;
+#pragma unroll
+    for (int k = 0; k < kScanDirect - 1; ++k) {
+      const uint4 u = in[min(k, t) * kScanThreads + threadIdx.x];
+      if (k < t) part += u.x + u.y + u.z + u.w;
     }
   }
-  for (int k = 0; k < kScanPer; ++k) {
-    const int e = k * kScanThreads + threadIdx.x;
-    tile[tile_slot(e)] = in[base + e];
-  }
-  const uint32_t before = block_add(part, sh);   // also orders the tile's LDS writes
-  uint32_t s = 0;
-  for (int k = 0; k < kScanPer; ++k) s += tile[tile_slot(threadIdx.x * kScanPer + k)];
-  uint32_t total;
-  uint32_t run = block_exclusive_scan(s, sh, total) + before;
-  for (int k = 0; k < kScanPer; ++k) {
-    const int sl = tile_slot(threadIdx.x * kScanPer + k);
-    const uint32_t v = tile[sl];
-    tile[sl] = run;
-    run += v;
-  }
-  __syncthreads();
-  for (int k = 0; k < kScanPer; ++k) {
-    const int e = k * kScanThreads + threadIdx.x;
-    out[base + e] = tile[tile_slot(e)];
-  }
-  if (threadIdx.x == 0) {
-    if (t == tiles - 1) out[static_cast<long long>(tiles) * kScanTile] = before + total;
-    if (t == 0) large[0] = 0u;
-  }
+  const uint32_t mine = v.x + v.y + v.z + v.w;
+  const uint32_t inc = wave_inclusive_scan(mine);
+  if ((threadIdx.x & 63) == 63) sh[wave] = inc;
+  uint32_t run = block_add(part, shp) + inc - mine;   // its barrier also orders sh
+#pragma unroll
+  for (int k = 0; k < kScanWaves; ++k) run += k < wave ? sh[k] : 0u;
+  out[at] = make_uint4(run, run + v.x, run + v.x + v.y, run + v.x + v.y + v.z);
+  if (threadIdx.x == kScanThreads - 1 && t == tiles - 1)
+    reinterpret_cast<uint32_t*>(out + static_cast<long long>(tiles) * kScanThreads)[0] = run + mine;
+  if (threadIdx.x == 0 && t == 0) large[0] = 0u;
 }
 
 __global__ void scatter_kernel(const uint32_t* __restrict__ key, const uint32_t* __restrict__ rank,
@@ -239,12 +189,12 @@ __device__ __forceinline__ void sort8(uint32_t (&v)[8]) {
   }
 }
 
-// position of particle id (global: sample id >> lnp) of per-sample [3][np] arrays
-__device__ __forceinline__ float4 gather3(const float* __restrict__ v, uint32_t id, int lnp) {
+// upper CIC weights of particle id (global: sample id >> lnp) from per-sample [3][np] positions
+__device__ __forceinline__ float3 gather_w1(const float* __restrict__ v, uint32_t id, int lnp) {
   const long long np = 1LL << lnp;
   const float* vs = v + (id >> lnp) * 3 * np;
   const long long loc = id & (np - 1);
-  return make_float4(vs[loc], vs[np + loc], vs[2 * np + loc], 0.0f);
+  return make_float3(w1_of(vs[loc]), w1_of(vs[np + loc]), w1_of(vs[2 * np + loc]));
 }
 
 // orders the wave's LDS accesses (its lanes exchange ids through its own part of the LDS)
@@ -284,7 +234,7 @@ __device__ __forceinline__ void wave_rank_sort(uint32_t* s, uint32_t k, int lane
 __global__ void __launch_bounds__(256) bin_sort_gather_kernel(const uint32_t* __restrict__ start,
                                                               uint32_t* sorted,
                                                               const float* __restrict__ pos,
-                                                              float4* __restrict__ spos, int lnp,
+                                                              float3* __restrict__ sw1, int lnp,
                                                               uint32_t* __restrict__ count,
                                                               uint32_t* __restrict__ large,
                                                               bool keep_ids) {
@@ -336,7 +286,7 @@ __global__ void __launch_bounds__(256) bin_sort_gather_kernel(const uint32_t* __
     for (uint32_t i = lane; i < total; i += 64) {
       const uint32_t id = my[i];
       if (keep_ids) sorted[run + i] = id;
-      spos[run + i] = gather3(pos, id, lnp);
+      sw1[run + i] = gather_w1(pos, id, lnp);
     }
     wave_sync();
     run = end;
@@ -370,7 +320,7 @@ __global__ void __launch_bounds__(256) bin_sort_large_kernel(const uint32_t* __r
                                                              uint32_t* sorted,
                                                              const uint32_t* __restrict__ large,
                                                              const float* __restrict__ pos,
-                                                             float4* __restrict__ spos, int lnp) {
+                                                             float3* __restrict__ sw1, int lnp) {
   __shared__ uint32_t sh[kLdsSort];
   const uint32_t count = large[0];
   for (uint32_t e = blockIdx.x; e < count; e += gridDim.x) {
@@ -390,36 +340,36 @@ __global__ void __launch_bounds__(256) bin_sort_large_kernel(const uint32_t* __r
                         [&](uint32_t i, uint32_t v) { g[i] = v; });
     }
     __syncthreads();
-    for (uint32_t i = threadIdx.x; i < k; i += blockDim.x) spos[lo + i] = gather3(pos, g[i], lnp);
+    for (uint32_t i = threadIdx.x; i < k; i += blockDim.x) sw1[lo + i] = gather_w1(pos, g[i], lnp);
     __syncthreads();
   }
 }
 
-// out[j] = (v[0][id], v[1][id], v[2][id], 0) for id = sorted[j] (global particle index: sample
-// id >> lnp, particle id & (np - 1) of a per-sample [3][np] array)
-__global__ void gather_sorted_kernel(const uint32_t* __restrict__ sorted,
-                                     const float* __restrict__ v, float4* __restrict__ out,
-                                     long long total, int lnp) {
-  const long long j = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (j >= total) return;
-  out[j] = gather3(v, sorted[j], lnp);
-}
-
 // ---------------------------------------------------------------------------- deposit
-// A block owns a tile of TX x TY x TZ cells.  Pass 1: for every bin of the tile and of its
-// low halo (the bins that reach the tile), one thread sums over the bin's particles, in
-// ascending order, the 8 CIC corner weights (times one component of the particle's vector
-// for the vector deposit) into LDS:
+// A block owns a column of TX x TY cells and walks along z.  For every plane of bins that
+// reaches its cells one thread per bin of the plane (and of its low x and y halo) sums over the
+// bin's particles, in ascending order, the 8 CIC corner weights (times the particle's vector
+// for the vector deposit) and puts them into LDS:
 //   W[o][b] = sum_{p in b} prod_d (o_d ? w1_d : 1 - w1_d),  o in {0,1}^3.
-// Pass 2: cell c adds W[o][c - o] over o in a fixed order.  Each particle's weights are
-// formed once per tile that sees its bin (about 1.5 times) instead of once per cell, and the
-// sums are reproducible bit for bit.
-template <int TX, int TY, int TZ>
-struct DepTile {
-  static constexpr int BX = TX + 1, BY = TY + 1, BZ = TZ + 1;
-  static constexpr int NB = BX * BY * BZ;           // bins read by a tile
-  static constexpr int NC = TX * TY * TZ;           // cells of a tile
-  static constexpr int PER = (NB + 255) / 256;      // bins per thread
+// A cell then adds W[o][c - o] over o in a fixed order; the corners with o_z = 1 wait in its
+// registers for the next plane.  Each particle's weights are formed once per column that sees
+// its bin (1.3 times) instead of once per cell, and the sums are reproducible bit for bit.
+// What bounds it is the chain bounds -> particle -> sum of each bin, so the walk keeps the next
+// planes' loads in flight; a block per tile of 32 x 4 x 4, which met that chain once per bin of
+// a thread, took 183 us at 256^3 against 120 (345 MB: 2.9 TB/s), and 63 against 41 a step on
+// average in a clustered 128^3 run; 32^3: 7.2 against 5.1.  Columns of 32 x 8: 130 at 256^3,
+// 22 at 128^3 as here; longer walks leave the chip idle (see launch_columns).  Loading three or
+// four particles ahead instead of two, or giving the bins of more to a second pass with full
+// lanes: 5 to 20% slower.
+// particles of a bin that its thread holds ahead of their plane
+constexpr int kDepAhead = 2;
+
+template <int TX, int TY>
+struct DepCol {
+  static constexpr int BX = TX + 1, BY = TY + 1;
+  static constexpr int NB = BX * BY;                // bins of a plane
+  static constexpr int NC = TX * TY;                // cells of a plane
+  static constexpr int THREADS = (NB + 63) / 64 * 64;
 };
 
 // Bins of more than kCrowded particles (dense halos gather hundreds or thousands of
@@ -429,269 +379,227 @@ struct DepTile {
 // stay reproducible bit for bit and no thread loops over a crowded bin alone.
 constexpr uint32_t kCrowded = 16;
 
-// sum of v over the 64 lanes of the wave, every lane receiving it (fixed order)
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float v) {
+  const int o = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true);
+  return v + __builtin_bit_cast(float, o);
 }
 
-// cell of tile bin b (the tile at x0, y0, z0 and its low halo)
-template <int BX, int BY>
-__device__ __forceinline__ int tile_bin_cell(int b, int x0, int y0, int z0, int n) {
-  const int bx = b % BX, by = (b / BX) % BY, bz = b / (BX * BY);
-  return (wrapi(z0 - 1 + bz, n) * n + wrapi(y0 - 1 + by, n)) * n + wrapi(x0 - 1 + bx, n);
-}
-
-// W[o][b] (or the weights times one component v of sval, VEC) of the crowded bins listed in
-// list[0..count): wave w of the block takes entries w, w + waves, ...
-template <int TX, int TY, int TZ, bool VEC>
-__device__ __forceinline__ void crowded_bin_sums(const uint32_t* __restrict__ start,
-                                                 const float4* __restrict__ spos,
-                                                 const float4* __restrict__ sval, int v,
-                                                 const uint16_t* list, int count, int x0, int y0,
-                                                 int z0, int n, float* W) {
-  using T = DepTile<TX, TY, TZ>;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
-  for (int e = wave; e < count; e += waves) {
-    const int b = list[e];
-    const int cell = tile_bin_cell<T::BX, T::BY>(b, x0, y0, z0, n);
-    const uint32_t lo = start[cell], hi = start[cell + 1];
-    float acc[8];
+// Sums of v[0..8) over the 64 lanes of the wave, every lane receiving them: the butterfly
+// v += v[lane ^ off], off = 32 ... 1, from 8 on in register moves (a rotation by off within 16
+// lanes stands for the exchange once the wider levels have made the lanes repeat).
+__device__ __forceinline__ void wave_sum(float (&v)[8]) {
 #pragma unroll
-    for (int o = 0; o < 8; ++o) acc[o] = 0.0f;
-    for (uint32_t j = lo + lane; j < hi; j += 64) {
-      const float4 p = spos[j];
-      float val = 1.0f;
-      if (VEC) {
-        const float4 q = sval[j];
-        val = v == 0 ? q.x : (v == 1 ? q.y : q.z);
-      }
-      const float wx = w1_of(p.x), wy = w1_of(p.y), wz = w1_of(p.z);
+  for (int off = 32; off >= 16; off >>= 1)
 #pragma unroll
-      for (int o = 0; o < 8; ++o) {
-        const float w = wsel(wx, o & 1) * wsel(wy, (o >> 1) & 1) * wsel(wz, o >> 2);
-        acc[o] += VEC ? w * val : w;
-      }
-    }
-#pragma unroll
-    for (int o = 0; o < 8; ++o) {
-      const float t = wave_sum(acc[o]);
-      if (lane == 0) W[o * T::NB + b] = t;
-    }
-  }
-}
-
-// Pass 1 of the density deposit: W[o][b] for the bins of the tile and its halo.
-template <int TX, int TY, int TZ>
-__device__ __forceinline__ void deposit_tile(const uint32_t* __restrict__ start,
-                                             const float4* __restrict__ spos, int n, int x0,
-                                             int y0, int z0, float* W) {
-  using T = DepTile<TX, TY, TZ>;
-  __shared__ int ncrowd;
-  __shared__ uint16_t crowd[T::NB];
-  if (threadIdx.x == 0) ncrowd = 0;
-  __syncthreads();
-  // bounds of this thread's bins first (independent loads), then their particles
-  uint32_t lo[T::PER], hi[T::PER];
-#pragma unroll
-  for (int k = 0; k < T::PER; ++k) {
-    const int b = threadIdx.x + 256 * k;
-    lo[k] = hi[k] = 0;
-    if (b < T::NB) {
-      const int bx = b % T::BX, by = (b / T::BX) % T::BY, bz = b / (T::BX * T::BY);
-      const long long cell = (static_cast<long long>(wrapi(z0 - 1 + bz, n)) * n +
-                              wrapi(y0 - 1 + by, n)) * n + wrapi(x0 - 1 + bx, n);
-      lo[k] = start[cell];
-      hi[k] = start[cell + 1];
-    }
-  }
-  // the first particle of every bin of this thread (one round of independent loads; bins
-  // seldom hold more than one particle before clustering)
-  float4 p0[T::PER];
-#pragma unroll
-  for (int k = 0; k < T::PER; ++k) p0[k] = spos[lo[k] < hi[k] ? lo[k] : 0u];
-#pragma unroll
-  for (int k = 0; k < T::PER; ++k) {
-    const int b = threadIdx.x + 256 * k;
-    if (b >= T::NB) continue;
-    if (hi[k] - lo[k] > kCrowded) {
-      // the list order only decides which wave sums the bin
-      crowd[atomicAdd(&ncrowd, 1)] = static_cast<uint16_t>(b);
-      continue;
-    }
-    float acc[8];
-#pragma unroll
-    for (int o = 0; o < 8; ++o) acc[o] = 0.0f;
-    for (uint32_t j = lo[k]; j < hi[k]; ++j) {
-      const float4 p = j == lo[k] ? p0[k] : spos[j];
-      const float wx = w1_of(p.x), wy = w1_of(p.y), wz = w1_of(p.z);
-#pragma unroll
-      for (int o = 0; o < 8; ++o)
-        acc[o] += wsel(wx, o & 1) * wsel(wy, (o >> 1) & 1) * wsel(wz, o >> 2);
-    }
-#pragma unroll
-    for (int o = 0; o < 8; ++o) W[o * T::NB + b] = acc[o];
-  }
-  __syncthreads();
-  crowded_bin_sums<TX, TY, TZ, false>(start, spos, nullptr, 0, crowd, ncrowd, x0, y0, z0, n, W);
-}
-
-// sum over the 8 corners of cell (cx, cy, cz) of the tile
-template <int TX, int TY, int TZ>
-__device__ __forceinline__ float tile_cell_sum(const float* W, int cx, int cy, int cz) {
-  using T = DepTile<TX, TY, TZ>;
-  float s = 0.0f;
+    for (int o = 0; o < 8; ++o) v[o] += __shfl_xor(v[o], off, 64);
 #pragma unroll
   for (int o = 0; o < 8; ++o) {
-    const int b = ((cz + 1 - (o >> 2)) * T::BY + (cy + 1 - ((o >> 1) & 1))) * T::BX +
-                  (cx + 1 - (o & 1));
-    s += W[o * T::NB + b];
+    v[o] = dpp_add<0x128>(v[o]);   // row_ror:8
+    v[o] = dpp_add<0x124>(v[o]);   // row_ror:4
+    v[o] = dpp_add<0x4e>(v[o]);    // quad_perm [2,3,0,1]
+    v[o] = dpp_add<0xb1>(v[o]);    // quad_perm [1,0,3,2]
   }
-  return s;
 }
 
-// tile t of a sample: x fastest
-template <int TX, int TY, int TZ>
-__device__ __forceinline__ void tile_origin(int n, int& x0, int& y0, int& z0) {
+// acc[o] += prod_d (o_d ? w1_d : 1 - w1_d), the products formed as (wx wy) wz
+__device__ __forceinline__ void add_weights(const float3& w, float (&acc)[8]) {
+#pragma unroll
+  for (int o = 0; o < 8; ++o)
+    acc[o] = fmaf(wsel(w.x, o & 1) * wsel(w.y, (o >> 1) & 1), wsel(w.z, o >> 2), acc[o]);
+}
+
+// the sums of one particle of weights w: the CIC weights, or (VEC) these times its vector q
+template <int NV>
+__device__ __forceinline__ void add_particle(const float3& w, const float3& q,
+                                             float (&acc)[NV][8]) {
+  if constexpr (NV == 3) {
+    add_corners(w.x, w.y, w.z, q.x, acc[0]);
+    add_corners(w.x, w.y, w.z, q.y, acc[1]);
+    add_corners(w.x, w.y, w.z, q.z, acc[2]);
+  } else {
+    add_weights(w, acc[0]);
+  }
+}
+
+// Column walk over the cell planes [z0, z0 + planes) of the column at (x0, y0).  Loads run
+// ahead of the sums: while a plane is summed, the first kDepAhead particles of the next
+// planes' bins (D planes ahead) and the bounds of the one after are on their way.
+// VEC: out[3][nc] += scale times the deposit of field[3][np], component by component through
+// LDS; the vectors are read through the particle ids, one plane ahead (256^3: 330 us with 838 MB;
+// gathering them into bin order first, as a pass per field, 102 + 321; a third of 960 threads
+// for each component: 410).  Else out = field + m_dm times the deposit of the weights + offset.
+template <int TX, int TY, bool VEC>
+__global__ void __launch_bounds__((DepCol<TX, TY>::THREADS)) deposit_kernel(
+    const uint32_t* __restrict__ start, const float3* __restrict__ sw1,
+    const uint32_t* __restrict__ sorted, const float* __restrict__ field, long long stride,
+    float m_dm, float offset, bool merged, float* __restrict__ out, int n, int planes,
+    const StepScal* __restrict__ tab) {
+  using T = DepCol<TX, TY>;
+  constexpr int NV = VEC ? 3 : 1, A = kDepAhead;
+  constexpr int D = VEC ? 1 : 2;         // planes between a particle's load and its use
+  __shared__ float W[2][8 * T::NB];
+  __shared__ int ncrowd[3];
+  __shared__ uint16_t crowd[T::NB];
+  __shared__ uint2 range[T::NB];
+  if (!sample_active(tab, blockIdx.y)) return;
   const int tx = n / TX, ty = n / TY;
   const int t = blockIdx.x;
-  x0 = (t % tx) * TX;
-  y0 = ((t / tx) % ty) * TY;
-  z0 = (t / (tx * ty)) * TZ;
-}
-
-template <int TX, int TY, int TZ>
-__global__ void __launch_bounds__(256) deposit_kernel(const uint32_t* __restrict__ start,
-                                                      const float4* __restrict__ spos,
-                                                      const float* __restrict__ rho_gas,
-                                                      long long rho_stride, float m_dm,
-                                                      float offset, float* __restrict__ out,
-                                                      int n, const StepScal* __restrict__ tab) {
-  using T = DepTile<TX, TY, TZ>;
-  __shared__ float W[8 * T::NB];
-  if (!sample_active(tab, blockIdx.y)) return;
-  const long long nc = static_cast<long long>(n) * n * n;
-  start += blockIdx.y * nc;
-  if (rho_gas) rho_gas += blockIdx.y * rho_stride;
-  out += blockIdx.y * nc;
-  int x0, y0, z0;
-  tile_origin<TX, TY, TZ>(n, x0, y0, z0);
-  deposit_tile<TX, TY, TZ>(start, spos, n, x0, y0, z0, W);
-  __syncthreads();
-  for (int t = threadIdx.x; t < T::NC; t += 256) {
-    const int cx = t % TX, cy = (t / TX) % TY, cz = t / (TX * TY);
-    const long long c = (static_cast<long long>(z0 + cz) * n + (y0 + cy)) * n + (x0 + cx);
-    const float g = rho_gas ? rho_gas[c] : 0.0f;
-    out[c] = g + m_dm * tile_cell_sum<TX, TY, TZ>(W, cx, cy, cz) + offset;
-  }
-}
-
-// Vector deposit: the three components go through the same 8-corner LDS table one after the
-// other (a third of the LDS of a 24-sum table, so twice as many blocks per CU); the CIC
-// weights of the first particle of each bin stay in registers across the three passes.
-// (Reading the vector field through the bins' particle ids, one component per pass, instead
-// of gathering it into bin order first, took 660 us against 432 + 104 us at 256^3: the
-// dependent loads of every pass and halo bin cost more than the gather.)
-template <int TX, int TY, int TZ>
-__global__ void __launch_bounds__(256) deposit_vec_kernel(const uint32_t* __restrict__ start,
-                                                          const float4* __restrict__ spos,
-                                                          const float4* __restrict__ sval,
-                                                          bool merged, float* __restrict__ out,
-                                                          int n, const StepScal* __restrict__ tab) {
-  using T = DepTile<TX, TY, TZ>;
-  constexpr int CPT = (T::NC + 255) / 256;   // cells per thread
-  __shared__ float W[8 * T::NB];
-  __shared__ int ncrowd;
-  __shared__ uint16_t crowd[T::NB];
-  const StepScal& sc = tab[blockIdx.y];
-  if (!sc.active) return;
-  if (threadIdx.x == 0) ncrowd = 0;
-  __syncthreads();
-  const float scale = merged ? sc.h_dm : sc.h_open;
-  const long long nc = static_cast<long long>(n) * n * n;
-  start += blockIdx.y * nc;
-  out += blockIdx.y * 3 * nc;
-  int x0, y0, z0;
-  tile_origin<TX, TY, TZ>(n, x0, y0, z0);
-  uint32_t lo[T::PER], hi[T::PER];
+  const int x0 = t % tx * TX;
+  const int y0 = t / tx % ty * TY;
+  const int z0 = t / (tx * ty) * planes;
+  const unsigned nn = n * n, nc = nn * n;
+  const int b = threadIdx.x, lane = threadIdx.x & 63;
+  start += static_cast<long long>(blockIdx.y) * nc;
+  out += static_cast<long long>(blockIdx.y) * NV * nc;
+  if (field) field += blockIdx.y * stride;
+  float scale = m_dm;
+  if (VEC) scale = merged ? tab[blockIdx.y].h_dm : tab[blockIdx.y].h_open;
+  const int col = wrapi(y0 - 1 + b / T::BX, n) * n + wrapi(x0 - 1 + b % T::BX, n);
+  // bounds of this thread's bin of plane k (cells z0 - 1 + k)
+  const auto bounds = [&](int k) {
+    if (b >= T::NB || k > planes) return make_uint2(0u, 0u);
+    const uint32_t* s = start + (wrapi(z0 - 1 + k, n) * nn + col);
+    return make_uint2(s[0], s[1]);
+  };
+  // particle i of a bin, or any where it has fewer
+  const auto at = [](const uint2& r, int i) { return r.x + i < r.y ? r.x + i : 0u; };
+  // the vector of the particle with global id g (the sample in the bits above nc)
+  const auto vector_of = [&](uint32_t g) {
+    const unsigned i = g & (nc - 1);
+    return make_float3(field[i], field[nc + i], field[2 * nc + i]);
+  };
+  constexpr int R = D + 1 + VEC;   // planes whose bounds are known
+  uint2 r[R];
 #pragma unroll
-  for (int k = 0; k < T::PER; ++k) {
-    const int b = threadIdx.x + 256 * k;
-    lo[k] = hi[k] = 0;
-    if (b < T::NB) {
-      const int bx = b % T::BX, by = (b / T::BX) % T::BY, bz = b / (T::BX * T::BY);
-      const long long cell = (static_cast<long long>(wrapi(z0 - 1 + bz, n)) * n +
-                              wrapi(y0 - 1 + by, n)) * n + wrapi(x0 - 1 + bx, n);
-      lo[k] = start[cell];
-      hi[k] = start[cell + 1];
+  for (int d = 0; d < R; ++d) r[d] = bounds(d);
+  float3 p[D][A], q[A];
+  uint32_t id[A];
+#pragma unroll
+  for (int d = 0; d < D; ++d)
+#pragma unroll
+    for (int i = 0; i < A; ++i) p[d][i] = sw1[at(r[d], i)];
+  if (VEC) {
+#pragma unroll
+    for (int i = 0; i < A; ++i) id[i] = sorted[at(r[0], i)];
+#pragma unroll
+    for (int i = 0; i < A; ++i) {
+      q[i] = vector_of(id[i]);
+      id[i] = sorted[at(r[1], i)];
     }
   }
-  // crowded bins: listed once, summed by waves for each component
-  bool crowded[T::PER];
-#pragma unroll
-  for (int k = 0; k < T::PER; ++k) {
-    const int b = threadIdx.x + 256 * k;
-    crowded[k] = b < T::NB && hi[k] - lo[k] > kCrowded;
-    if (crowded[k]) crowd[atomicAdd(&ncrowd, 1)] = static_cast<uint16_t>(b);
-  }
-  float w0[T::PER][3];   // CIC weights of the first particle of each bin
-  float4 v0[T::PER];
-#pragma unroll
-  for (int k = 0; k < T::PER; ++k) {
-    const uint32_t j = lo[k] < hi[k] ? lo[k] : 0u;
-    const float4 p = spos[j];
-    w0[k][0] = w1_of(p.x);
-    w0[k][1] = w1_of(p.y);
-    w0[k][2] = w1_of(p.z);
-    v0[k] = sval[j];
-  }
+  const int cx = b % TX, cy = b / TX;   // this thread's cell (b < NC)
+  const int wat = (cy + 1) * T::BX + cx + 1;
+  float ahead[NV][4];   // corners with o_z = 1, for the cell of the next plane
+  if (threadIdx.x < 3) ncrowd[threadIdx.x] = 0;
   __syncthreads();
-  float sum[3][CPT];
+  for (int k = 0, step = 0; k <= planes; ++k) {
+    float acc[NV][8];
 #pragma unroll
-  for (int v = 0; v < 3; ++v) {
-    crowded_bin_sums<TX, TY, TZ, true>(start, spos, sval, v, crowd, ncrowd, x0, y0, z0, n, W);
+    for (int v = 0; v < NV; ++v)
 #pragma unroll
-    for (int k = 0; k < T::PER; ++k) {
-      const int b = threadIdx.x + 256 * k;
-      if (b >= T::NB) continue;
-      if (crowded[k]) continue;   // summed by a wave
-      float acc[8];
+      for (int o = 0; o < 8; ++o) acc[v][o] = 0.0f;
+    float3 p0[A], q0[A];
 #pragma unroll
-      for (int o = 0; o < 8; ++o) acc[o] = 0.0f;
-      if (lo[k] < hi[k]) {
-        const float val = v == 0 ? v0[k].x : (v == 1 ? v0[k].y : v0[k].z);
-        add_corners(w0[k][0], w0[k][1], w0[k][2], val, acc);
-      }
-      for (uint32_t j = lo[k] + 1; j < hi[k]; ++j) {
-        const float4 p = spos[j];
-        const float4 q = sval[j];
-        const float val = v == 0 ? q.x : (v == 1 ? q.y : q.z);
-        add_corners(w1_of(p.x), w1_of(p.y), w1_of(p.z), val, acc);
-      }
-#pragma unroll
-      for (int o = 0; o < 8; ++o) W[o * T::NB + b] = acc[o];
+    for (int i = 0; i < A; ++i) {
+      p0[i] = p[0][i];
+      if (D == 2) p[0][i] = p[1][i];
+      if (VEC) q0[i] = q[i];
     }
-    __syncthreads();
+    const uint2 r0 = r[0];
 #pragma unroll
-    for (int i = 0; i < CPT; ++i) {
-      const int t = threadIdx.x + 256 * i;
-      sum[v][i] = 0.0f;
-      if (t < T::NC) {
-        const int cx = t % TX, cy = (t / TX) % TY, cz = t / (TX * TY);
-        sum[v][i] = tile_cell_sum<TX, TY, TZ>(W, cx, cy, cz);
+    for (int d = 0; d + 1 < R; ++d) r[d] = r[d + 1];
+    float before[NV];   // what the cell's sum is added to
+    const unsigned c = (z0 - 1 + k) * nn + (y0 + cy) * n + (x0 + cx);
+    if (k > 0 && b < T::NC) {
+#pragma unroll
+      for (int v = 0; v < NV; ++v)
+        before[v] = VEC ? out[static_cast<long long>(v) * nc + c] : (field ? field[c] : 0.0f);
+    }
+    if (k + D <= planes) {
+#pragma unroll
+      for (int i = 0; i < A; ++i) {
+        p[D - 1][i] = sw1[at(r[D - 1], i)];
+        if (VEC) q[i] = vector_of(id[i]);
+      }
+      if (VEC) {
+#pragma unroll
+        for (int i = 0; i < A; ++i) id[i] = sorted[at(r[R - 2], i)];
+      }
+      r[R - 1] = bounds(k + R);
+    }
+    const bool crowded = r0.y - r0.x > kCrowded;
+    if (crowded) {
+      // the list order only decides which wave sums the bin
+      const int e = atomicAdd(&ncrowd[k % 3], 1);
+      crowd[e] = static_cast<uint16_t>(b);
+      range[e] = r0;
+    } else if (b < T::NB) {
+#pragma unroll
+      for (int i = 0; i < A; ++i)
+        if (r0.x + i < r0.y) add_particle<NV>(p0[i], q0[i], acc);
+      for (uint32_t j = r0.x + A; j < r0.y; j += A) {
+#pragma unroll
+        for (int i = 0; i < A; ++i) {
+          const uint32_t ji = min(j + i, r0.y - 1);
+          p0[i] = sw1[ji];
+          if (VEC) q0[i] = vector_of(sorted[ji]);
+        }
+#pragma unroll
+        for (int i = 0; i < A; ++i)
+          if (j + i < r0.y) add_particle<NV>(p0[i], q0[i], acc);
       }
     }
-    __syncthreads();
-  }
 #pragma unroll
-  for (int i = 0; i < CPT; ++i) {
-    const int t = threadIdx.x + 256 * i;
-    if (t >= T::NC) continue;
-    const int cx = t % TX, cy = (t / TX) % TY, cz = t / (TX * TY);
-    const long long c = (static_cast<long long>(z0 + cz) * n + (y0 + cy)) * n + (x0 + cx);
+    for (int v = 0; v < NV; ++v, ++step) {
+      float* w = W[step & 1];
+      if (b < T::NB && !crowded) {
 #pragma unroll
-    for (int v = 0; v < 3; ++v) out[v * nc + c] += scale * sum[v][i];
+        for (int o = 0; o < 8; ++o) w[o * T::NB + b] = acc[v][o];
+      }
+      __syncthreads();
+      const int count = ncrowd[k % 3];
+      if (count > 0) {
+        for (int e = b >> 6; e < count; e += T::THREADS / 64) {
+          const int bin = crowd[e];
+          const uint2 rc = range[e];
+          float s[1][8];
+#pragma unroll
+          for (int o = 0; o < 8; ++o) s[0][o] = 0.0f;
+          for (uint32_t j = rc.x + lane; j < rc.y; j += 64) {
+            const float3 pj = sw1[j];
+            if constexpr (VEC)
+              add_corners(pj.x, pj.y, pj.z,
+                          field[static_cast<long long>(v) * nc + (sorted[j] & (nc - 1))], s[0]);
+            else
+              add_weights(pj, s[0]);
+          }
+          wave_sum(s[0]);
+          if (lane == 0) {
+#pragma unroll
+            for (int o = 0; o < 8; ++o) w[o * T::NB + bin] = s[0][o];
+          }
+        }
+        __syncthreads();
+      }
+      if (v == NV - 1 && threadIdx.x == 0) ncrowd[(k + 2) % 3] = 0;
+      if (b < T::NC) {
+        if (k > 0) {
+          float sum = 0.0f;
+#pragma unroll
+          for (int o = 0; o < 4; ++o) sum += w[o * T::NB + wat - (o >> 1) * T::BX - (o & 1)];
+#pragma unroll
+          for (int o = 0; o < 4; ++o) sum += ahead[v][o];
+          if (VEC)
+            out[static_cast<long long>(v) * nc + c] = fmaf(scale, sum, before[v]);
+          else
+            out[c] = before[v] + scale * sum + offset;
+        }
+#pragma unroll
+        for (int o = 0; o < 4; ++o)
+          ahead[v][o] = w[(4 + o) * T::NB + wat - (o >> 1) * T::BX - (o & 1)];
+      }
+    }
   }
 }
 
@@ -762,22 +670,18 @@ __global__ void __launch_bounds__(256) readout_g_kernel(const float4* __restrict
 
 // Stars formed in a step, associated with the dark matter (Sec. 2.4.1): each particle's
 // auxiliary field gains the CIC read-out of the step's new stars znew at its position.
-// Particles in bin order (spos, sorted: global ids, sample in the high bits), so that
-// neighbouring threads read neighbouring cells; samples that sit the step out are skipped.
+// Samples that sit the step out are skipped.
 __global__ void __launch_bounds__(256) star_readout_kernel(const float* __restrict__ znew,
-                                                           const float4* __restrict__ spos,
-                                                           const uint32_t* __restrict__ sorted,
+                                                           const float* __restrict__ pos,
                                                            float* __restrict__ aux, int n,
-                                                           long long total, int lnp,
+                                                           long long np,
                                                            const StepScal* __restrict__ tab) {
-  const long long j = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (j >= total) return;
-  const uint32_t id = sorted[j];
-  const long long smp = id >> lnp;
-  if (!sample_active(tab, static_cast<int>(smp))) return;
-  const float* zs = znew + (smp << lnp);   // n^3 cells = n^3 particles per sample
-  const float4 x = spos[j];
-  const Cic w = cic_of(x.x, x.y, x.z, n);
+  const long long i = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (i >= np || !sample_active(tab, blockIdx.y)) return;
+  znew += blockIdx.y * np;   // n^3 cells = n^3 particles per sample
+  pos += blockIdx.y * 3 * np;
+  aux += blockIdx.y * np;
+  const Cic w = cic_of(pos[i], pos[np + i], pos[2 * np + i], n);
   float v = 0.0f;
 #pragma unroll
   for (int oz = 0; oz < 2; ++oz)
@@ -786,8 +690,8 @@ __global__ void __launch_bounds__(256) star_readout_kernel(const float* __restri
 #pragma unroll
       for (int ox = 0; ox < 2; ++ox)
         v = fmaf(wsel(w.w1[0], ox) * wsel(w.w1[1], oy) * wsel(w.w1[2], oz),
-                 zs[corner(w, ox, oy, oz, n)], v);
-  aux[id] += v;
+                 znew[corner(w, ox, oy, oz, n)], v);
+  aux[i] += v;
 }
 
 __device__ __forceinline__ float wrap_pos(float x, float fn) {
@@ -1055,61 +959,67 @@ void launch_sort(hipStream_t st, const Bins& bins, const float* pos, const Batch
   const int tiles = static_cast<int>(scan_block_count(nbins));
   const bool direct = tiles <= kScanDirect;
   if (!direct) {
-    hipLaunchKernelGGL(scan_sums_kernel, dim3(tiles), dim3(kScanThreads), 0, st, bins.count,
-                       bins.block_sums);
+    hipLaunchKernelGGL(scan_sums_kernel, dim3(tiles), dim3(kScanThreads), 0, st,
+                       reinterpret_cast<const uint4*>(bins.count), bins.block_sums);
     DH_LAUNCH_CHECK();
   }
-  hipLaunchKernelGGL(scan_kernel, dim3(tiles), dim3(kScanThreads), 0, st, bins.count,
-                     direct ? nullptr : bins.block_sums, bins.start, tiles, bins.large);
+  hipLaunchKernelGGL(scan_kernel, dim3(tiles), dim3(kScanThreads), 0, st,
+                     reinterpret_cast<const uint4*>(bins.count),
+                     direct ? nullptr : bins.block_sums, reinterpret_cast<uint4*>(bins.start),
+                     tiles, bins.large);
   DH_LAUNCH_CHECK();
   hipLaunchKernelGGL(scatter_kernel, dim3(blocks_for(total, 256)), dim3(256), 0, st, bins.key,
                      bins.rank, bins.start, bins.sorted, total);
   DH_LAUNCH_CHECK();
   hipLaunchKernelGGL(bin_sort_gather_kernel, dim3(static_cast<unsigned>(nbins / 256)), dim3(256), 0,
-                     st, bins.start, bins.sorted, pos, bins.spos, lnp, bins.count, bins.large,
+                     st, bins.start, bins.sorted, pos, bins.sw1, lnp, bins.count, bins.large,
                      keep_ids);
   DH_LAUNCH_CHECK();
   hipLaunchKernelGGL(bin_sort_large_kernel, dim3(kLargeSortBlocks), dim3(256), 0, st, bins.start,
-                     bins.sorted, bins.large, pos, bins.spos, lnp);
+                     bins.sorted, bins.large, pos, bins.sw1, lnp);
   DH_LAUNCH_CHECK();
 }
 
-void launch_gather_sorted(hipStream_t st, const Bins& bins, const float* v, const Batch& b) {
-  const long long total = b.nc() * b.S;
-  hipLaunchKernelGGL(gather_sorted_kernel, dim3(blocks_for(total, 256)), dim3(256), 0, st,
-                     bins.sorted, v, bins.sval, total, log2_ll(b.nc()));
+namespace {
+
+template <int TX, int TY, bool VEC>
+void launch_columns(hipStream_t st, const Bins& bins, const float* field, long long stride,
+                    float m_dm, float offset, bool merged, float* out, const Batch& b) {
+  using T = DepCol<TX, TY>;
+  // longer walks read fewer halo planes, shorter ones fill the chip: 256^3 takes 129 / 120 / 123
+  // us with 4 / 8 / 16 planes (16384 blocks with 8), 128^3 21.8 / 22.0 / 23.0 with 2 / 4 / 8
+  // (4096 with 4; a clustered state 38 / 41 / 53, its vector deposit 59 / 54 / 59), 32^3 5.1 / 6.2 /
+  // 8.3 with 1 / 2 / 4 (256 with 1)
+  int planes = 8;
+  while (planes > 1 && b.nc() * b.S / (T::NC * planes) < 4096) planes >>= 1;
+  hipLaunchKernelGGL((deposit_kernel<TX, TY, VEC>),
+                     dim3(static_cast<unsigned>(b.nc() / (T::NC * planes)), b.S),
+                     dim3(T::THREADS), 0, st, bins.start, bins.sw1, bins.sorted,
+                     field, stride, m_dm, offset, merged, out, b.n, planes, b.tab);
   DH_LAUNCH_CHECK();
 }
+
+// columns of 32 x 4 cells (16 x 8 at n = 16)
+template <bool VEC>
+void launch_columns(hipStream_t st, const Bins& bins, const float* field, long long stride,
+                    float m_dm, float offset, bool merged, float* out, const Batch& b) {
+  if (b.n >= 32)
+    launch_columns<32, 4, VEC>(st, bins, field, stride, m_dm, offset, merged, out, b);
+  else
+    launch_columns<16, 8, VEC>(st, bins, field, stride, m_dm, offset, merged, out, b);
+}
+
+}  // namespace
 
 void launch_deposit(hipStream_t st, const Bins& bins, const float* rho_gas,
                     long long rho_stride, float m_dm, float offset, float* out, const Batch& b) {
-  // tiles of 32 x 4 x 4 cells (16 x 4 x 4 at n = 16): 26 KB of LDS, six blocks per CU
-  if (b.n >= 32) {
-    const unsigned tiles = static_cast<unsigned>(b.nc() / (32 * 4 * 4));
-    hipLaunchKernelGGL((deposit_kernel<32, 4, 4>), dim3(tiles, b.S), dim3(256), 0, st,
-                       bins.start, bins.spos, rho_gas, rho_stride, m_dm, offset, out, b.n, b.tab);
-  } else {
-    const unsigned tiles = static_cast<unsigned>(b.nc() / (16 * 4 * 4));
-    hipLaunchKernelGGL((deposit_kernel<16, 4, 4>), dim3(tiles, b.S), dim3(256), 0, st,
-                       bins.start, bins.spos, rho_gas, rho_stride, m_dm, offset, out, b.n, b.tab);
-  }
-  DH_LAUNCH_CHECK();
+  launch_columns<false>(st, bins, rho_gas, rho_stride, m_dm, offset, false, out, b);
 }
 
-void launch_deposit_vec(hipStream_t st, const Bins& bins, bool merged, float* out_accum,
-                        const Batch& b) {
+void launch_deposit_vec(hipStream_t st, const Bins& bins, const float* v, bool merged,
+                        float* out_accum, const Batch& b) {
   if (!b.tab) throw ArgError("deposit_vec: step table required");
-  // tiles of 32 x 4 x 4 cells (16 x 4 x 4 at n = 16)
-  if (b.n >= 32) {
-    const unsigned tiles = static_cast<unsigned>(b.nc() / (32 * 4 * 4));
-    hipLaunchKernelGGL((deposit_vec_kernel<32, 4, 4>), dim3(tiles, b.S), dim3(256), 0, st,
-                       bins.start, bins.spos, bins.sval, merged, out_accum, b.n, b.tab);
-  } else {
-    const unsigned tiles = static_cast<unsigned>(b.nc() / (16 * 4 * 4));
-    hipLaunchKernelGGL((deposit_vec_kernel<16, 4, 4>), dim3(tiles, b.S), dim3(256), 0, st,
-                       bins.start, bins.spos, bins.sval, merged, out_accum, b.n, b.tab);
-  }
-  DH_LAUNCH_CHECK();
+  launch_columns<true>(st, bins, v, 3 * b.nc(), 0.0f, 0.0f, merged, out_accum, b);
 }
 
 void launch_grad(hipStream_t st, const float* phi, float4* g4, const Batch& b) {
@@ -1125,12 +1035,10 @@ void launch_readout_g(hipStream_t st, const float4* g4, const float* pos, float*
   DH_LAUNCH_CHECK();
 }
 
-void launch_star_readout(hipStream_t st, const float* znew, const float4* spos,
-                         const uint32_t* sorted, float* aux, const Batch& b) {
-  if (!b.tab) throw ArgError("star read-out: step table required");
-  const long long total = b.nc() * b.S;
-  hipLaunchKernelGGL(star_readout_kernel, dim3(blocks_for(total, 256)), dim3(256), 0, st, znew,
-                     spos, sorted, aux, b.n, total, log2_ll(b.nc()), b.tab);
+void launch_star_readout(hipStream_t st, const float* znew, const float* pos, float* aux,
+                         const Batch& b) {
+  hipLaunchKernelGGL(star_readout_kernel, per_sample(b.nc(), b), dim3(256), 0, st, znew, pos, aux,
+                     b.n, b.nc(), b.tab);
   DH_LAUNCH_CHECK();
 }
 
