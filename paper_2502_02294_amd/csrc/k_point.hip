@@ -152,46 +152,70 @@ constexpr float kMaxLogitU = 17.5f;
 
 __device__ __forceinline__ float fast_exp(float x) { return __expf(x); }
 __device__ __forceinline__ float fast_log(float x) { return __logf(x); }
+// log x of a normal x for the estimates (one hardware log2; __logf adds a dozen instructions
+// for denormal x and the last bit)
+__device__ __forceinline__ float log_estimate(float x) {
+  return 0.69314718f * __builtin_amdgcn_logf(x);
+}
 // 1 - exp(-x) for x >= 0, relative error below 1e-4
 __device__ __forceinline__ float one_minus_exp_neg(float x) {
   return x < 1e-3f ? x * (1.0f - 0.5f * x) : 1.0f - fast_exp(-x);
 }
 __device__ __forceinline__ float fast_log_sigmoid(float y) {
-  return fminf(y, 0.0f) - fast_log(1.0f + fast_exp(-fabsf(y)));
+  return fminf(y, 0.0f) - log_estimate(1.0f + fast_exp(-fabsf(y)));
 }
 // log p - log(1 - p) from log p
 __device__ __forceinline__ float fast_logit_of_log(float logp) {
-  return logp - fast_log(1.0f - fast_exp(logp));
+  return logp - log_estimate(1.0f - fast_exp(logp));
 }
 
-__device__ __forceinline__ bool screened_out(float logit_pi, float logit_u, const SourceArgs& a) {
-  return (logit_pi + logit_u) / static_cast<float>(a.tau) < -110.0f;
+__device__ __forceinline__ bool screened_out(float logit_pi, float logit_u, float inv_tau) {
+  return (logit_pi + logit_u) * inv_tau < -110.0f;
 }
 __device__ __forceinline__ float logit_u_of(double u) {
   const float uf = static_cast<float>(u);
-  return fast_log(uf) - fast_log(1.0f - uf);
+  return log_estimate(uf) - log_estimate(1.0f - uf);
+}
+
+// a scalar that is the same in the whole wave, kept in a scalar register
+__device__ __forceinline__ float uniform_f(double x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(
+                                       __builtin_bit_cast(int, static_cast<float>(x))));
+}
+
+// What the FP32 passes over the cells (the screening estimate and the CFL speed) take from the
+// step's FP64 scalars, converted once a thread before its cells.
+struct CellScal {
+  float ia, efloor, gm2, gg1;
+  float t_per_e, inv_rho_mean, c_x, delta_c, k_rho, t_c, k_t, inv_tau;
+  int mode;
+};
+__device__ __forceinline__ CellScal cell_scalars(const SourceArgs& a, double gg1) {
+  return {uniform_f(1.0 / a.a), uniform_f(a.efloor),       uniform_f(a.gamma - 2.0),
+          uniform_f(gg1),       uniform_f(a.t_per_e),      uniform_f(a.inv_rho_mean),
+          uniform_f(a.c_x),     uniform_f(a.delta_c),      uniform_f(a.k_rho),
+          uniform_f(a.t_c),     uniform_f(a.k_t),          uniform_f(a.inv_tau),
+          a.mode};
 }
 
 // FP32 estimate of log pi0 - log(1 - pi0) of the plain source term (relaxed mode only)
 template <int NQ = 5>
-__device__ __forceinline__ float draw_logit_estimate(const float* q5, const SourceArgs& a) {
+__device__ __forceinline__ float draw_logit_estimate(const float* q5, const CellScal& a) {
   if (a.mode != 2) return INFINITY;
   const float rho = q5[0];
-  const float ir = rcp_approx(rho), ia = static_cast<float>(1.0 / a.a);
-  const float iar = ia * ir;
+  const float iar = a.ia * rcp_approx(rho);
   const float u0 = q5[1] * iar, u1 = q5[2] * iar, u2 = q5[3] * iar;
-  float e_raw = q5[4] * ia * iar - 0.5f * (u0 * u0 + u1 * u1 + u2 * u2);
-  if (NQ == 6 && !dual_total_branch(q5))
-    e_raw = q5[5] * ia * ia * pow_approx(rho, static_cast<float>(a.gamma - 2.0));
-  const float e = fmaxf(e_raw, static_cast<float>(a.efloor));
-  const float temp = e * static_cast<float>(a.t_per_e);
-  const float delta = rho * static_cast<float>(a.inv_rho_mean);
+  float e_raw = q5[4] * a.ia * iar - 0.5f * (u0 * u0 + u1 * u1 + u2 * u2);
+  if (NQ == 6 && !dual_total_branch(q5)) e_raw = q5[5] * a.ia * a.ia * pow_approx(rho, a.gm2);
+  const float e = fmaxf(e_raw, a.efloor);
+  const float temp = e * a.t_per_e;
+  const float delta = rho * a.inv_rho_mean;
   // x = eps dt / t_ff = c_x sqrt(delta)
-  const float psf = one_minus_exp_neg(static_cast<float>(a.c_x) * sqrt_approx(delta));
+  const float psf = one_minus_exp_neg(a.c_x * sqrt_approx(delta));
   if (!(psf > 1e-30f)) return INFINITY;
-  const float y1 = (delta - static_cast<float>(a.delta_c)) * static_cast<float>(a.k_rho);
-  const float y2 = (static_cast<float>(a.t_c) - temp) * static_cast<float>(a.k_t);
-  return fast_logit_of_log(fast_log(psf) + fast_log_sigmoid(y1) + fast_log_sigmoid(y2));
+  const float y1 = (delta - a.delta_c) * a.k_rho;
+  const float y2 = (a.t_c - temp) * a.k_t;
+  return fast_logit_of_log(log_estimate(psf) + fast_log_sigmoid(y1) + fast_log_sigmoid(y2));
 }
 
 // sigmoid(y) and log sigmoid(y) from one exponential: t = exp(-|y|),
@@ -264,17 +288,15 @@ __device__ __forceinline__ void load_q(const float* __restrict__ q, long long c,
 // flags a broken state.  With the dual-energy entropy (NQ = 6, gm2 = gamma - 2) c_s takes the
 // selected internal energy.
 template <int NQ = 5>
-__device__ __forceinline__ double cell_speed(const float* q5, double a, double gg1,
-                                             double efloor, float gm2 = 0.0f) {
+__device__ __forceinline__ float cell_speed(const float* q5, const CellScal& a) {
   const float rho = q5[0];
-  const float ia = static_cast<float>(1.0 / a);
+  const float ia = a.ia;
   const float iar = ia * rcp_approx(rho);
   const float u0 = q5[1] * iar, u1 = q5[2] * iar, u2 = q5[3] * iar;
   const float e_raw = q5[4] * ia * iar - 0.5f * (u0 * u0 + u1 * u1 + u2 * u2);
   float e_sel = e_raw;
-  if (NQ == 6 && !dual_total_branch(q5)) e_sel = q5[5] * ia * ia * pow_approx(rho, gm2);
-  const float cs =
-      sqrt_approx(static_cast<float>(gg1) * fmaxf(e_sel, static_cast<float>(efloor)));
+  if (NQ == 6 && !dual_total_branch(q5)) e_sel = q5[5] * ia * ia * pow_approx(rho, a.gm2);
+  const float cs = sqrt_approx(a.gg1 * fmaxf(e_sel, a.efloor));
   const float sp = (fmaxf(fabsf(u0), fmaxf(fabsf(u1), fabsf(u2))) + cs) * ia;
   // every component of the total energy enters e_raw, so a NaN or infinity anywhere in the
   // cell shows there (fmaxf and the floor would drop a NaN); the entropy is checked by itself
@@ -292,7 +314,7 @@ __device__ __forceinline__ void dual_close(float* q, double e_sn, float r1g) {
   if (dual_sync_branch(q)) q[5] = dual_internal(q) * r1g;
 }
 
-// Closing pass of a step over kRedPer cells per thread: gas half kick, optional tape copy,
+// Closing pass of a step over `per` cells per thread: gas half kick, optional tape copy,
 // source term, CFL block maximum of the result.  !FULL (the reverse pass's recomputation):
 // no star field and no CFL maxima, which only the forward run needs.  znew (optional): the
 // step's draw z of every cell (0 where no star forms), for the stars' read-out on the
@@ -301,8 +323,14 @@ __device__ __forceinline__ void dual_close(float* q, double e_sn, float r1g) {
 // CFL maxima are then left to the injection pass (partial may be null).
 // NQ = 6 (dual energy): the entropy also takes the injected energy, then the end-of-step
 // reset (dual_close); with the smoothed injection both follow in the injection pass.
+// Early on the pass is bounded by the arithmetic of the estimate and the CFL speed, so what is
+// the same in every cell is converted once (CellScal) and the estimate takes bare hardware
+// logarithms; five waves per SIMD (96 registers, nothing spilled) hide the loads: 256^3
+// 241 -> 209 us (13 fields: 4.2 TB/s), 128^3 45 -> 39, 13 x 64^3 74 -> 64; six waves or eight
+// with the source term's FP64 values in scratch: 215, 231.  NQ = 6 keeps its 141 registers (at
+// 96 it spills: 64^3 13.9 -> 16.6 us).
 template <bool FULL, int NQ>
-__global__ void __launch_bounds__(kRedThreads) close_step_kernel(
+__global__ void __launch_bounds__(kRedThreads, NQ == 5 ? 5 : 1) close_step_kernel(
     const float* q_in, float* q, const float4* __restrict__ g4, float* __restrict__ star,
     float* __restrict__ q_kicked, double gg1, double* partial, long long nc,
     const StepScal* __restrict__ tab, float* __restrict__ znew, float* __restrict__ sn_out, int per) {
@@ -321,8 +349,9 @@ __global__ void __launch_bounds__(kRedThreads) close_step_kernel(
   if (FULL) star += blockIdx.y * nc;
   if (znew) znew += blockIdx.y * nc;
   if (sn_out) sn_out += blockIdx.y * nc;
-  const float gm2 = static_cast<float>(a.gamma - 2.0), g1m = static_cast<float>(1.0 - a.gamma);
-  double vmax[1] = {0.0};
+  const CellScal cs = cell_scalars(a, gg1);
+  const float g1m = static_cast<float>(1.0 - a.gamma);
+  float vm = 0.0f;
   const long long base = static_cast<long long>(blockIdx.x) * kRedThreads * per;
   for (int r = 0; r < per; ++r) {
     const long long c = base + r * kRedThreads + threadIdx.x;
@@ -338,12 +367,12 @@ __global__ void __launch_bounds__(kRedThreads) close_step_kernel(
 #pragma unroll
       for (int k = 0; k < NQ; ++k) q_kicked[k * nc + c] = q5[k];
     }
-    const float lg = a.mode != 0 ? draw_logit_estimate<NQ>(q5, a) : 0.0f;
+    const float lg = cs.mode != 0 ? draw_logit_estimate<NQ>(q5, cs) : 0.0f;
     float zc = 0.0f, inj = 0.0f;
     double e_add = 0.0;   // energy injected into this cell
-    if (a.mode != 0 && !screened_out(lg, kMaxLogitU, a)) {
+    if (cs.mode != 0 && !screened_out(lg, kMaxLogitU, cs.inv_tau)) {
       const double u = starform_uniform(c, a);
-      if (!screened_out(lg, logit_u_of(u), a)) {
+      if (!screened_out(lg, logit_u_of(u), cs.inv_tau)) {
         const SrcCell s = source_eval<NQ>(q5, u, a);
         if (s.z != 0.0) {
           const double e_sn = a.a * a.a * s.rho * s.z * a.e0_code;
@@ -361,10 +390,12 @@ __global__ void __launch_bounds__(kRedThreads) close_step_kernel(
     if (NQ == 6 && !sn_out) dual_close(q5, e_add, pow_approx(q5[0], g1m));
     if (znew) znew[c] = zc;
     if (sn_out) sn_out[c] = inj;
+    if (q != q_in) q[c] = q5[0];   // the closing pass leaves the density as it is
 #pragma unroll
-    for (int k = (q == q_in ? 1 : 0); k < NQ; ++k) q[k * nc + c] = q5[k];
-    if (do_max) vmax[0] = fmax(vmax[0], cell_speed<NQ>(q5, a.a, gg1, a.efloor, gm2));
+    for (int k = 1; k < NQ; ++k) q[k * nc + c] = q5[k];
+    if (do_max) vm = fmaxf(vm, cell_speed<NQ>(q5, cs));
   }
+  double vmax[1] = {vm};
   if (do_max) block_reduce_store<1, true>(vmax, sample_partials(partial), partial_stride());
 }
 
@@ -407,9 +438,10 @@ __global__ void __launch_bounds__(kRedThreads) sn_inject_kernel(
   const SourceArgs& a = sc.src;
   sn += blockIdx.y * nc;
   q += blockIdx.y * NQ * nc;
-  const float gm2 = static_cast<float>(a.gamma - 2.0), g1m = static_cast<float>(1.0 - a.gamma);
+  const CellScal cs = cell_scalars(a, gg1);
+  const float g1m = static_cast<float>(1.0 - a.gamma);
   const unsigned n1 = static_cast<unsigned>(n - 1);
-  double vmax[1] = {0.0};
+  float vm = 0.0f;
   const long long base = static_cast<long long>(blockIdx.x) * kRedThreads * per;
   for (int r = 0; r < per; ++r) {
     const long long c = base + r * kRedThreads + threadIdx.x;
@@ -423,7 +455,7 @@ __global__ void __launch_bounds__(kRedThreads) sn_inject_kernel(
       dual_close(q6, add, pow_approx(q6[0], g1m));
       q[4 * nc + c] = q6[4];
       q[5 * nc + c] = q6[5];
-      if (partial) vmax[0] = fmax(vmax[0], cell_speed<NQ>(q6, a.a, gg1, a.efloor, gm2));
+      if (partial) vm = fmaxf(vm, cell_speed<NQ>(q6, cs));
       continue;
     }
     const float e4 = q[4 * nc + c] + add;
@@ -432,9 +464,10 @@ __global__ void __launch_bounds__(kRedThreads) sn_inject_kernel(
       float q5[5];
       load_q(q, c, nc, q5);
       q5[4] = e4;
-      vmax[0] = fmax(vmax[0], cell_speed(q5, a.a, gg1, a.efloor));
+      vm = fmaxf(vm, cell_speed(q5, cs));
     }
   }
+  double vmax[1] = {vm};
   if (partial) block_reduce_store<1, true>(vmax, sample_partials(partial), partial_stride());
 }
 
@@ -516,12 +549,12 @@ __global__ void __launch_bounds__(256) smooth27_kernel(const float* __restrict__
 // share through the entropy).  NQ = 6: T follows the selected internal energy.
 template <int NQ = 5>
 __device__ __forceinline__ void source_cell_vjp(const float* q5, long long c,
-                                                const SourceArgs& a, float* l5, double li,
-                                                double acc[2]) {
-  const float lg = draw_logit_estimate<NQ>(q5, a);
-  if (screened_out(lg, kMaxLogitU, a)) return;
+                                                const SourceArgs& a, const CellScal& cs, float* l5,
+                                                double li, double acc[2]) {
+  const float lg = draw_logit_estimate<NQ>(q5, cs);
+  if (screened_out(lg, kMaxLogitU, cs.inv_tau)) return;
   const double u = starform_uniform(c, a);
-  if (screened_out(lg, logit_u_of(u), a)) return;
+  if (screened_out(lg, logit_u_of(u), cs.inv_tau)) return;
   const SrcCell s = source_eval<NQ>(q5, u, a);
   const double le = l5[4];
   const double K = a.a * a.a * a.e0_code;
@@ -568,13 +601,13 @@ __device__ __forceinline__ void source_cell_vjp(const float* q5, long long c,
 // before the source term.  The draw and the injected energy are recomputed as the closing
 // pass made them.
 __device__ __forceinline__ void dual_close_vjp(const float* q, long long c, const SourceArgs& a,
-                                               float* l, double acc[2]) {
+                                               const CellScal& cs, float* l, double acc[2]) {
   double e_sn = 0.0;
-  if (a.mode != 0) {
-    const float lg = draw_logit_estimate<6>(q, a);
-    if (!screened_out(lg, kMaxLogitU, a)) {
+  if (cs.mode != 0) {
+    const float lg = draw_logit_estimate<6>(q, cs);
+    if (!screened_out(lg, kMaxLogitU, cs.inv_tau)) {
       const double u = starform_uniform(c, a);
-      if (!screened_out(lg, logit_u_of(u), a)) {
+      if (!screened_out(lg, logit_u_of(u), cs.inv_tau)) {
         const SrcCell s = source_eval<6>(q, u, a);
         if (s.z != 0.0) e_sn = a.a * a.a * s.rho * s.z * a.e0_code;
       }
@@ -609,7 +642,7 @@ __device__ __forceinline__ void dual_close_vjp(const float* q, long long c, cons
   // the injection: Et' = Et + e_sn, S' = S + e_sn r1g, e_sn = a^2 rho z E0
   if (e_sn != 0.0) lr += ls * e_sn * (1.0 - a.gamma) * r1g / static_cast<double>(q[0]);
   l[0] = static_cast<float>(lr);
-  if (a.mode != 0) source_cell_vjp<6>(q, c, a, l, le + ls * r1g, acc);
+  if (cs.mode != 0) source_cell_vjp<6>(q, c, a, cs, l, le + ls * r1g, acc);
 }
 
 // Adjoint of the closing pass of a step (plain source term): lam (in: adjoint after the
@@ -622,8 +655,10 @@ __device__ __forceinline__ void dual_close_vjp(const float* q, long long c, cons
 // every sample moves in both steps.
 // lam_inj (optional): the adjoint of the injected energy of each cell when the injection is
 // smoothed (the smoothing of the energy adjoint).
+// Bounded by its 29 fields (256^3: 400 us, 4.9 TB/s) at four waves per SIMD (128 registers; with
+// 139, three waves: 13 x 64^3 102 us against 88).
 template <bool OPEN, int NQ>
-__global__ void __launch_bounds__(kRedThreads) source_kick_vjp_kernel(
+__global__ void __launch_bounds__(kRedThreads, NQ == 5 ? 4 : 1) source_kick_vjp_kernel(
     const float* __restrict__ q_kick, const float4* __restrict__ g4, float* __restrict__ lam,
     float* __restrict__ lam_g, double* partial, long long nc, const StepScal* __restrict__ tab,
     const float* __restrict__ q_open, float* __restrict__ lam_g_open,
@@ -646,6 +681,7 @@ __global__ void __launch_bounds__(kRedThreads) source_kick_vjp_kernel(
     lam_g_open += blockIdx.y * 3 * nc;
     h_open = tab_open[blockIdx.y].h;
   }
+  const CellScal cs = cell_scalars(a, 0.0);
   double acc[2] = {0.0, 0.0};
   const long long base = static_cast<long long>(blockIdx.x) * kRedThreads * per;
   for (int r = 0; r < per; ++r) {
@@ -669,9 +705,9 @@ __global__ void __launch_bounds__(kRedThreads) source_kick_vjp_kernel(
     q5[2] = m[1];
     q5[3] = m[2];
     if (NQ == 6 && !lam_inj)
-      dual_close_vjp(q5, c, a, l5, acc);
-    else if (a.mode != 0)
-      source_cell_vjp<NQ>(q5, c, a, l5, lam_inj ? lam_inj[c] : l5[4], acc);
+      dual_close_vjp(q5, c, a, cs, l5, acc);
+    else if (cs.mode != 0)
+      source_cell_vjp<NQ>(q5, c, a, cs, l5, lam_inj ? lam_inj[c] : l5[4], acc);
     float lg[3];
     kick_cell_vjp(q5[0], m0, gv, h, l5, lg);
 #pragma unroll
@@ -815,7 +851,8 @@ __global__ void __launch_bounds__(kRedThreads) close_step_mlp_kernel(
   q_in += blockIdx.y * NQ * nc;
   q += blockIdx.y * NQ * nc;
   if (q_kicked) q_kicked += blockIdx.y * NQ * nc;
-  const float gm2 = static_cast<float>(a.gamma - 2.0), g1m = static_cast<float>(1.0 - a.gamma);
+  const CellScal cs = cell_scalars(a, gg1);
+  const float g1m = static_cast<float>(1.0 - a.gamma);
   g4 += blockIdx.y * nc;
   star += blockIdx.y * nc;
   if (znew) znew += blockIdx.y * nc;
@@ -827,7 +864,7 @@ __global__ void __launch_bounds__(kRedThreads) close_step_mlp_kernel(
   __syncthreads();   // the weights; from here on every wave works on its own cells
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int g = lane >> 4, cl = lane & 15;
-  double vmax[1] = {0.0};
+  float vm = 0.0f;
   const long long base = static_cast<long long>(blockIdx.x) * kRedThreads * per;
   for (int r = 0; r < per; ++r) {
     const long long c = base + r * kRedThreads + threadIdx.x;
@@ -867,10 +904,10 @@ __global__ void __launch_bounds__(kRedThreads) close_step_mlp_kernel(
     if (valid) {
       const float o0 = stage[wave][lane][5], o1 = stage[wave][lane][6];
       const float lg = closure_logit_estimate(o0, o1, a);
-      const double u = screened_out(lg, kMaxLogitU, a) ? 0.5 : starform_uniform(c, a);
+      const double u = screened_out(lg, kMaxLogitU, cs.inv_tau) ? 0.5 : starform_uniform(c, a);
       float zc = 0.0f, inj = 0.0f;
       double e_add = 0.0;   // energy injected into this cell
-      if (!screened_out(lg, kMaxLogitU, a) && !screened_out(lg, logit_u_of(u), a)) {
+      if (!screened_out(lg, kMaxLogitU, cs.inv_tau) && !screened_out(lg, logit_u_of(u), cs.inv_tau)) {
         const ClosureDraw d = closure_draw(o0, o1, u, a);
         if (d.z != 0.0) {
           const double e_sn = a.a * a.a * static_cast<double>(q5[0]) * d.z * a.e0_code;
@@ -887,12 +924,14 @@ __global__ void __launch_bounds__(kRedThreads) close_step_mlp_kernel(
       if (NQ == 6 && !sn_out) dual_close(q5, e_add, pow_approx(q5[0], g1m));
       if (znew) znew[c] = zc;
       if (sn_out) sn_out[c] = inj;
+      if (q != q_in) q[c] = q5[0];
 #pragma unroll
-      for (int k = (q == q_in ? 1 : 0); k < NQ; ++k) q[k * nc + c] = q5[k];
-      if (partial) vmax[0] = fmax(vmax[0], cell_speed<NQ>(q5, a.a, gg1, a.efloor, gm2));
+      for (int k = 1; k < NQ; ++k) q[k * nc + c] = q5[k];
+      if (partial) vm = fmaxf(vm, cell_speed<NQ>(q5, cs));
     }
     wave_sync();
   }
+  double vmax[1] = {vm};
   if (partial) {
     // the stage, free once every wave is done, holds the reduction (no LDS of its own, so
     // more blocks share a CU)
@@ -923,6 +962,7 @@ __global__ void __launch_bounds__(kRedThreads, 2) source_vjp_mlp_kernel(
   q += blockIdx.y * NQ * nc;
   lam += blockIdx.y * NQ * nc;
   if (lam_inj) lam_inj += blockIdx.y * nc;
+  const CellScal cs = cell_scalars(a, 0.0);
   const float g1m = static_cast<float>(1.0 - a.gamma);
   __shared__ uint4 fr[mlp::kFrAll * 64];
   __shared__ __attribute__((aligned(16))) float bias[mlp::kBias];
@@ -974,8 +1014,8 @@ __global__ void __launch_bounds__(kRedThreads, 2) source_vjp_mlp_kernel(
         if (valid) {
           const float o0 = stage[wave][lane][5], o1 = stage[wave][lane][6];
           const float lg = closure_logit_estimate(o0, o1, a);
-          const double u = screened_out(lg, kMaxLogitU, a) ? 0.5 : starform_uniform(c, a);
-          const bool drawn = !screened_out(lg, kMaxLogitU, a) && !screened_out(lg, logit_u_of(u), a);
+          const double u = screened_out(lg, kMaxLogitU, cs.inv_tau) ? 0.5 : starform_uniform(c, a);
+          const bool drawn = !screened_out(lg, kMaxLogitU, cs.inv_tau) && !screened_out(lg, logit_u_of(u), cs.inv_tau);
           ClosureDraw d{};
           if (drawn) {
             d = closure_draw(o0, o1, u, a);
@@ -1141,17 +1181,22 @@ __global__ void __launch_bounds__(kRedThreads) cfl_partial_kernel(const float* _
                                                                   double gg1, double efloor,
                                                                   float gm2, double* partial,
                                                                   long long nc, int per) {
-  const double a = a_cur[blockIdx.y];
+  CellScal cs{};
+  cs.ia = uniform_f(1.0 / a_cur[blockIdx.y]);
+  cs.efloor = static_cast<float>(efloor);
+  cs.gg1 = static_cast<float>(gg1);
+  cs.gm2 = gm2;
   q += blockIdx.y * NQ * nc;
-  double v[1] = {0.0};
+  float vm = 0.0f;
   const long long base = static_cast<long long>(blockIdx.x) * kRedThreads * per;
   for (int r = 0; r < per; ++r) {
     const long long c = base + r * kRedThreads + threadIdx.x;
     if (c >= nc) break;
     float q5[NQ];
     load_q<NQ>(q, c, nc, q5);
-    v[0] = fmax(v[0], cell_speed<NQ>(q5, a, gg1, efloor, gm2));
+    vm = fmaxf(vm, cell_speed<NQ>(q5, cs));
   }
+  double v[1] = {vm};
   block_reduce_store<1, true>(v, sample_partials(partial), partial_stride());
 }
 
