@@ -125,9 +125,8 @@ struct dh_sim {
   // scratch
   float *q2 = nullptr, *delta = nullptr, *cic = nullptr, *psi = nullptr, *fscratch = nullptr;
   float2 *spec = nullptr, *spec2 = nullptr, *tw = nullptr;
-  float4* g4 = nullptr;        // (-grad phi, 0) of the current potential
-  float4* g4b = nullptr;       // scratch acceleration field for the reverse pass and stages
-  int g4b_phi0_of = -1;         // g4b holds -grad of this step's phi0 (every sample moved), or -1
+  float3* g3 = nullptr;        // -grad phi of the current potential, for the particles
+  float3* g3b = nullptr;       // the same for the reverse pass and stages
   // Closing dark-matter half kicks left to the next step's kick-drift pass (one pass over the
   // particles instead of two): factor per sample, 0 when none.  Only the step loops of
   // run_to / forward / run_steps and the recomputation of the reverse pass defer, and they
@@ -173,6 +172,7 @@ struct dh_sim {
   // (same cells, same g): the step's start state and table
   bool open_pending = false;
   const float* open_q0 = nullptr;
+  const float* open_phi = nullptr;
   const StepScal* open_tab = nullptr;
   double* param_steps = nullptr;   // [cap][2 S] per-step dL/d(eps_sf, delta_c)
   double* host_params = nullptr;   // pinned: the loss's 2 S sums, then the steps used
@@ -482,7 +482,7 @@ void flush_kick(dh_sim* s) {
     tab[i] = e;
   }
   upload(s, s->cur_tab, tab.data(), static_cast<size_t>(s->S) * sizeof(StepScal));
-  dh::launch_kick(s->st, s->g4, s->pos, s->mom, Batch{s->n, s->S, s->cur_tab, s->nq});
+  dh::launch_kick(s->st, s->g3, s->pos, s->mom, Batch{s->n, s->S, s->cur_tab, s->nq});
   std::fill(s->kick_due.begin(), s->kick_due.end(), 0.0f);
   s->kick_pending = false;
 }
@@ -601,14 +601,13 @@ void poisson(dh_sim* s, const float* delta, float* phi_out, const Batch& b) {
   dh::fft_inverse_yx(s->st, s->spec, phi_out, s->tw, 1.0f, b);
 }
 
-// phi = Poisson(rho_gas + m_dm CIC(pos) - 1) and g4 = -grad(phi), with the bins of the
+// s->phi = Poisson(rho_gas + m_dm CIC(pos) - 1) and s->g3 = -grad(phi), with the bins of the
 // particle positions already built
-void potential_from_bins(dh_sim* s, const float* rho_gas, float* phi_out, float4* g4_out,
-                         const Batch& b) {
+void potential_from_bins(dh_sim* s, const float* rho_gas, const Batch& b) {
   dh::launch_deposit(s->st, s->bins, rho_gas, s->nq * s->nc, static_cast<float>(s->m_dm), -1.0f,
                      s->delta, b);
-  poisson(s, s->delta, phi_out, b);
-  dh::launch_grad(s->st, phi_out, g4_out, b);
+  poisson(s, s->delta, s->phi, b);
+  dh::launch_grad(s->st, s->phi, s->g3, b);
 }
 
 void state_changed(dh_sim* s) {
@@ -648,7 +647,7 @@ void close_pass(dh_sim* s, const float* q_in, float* q_kicked, bool full, bool r
   const bool smooth = s->cfg.sn_smooth && s->cfg.subgrid != DH_SUBGRID_OFF;
   const bool stars = readout && full && s->znew && s->cfg.subgrid != DH_SUBGRID_OFF;
   float* snb = sn ? sn : s->sn_buf;   // a tape keeps the injection field where it has room
-  dh::launch_close_step(s->st, q_in, s->q, s->g4, full ? s->star : nullptr, q_kicked,
+  dh::launch_close_step(s->st, q_in, s->q, s->phi, full ? s->star : nullptr, q_kicked,
                         s->cfg.gamma, full && !smooth ? s->cfl_red : nullptr, b, closure,
                         stars ? s->znew : nullptr, smooth ? snb : nullptr);
   if (smooth) dh::launch_sn_inject(s->st, snb, s->q, s->cfg.gamma, full ? s->cfl_red : nullptr, b);
@@ -667,6 +666,7 @@ void do_step(dh_sim* s, const StepPlan& sp, TapeStep* tp, bool defer, int store_
   const bool prev = s->kick_pending;
   const Batch b = batch(s, tab_of(s, sp));
   const float* pos_in = s->pos;
+  const float* phi_in = s->phi;   // phi_n, for the gas's opening kick
   if (tp) {
     tp->plan = sp;
     bool all = true;
@@ -679,6 +679,7 @@ void do_step(dh_sim* s, const StepPlan& sp, TapeStep* tp, bool defer, int store_
       std::swap(s->pos, tp->x0);
       std::swap(s->phi, tp->phi0);
       pos_in = tp->x0;
+      phi_in = tp->phi0;
     } else {
       copy_d2d(s, tp->q[0], s->q, s->nq * nc * s->S);
       copy_d2d(s, tp->x0, s->pos, 3 * np * s->S);
@@ -690,11 +691,11 @@ void do_step(dh_sim* s, const StepPlan& sp, TapeStep* tp, bool defer, int store_
     // the sweeps (the first one also applies the opening gas kick) and the closing pass write
     // their results straight into the tape
     const bool kept = recompute && store_k >= 0 && store_k < s->store_valid;
-    dh::launch_kick_drift(s->st, s->g4, pos_in, s->pos, s->mom, s->bins.key, nullptr, nullptr,
+    dh::launch_kick_drift(s->st, s->g3, pos_in, s->pos, s->mom, s->bins.key, nullptr, nullptr,
                           prev, b, kept ? nullptr : &s->bins);
     {
       KernelTimer kt(s, DH_KTIME_SWEEP_KICK);
-      dh::launch_sweep(s->st, tp->q[0], tp->q[2], b, sp.axes[0], s->g4);
+      dh::launch_sweep(s->st, tp->q[0], tp->q[2], b, sp.axes[0], phi_in);
     }
     for (int k = 1; k < 3; ++k) {
       KernelTimer kt(s, DH_KTIME_SWEEP);
@@ -704,13 +705,13 @@ void do_step(dh_sim* s, const StepPlan& sp, TapeStep* tp, bool defer, int store_
       // the forward kept this step's sort and potential: no sort, deposit or Poisson solve
       const StepStore& e = s->store[store_k];
       copy_d2d(s, s->phi, e.phi, nc * s->S);
-      dh::launch_grad(s->st, s->phi, s->g4, b);
+      dh::launch_grad(s->st, s->phi, s->g3, b);
       tp->vstart = e.start;
       tp->vsorted = e.sorted;
       tp->vsw1 = e.sw1;
     } else {
       dh::launch_sort(s->st, s->bins, s->pos, b, true, true);
-      potential_from_bins(s, tp->q[4], s->phi, s->g4, b);
+      potential_from_bins(s, tp->q[4], b);
       // the tape keeps this sort of x1 for the reverse pass; the next sort writes the tape's
       // former buffers
       std::swap(s->bins.start, tp->start);
@@ -727,23 +728,23 @@ void do_step(dh_sim* s, const StepPlan& sp, TapeStep* tp, bool defer, int store_
   } else {
     // opening half kicks with g_n (the gas one inside the first sweep), drift with
     // a(t + dt/2)
-    dh::launch_kick_drift(s->st, s->g4, s->pos, s->pos, s->mom, s->bins.key, nullptr, nullptr,
+    dh::launch_kick_drift(s->st, s->g3, s->pos, s->pos, s->mom, s->bins.key, nullptr, nullptr,
                           prev, b, &s->bins);
     // sweeps in the Strang order of the step (a sample that sits out is copied along)
     for (int k = 0; k < 3; ++k) {
       KernelTimer kt(s, k == 0 ? DH_KTIME_SWEEP_KICK : DH_KTIME_SWEEP);
-      dh::launch_sweep(s->st, s->q, s->q2, b, sp.axes[k], k == 0 ? s->g4 : nullptr);
+      dh::launch_sweep(s->st, s->q, s->q2, b, sp.axes[k], k == 0 ? phi_in : nullptr);
       std::swap(s->q, s->q2);
     }
     // Poisson at a(t + dt) from gas + DM (keys and their histogram were made by the drift)
     dh::launch_sort(s->st, s->bins, s->pos, b, true, store_k >= 0);
-    potential_from_bins(s, s->q, s->phi, s->g4, b);
+    potential_from_bins(s, s->q, b);
     // closing gas half kick with g_{n+1}, source term and the CFL maxima: one pass
     close_pass(s, s->q, nullptr, true, true, b, closure);
     if (store_k >= 0) keep_step(s, store_k);
   }
   // closing dark-matter half kick with g_{n+1} (deferred: the factor the table holds)
-  if (!defer) dh::launch_kick(s->st, s->g4, s->pos, s->mom, b);
+  if (!defer) dh::launch_kick(s->st, s->g3, s->pos, s->mom, b);
   DH_LAUNCH_CHECK();
   bool all = true;
   for (int i = 0; i < s->S; ++i) {
@@ -769,7 +770,7 @@ void do_step(dh_sim* s, const StepPlan& sp, TapeStep* tp, bool defer, int store_
 void refresh_potential(dh_sim* s) {
   const Batch b = batch(s, state_table(s));
   sort_particles(s, s->pos, b);
-  potential_from_bins(s, s->q, s->phi, s->g4, b);
+  potential_from_bins(s, s->q, b);
   s->phi_valid = true;
 }
 
@@ -865,7 +866,7 @@ void initial_conditions(dh_sim* s, const float* d_white) {
   dh::launch_fill(s->st, s->star, 0.0f, s->nc * s->S);
   if (s->aux) dh::launch_fill(s->st, s->aux, 0.0f, s->np * s->S);
   reset_clock(s);
-  potential_from_bins(s, s->q, s->phi, s->g4, batch(s, state_table(s)));
+  potential_from_bins(s, s->q, batch(s, state_table(s)));
   s->phi_valid = true;
   state_changed(s);
   s->initialised = true;
@@ -1143,7 +1144,7 @@ void load_ckpt(dh_sim* s, const Ckpt& c) {
   s->t = c.t;
   s->a = c.a;
   s->step = c.step;
-  dh::launch_grad(s->st, s->phi, s->g4, batch(s, nullptr));
+  dh::launch_grad(s->st, s->phi, s->g3, batch(s, nullptr));
   s->phi_valid = true;
   state_changed(s);
 }
@@ -1182,7 +1183,7 @@ void unstash_state(dh_sim* s) {
   s->t = c.t;
   s->a = c.a;
   s->step = c.step;
-  dh::launch_grad(s->st, s->phi, s->g4, batch(s, nullptr));
+  dh::launch_grad(s->st, s->phi, s->g3, batch(s, nullptr));
   s->phi_valid = true;
   state_changed(s);
 }
@@ -1197,14 +1198,14 @@ void unstash_state(dh_sim* s) {
 // finish_first_kick after the first step.  A sample that sat the step out keeps its adjoints.
 // defer_open: the step before is the next one to be processed (same tape): the opening gas
 // kick's adjoint may be left to its closing-pass adjoint (one pass over the cells).
-void opening_kick_vjp(dh_sim* s, const float* q0, const Batch& b) {
-  dh::launch_gas_kick_vjp(s->st, q0, s->g4b, s->lq, s->lg, b);
+void opening_kick_vjp(dh_sim* s, const float* q0, const float* phi0, const Batch& b) {
+  dh::launch_gas_kick_vjp(s->st, q0, phi0, s->lq, s->lg, b);
   dh::launch_grad_vjp(s->st, s->lg, nullptr, s->lphi, b);
 }
 
 void flush_open_vjp(dh_sim* s) {
   if (!s->open_pending) return;
-  opening_kick_vjp(s, s->open_q0, Batch{s->n, s->S, s->open_tab, s->nq});
+  opening_kick_vjp(s, s->open_q0, s->open_phi, Batch{s->n, s->S, s->open_tab, s->nq});
   s->open_pending = false;
 }
 
@@ -1215,17 +1216,13 @@ void step_vjp(dh_sim* s, const TapeStep& T, bool defer_open) {
   hipStream_t st = s->st;
   const bool source = s->cfg.subgrid != DH_SUBGRID_OFF;
   const bool closure = source && s->cfg.closure == DH_CLOSURE_MLP;
-  // source term and closing kicks (gas from Q4, DM at x1) -> lambda_g -> lambda_phi_{n+1}.
-  // phi1 of this step is phi0 of the next one (bit for bit, also across a checkpoint), whose
-  // gradient the previous call left in g4b when every sample moved in both steps
+  // source term and closing kicks (gas from Q4, DM at x1) -> lambda_g -> lambda_phi_{n+1}
   bool all = true;
   for (int i = 0; i < s->S; ++i) all = all && sp.smp[i].active;
-  const bool reuse = all && s->g4b_phi0_of == sp.step + 1;
   // with the dual-energy state and the smoothed injection the reset's adjoint below needs the
   // next step's opening kick taken first: not fused
-  const bool fuse_open = s->open_pending && reuse && !closure && !dual_smooth(s);
-  if (!fuse_open) flush_open_vjp(s);   // with the next step's g, still in g4b
-  if (!reuse) dh::launch_grad(st, T.phi1, s->g4b, b);
+  const bool fuse_open = s->open_pending && all && !closure && !dual_smooth(s);
+  if (!fuse_open) flush_open_vjp(s);   // with the next step's phi0
   const int nb = dh::source_vjp_blocks(s->n);
   // smoothed injection: the adjoint of each cell's injected energy is the smoothing of the
   // energy adjoint (the weights are symmetric); the next step's opening gas kick leaves the
@@ -1233,7 +1230,7 @@ void step_vjp(dh_sim* s, const TapeStep& T, bool defer_open) {
   const float* lam_inj = nullptr;
   if (source && s->cfg.sn_smooth && s->nq == 6) {
     // dual energy: the reset after the injection and the entropy's share of it first
-    dh::launch_inject_sync_vjp(st, T.q[4], s->g4b, T.sn, s->lq, s->sn_buf2, b);
+    dh::launch_inject_sync_vjp(st, T.q[4], T.phi1, T.sn, s->lq, s->sn_buf2, b);
     dh::launch_smooth27(st, s->sn_buf2, nc, s->sn_buf, b);
     lam_inj = s->sn_buf;
   } else if (source && s->cfg.sn_smooth) {
@@ -1242,13 +1239,13 @@ void step_vjp(dh_sim* s, const TapeStep& T, bool defer_open) {
   }
   if (closure) {
     dh::launch_source_vjp(st, T.q[5], s->lq, s->red, b, lam_inj);
-    dh::launch_gas_kick_vjp(st, T.q[4], s->g4b, s->lq, s->lg, b);
+    dh::launch_gas_kick_vjp(st, T.q[4], T.phi1, s->lq, s->lg, b);
   } else if (fuse_open) {
-    dh::launch_source_kick_vjp(st, T.q[4], s->g4b, s->lq, s->lg, s->red, b, s->open_q0, s->lg2,
+    dh::launch_source_kick_vjp(st, T.q[4], T.phi1, s->lq, s->lg, s->red, b, s->open_q0, s->lg2,
                                s->open_tab, lam_inj);
     s->open_pending = false;
   } else {
-    dh::launch_source_kick_vjp(st, T.q[4], s->g4b, s->lq, s->lg, s->red, b, nullptr, nullptr,
+    dh::launch_source_kick_vjp(st, T.q[4], T.phi1, s->lq, s->lg, s->red, b, nullptr, nullptr,
                                nullptr, lam_inj);
   }
   if (source)
@@ -1267,21 +1264,19 @@ void step_vjp(dh_sim* s, const TapeStep& T, bool defer_open) {
   // Poisson (symmetric operator) and deposit at x1
   poisson(s, s->lphi2, s->ldelta, b);
   dh::launch_axpy(st, s->lq, s->ldelta, 1.0f, nc, s->nq * nc, nc, false, b);
-  // with the kicks' term at x1 (g4b still holds g_{n+1}) and the drift
+  // with the kicks' term at x1 (g_{n+1}) and the drift
   // x1 = x0 + p_half dt / a_h^2: lambda_p += (dt / a_h^2) lambda_x
+  dh::launch_grad(st, T.phi1, s->g3b, b);
   dh::launch_deposit_vjp_pos(st, s->ldelta, T.x1, static_cast<float>(s->m_dm), s->lx, s->lp,
-                             s->g4b, b);
-  // g_n from phi_n: the first sweep's input is Q0 after the opening gas kick with it
-  dh::launch_grad(st, T.phi0, s->g4b, b);
-  s->g4b_phi0_of = all ? sp.step : -1;
-  // sweeps in reverse
+                             s->g3b, b);
+  // sweeps in reverse; the first sweep's input is Q0 after the opening gas kick with phi_n
   for (int k = 2; k >= 0; --k) {
     {
       KernelTimer kt(s, DH_KTIME_SWEEP_VJP);
       if (k > 0)
         dh::launch_sweep_vjp(st, T.q[1 + k], s->lq, s->lq2, b, sp.axes[k]);
       else
-        dh::launch_sweep_vjp(st, T.q[0], s->lq, s->lq2, b, sp.axes[0], s->g4b);
+        dh::launch_sweep_vjp(st, T.q[0], s->lq, s->lq2, b, sp.axes[0], T.phi0);
     }
     std::swap(s->lq, s->lq2);
   }
@@ -1289,9 +1284,10 @@ void step_vjp(dh_sim* s, const TapeStep& T, bool defer_open) {
   if (defer_open && all && !closure) {
     s->open_pending = true;
     s->open_q0 = T.q[0];
+    s->open_phi = T.phi0;
     s->open_tab = tab_of(s, sp);
   } else {
-    opening_kick_vjp(s, T.q[0], b);
+    opening_kick_vjp(s, T.q[0], T.phi0, b);
   }
 }
 
@@ -1299,12 +1295,11 @@ void step_vjp(dh_sim* s, const TapeStep& T, bool defer_open) {
 void finish_first_kick(dh_sim* s, const TapeStep& T) {
   const Batch b = batch(s, tab_of(s, T.plan));
   hipStream_t st = s->st;
-  dh::launch_grad(st, T.phi0, s->g4b, b);
-  s->g4b_phi0_of = -1;
   dh::launch_fill(st, s->lg, 0.0f, 3 * s->nc * s->S);
   sort_particles(s, T.x0, b, true);
   dh::launch_deposit_vec(st, s->bins, s->lp, false, s->lg, b);
-  dh::launch_kick_vjp_pos(st, s->g4b, T.x0, s->lp, false, s->lx, b);
+  dh::launch_grad(st, T.phi0, s->g3b, b);
+  dh::launch_kick_vjp_pos(st, s->g3b, T.x0, s->lp, false, s->lx, b);
   dh::launch_grad_vjp(st, s->lg, s->lphi, s->lphi, b);
 }
 
@@ -1517,8 +1512,8 @@ int dh_create(const dh_config* cfg, dh_sim** out) {
     DH_HIP(hipMemset(s->bins.count, 0, static_cast<size_t>(nc) * sizeof(uint32_t)));
     s->bins.large = s->alloc<uint32_t>(1 + dh::large_bin_capacity(np));
     s->bins.sw1 = s->alloc<float3>(np);
-    s->g4 = s->alloc<float4>(nc);
-    s->g4b = s->alloc<float4>(nc);
+    s->g3 = s->alloc<float3>(nc);
+    s->g3b = s->alloc<float3>(nc);
     s->cfl_red = s->alloc<double>(static_cast<long long>(dh::cfl_blocks(n)) * S + 1);
     s->red_blocks = dh::sum_blocks(s->nc);
     // 8 conservation sums, 2 loss or source sums, or up to n / 2 spectrum sums per sample
@@ -1779,7 +1774,7 @@ int dh_set_field(dh_sim* s, dh_field f, const float* d_in) {
         break;
       case DH_FIELD_PHI:
         copy_d2d(s, s->phi, d_in, nc * S);
-        dh::launch_grad(s->st, s->phi, s->g4, batch(s, nullptr));
+        dh::launch_grad(s->st, s->phi, s->g3, batch(s, nullptr));
         s->phi_valid = true;
         break;
       default: return fail(s, DH_E_INVAL, "field cannot be set");
@@ -1925,7 +1920,6 @@ int dh_backward(dh_sim* s, const float* d_grad_rho, float* d_grad_white, double*
     const int S = s->S;
     const long long nc = s->nc, np = s->np;
     const int nsteps = s->fwd_steps;
-    s->g4b_phi0_of = -1;
     s->open_pending = false;
     const int K = s->cfg.ckpt_every;
     if (!s->lq) {
@@ -2251,9 +2245,8 @@ int dh_stage_readout(dh_sim* s, const float* d_phi, const float* d_pos, float* d
   if (!s || !d_phi || !d_pos || !d_g) return DH_E_INVAL;
   return guarded(s, [&]() -> int {
     const Batch one{s->n, 1, nullptr, s->nq};
-    dh::launch_grad(s->st, d_phi, s->g4b, one);
-    s->g4b_phi0_of = -1;
-    dh::launch_readout_g(s->st, s->g4b, d_pos, d_g, one);
+    dh::launch_grad(s->st, d_phi, s->g3b, one);
+    dh::launch_readout_g(s->st, s->g3b, d_pos, d_g, one);
     return DH_OK;
   });
 }

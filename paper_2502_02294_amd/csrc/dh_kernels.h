@@ -52,14 +52,14 @@ __device__ __forceinline__ bool sample_active(const StepScal* tab, int smp) {
 }
 
 // ---- hydro (k_hydro.hip): one sweep with dt, h1, h2 of the table (tab required)
-// With g4 (the first sweep of a step): the opening gas half kick (the table's h) is applied
+// With phi (the first sweep of a step): the opening gas half kick (the table's h) is applied
 // to each cell as it is loaded.
 void launch_sweep(hipStream_t st, const float* qin, float* qout, const Batch& b, int axis,
-                  const float4* g4 = nullptr);
-// adjoint of one sweep: lam_in = (dU'/dU)^T lam_out at U = qin (not in place); with g4 (the
+                  const float* phi = nullptr);
+// adjoint of one sweep: lam_in = (dU'/dU)^T lam_out at U = qin (not in place); with phi (the
 // first sweep of a step) U is qin after the opening gas half kick, applied again on load
 void launch_sweep_vjp(hipStream_t st, const float* qin, const float* lam_out, float* lam_in,
-                      const Batch& b, int axis, const float4* g4 = nullptr);
+                      const Batch& b, int axis, const float* phi = nullptr);
 
 // ---- particle mesh (k_pm.hip)
 // Keys are global bins: sample * n^3 + CIC base cell, so one counting sort orders the
@@ -95,30 +95,30 @@ void launch_deposit(hipStream_t st, const Bins& bins, const float* rho_gas,
 // scale = h_open (merged: h_dm) of the table
 void launch_deposit_vec(hipStream_t st, const Bins& bins, const float* v, bool merged,
                         float* out_accum, const Batch& b);
-// g4 = (-grad phi, 0) by two-point central differences
-void launch_grad(hipStream_t st, const float* phi, float4* g4, const Batch& b);
-// g at particles: out[3][np] = CIC read-out of g4
-void launch_readout_g(hipStream_t st, const float4* g4, const float* pos, float* out,
+// g3 = g = -grad(phi) by two-point central differences
+void launch_grad(hipStream_t st, const float* phi, float3* g3, const Batch& b);
+// g at particles: out[3][np] = CIC read-out of g3
+void launch_readout_g(hipStream_t st, const float3* g3, const float* pos, float* out,
                       const Batch& b);
 // opening kick (h_open) + drift (drift) + keys: positions read from pos_in and written to pos
 // (the same array for an update in place); optional copies of the new momenta and positions.
 // prev: first the previous step's closing kick (h_prev of the table), as launch_kick would.
 // count_into (optional, key == count_into->key): also the histogram of the following
 // launch_sort(..., counted = true) (arrival ranks)
-void launch_kick_drift(hipStream_t st, const float4* g4, const float* pos_in, float* pos,
+void launch_kick_drift(hipStream_t st, const float3* g3, const float* pos_in, float* pos,
                        float* mom, uint32_t* key, float* mom_copy, float* pos_copy, bool prev,
                        const Batch& b, const Bins* count_into = nullptr);
 // closing kick p += h_close g(x)
-void launch_kick(hipStream_t st, const float4* g4, const float* pos, float* mom, const Batch& b);
+void launch_kick(hipStream_t st, const float3* g3, const float* pos, float* mom, const Batch& b);
 // adjoint of p' = p + k g(x) with respect to x: lam_x += k sum_c dw/dx (g_c . lam_p'), with
 // k = h_open (merged: h_dm) of the table
-void launch_kick_vjp_pos(hipStream_t st, const float4* g4, const float* pos,
+void launch_kick_vjp_pos(hipStream_t st, const float3* g3, const float* pos,
                          const float* lam_p, bool merged, float* lam_x, const Batch& b);
 // adjoint of the deposit wrt positions: lam_x += mass sum_c lam_delta_c dw_c/dx; with lam_p
-// (table required), first (with g4) the merged kicks' term of launch_kick_vjp_pos and last
+// (table required), first (with g3) the merged kicks' term of launch_kick_vjp_pos and last
 // the drift's adjoint lam_p += drift lam_x
 void launch_deposit_vjp_pos(hipStream_t st, const float* lam_delta, const float* pos,
-                            float mass, float* lam_x, float* lam_p, const float4* g4,
+                            float mass, float* lam_x, float* lam_p, const float3* g3,
                             const Batch& b);
 // y[s] += a x[s] over `count` values per sample (strides ys, xs); a times the table's drift
 // factor if by_drift
@@ -181,16 +181,16 @@ void launch_fli_obs(hipStream_t st, const float* q, double a, double irm, double
 
 // ---- pointwise / reductions (k_point.hip)
 // (the opening gas half kick is applied inside the first sweep of a step: launch_sweep)
-void launch_gas_kick_vjp(hipStream_t st, const float* q_before, const float4* g4, float* lam_q,
+void launch_gas_kick_vjp(hipStream_t st, const float* q_before, const float* phi, float* lam_q,
                          float* lam_g, const Batch& b);
-// closing pass of a step, from q_in (may equal q) into q: gas half kick with g4, optional
+// closing pass of a step, from q_in (may equal q) into q: gas half kick with phi, optional
 // copy of the kicked state to q_kicked (tape), source term (if src.mode != 0; with the
 // learned closure if `closure`), FP64 block maxima of the CFL speed of the result at src.a
 // into block_max[S][cfl_blocks(n)].  star and block_max both null (plain source only): the
 // star field and the CFL maxima are skipped (the reverse pass's recomputation).  znew: the
 // step's draw of every cell (0 where none; needs star).  sn_out: the supernova energy of
 // every cell goes there instead of into the cell (for launch_sn_inject; block_max null).
-void launch_close_step(hipStream_t st, const float* q_in, float* q, const float4* g4,
+void launch_close_step(hipStream_t st, const float* q_in, float* q, const float* phi,
                        float* star, float* q_kicked, double gamma, double* block_max,
                        const Batch& b, bool closure, float* znew = nullptr,
                        float* sn_out = nullptr);
@@ -203,9 +203,9 @@ void launch_sn_inject(hipStream_t st, const float* sn, float* q, double gamma, d
 void launch_smooth27(hipStream_t st, const float* in, long long in_stride, float* out,
                      const Batch& b);
 // dual-energy state: adjoint of the smoothed injection and the reset after it, at q4 (the state
-// after the sweeps) with the closing gas kick (g4) and the step's injection field sn; lam
+// after the sweeps) with the closing gas kick (phi) and the step's injection field sn; lam
 // updated in place, lam_add[s][n^3] = adjoint of each cell's smoothed energy
-void launch_inject_sync_vjp(hipStream_t st, const float* q4, const float4* g4, const float* sn,
+void launch_inject_sync_vjp(hipStream_t st, const float* q4, const float* phi, const float* sn,
                             float* lam, float* lam_add, const Batch& b);
 // adjoint of the source term with the learned closure; dL/d(eps_sf, delta_c) partials per
 // block: partials[(v S + s) nb + block], nb = source_vjp_blocks(n).  lam_inj: adjoint of
@@ -213,12 +213,12 @@ void launch_inject_sync_vjp(hipStream_t st, const float* q4, const float4* g4, c
 void launch_source_vjp(hipStream_t st, const float* q_before, float* lam_q, double* partials,
                        const Batch& b, const float* lam_inj = nullptr);
 // adjoint of the closing pass with the plain source term (or none, src.mode 0) from the
-// state q_kick before the closing gas half kick with g4 (the kicked state is recomputed):
+// state q_kick before the closing gas half kick with phi (the kicked state is recomputed):
 // the source, then the kick (lam_g = adjoint of g), in one pass; partials as
 // launch_source_vjp (zeros without source).  With q_open: first the adjoint of the next
-// step's opening gas kick (its start state q_open, table tab_open, the same g4; every sample
+// step's opening gas kick (its start state q_open, table tab_open, the same phi; every sample
 // active in both steps), its adjoint of g into lam_g_open.
-void launch_source_kick_vjp(hipStream_t st, const float* q_kick, const float4* g4,
+void launch_source_kick_vjp(hipStream_t st, const float* q_kick, const float* phi,
                             float* lam_q, float* lam_g, double* partials, const Batch& b,
                             const float* q_open = nullptr, float* lam_g_open = nullptr,
                             const StepScal* tab_open = nullptr, const float* lam_inj = nullptr);

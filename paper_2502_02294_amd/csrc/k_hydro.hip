@@ -62,7 +62,7 @@ __device__ __forceinline__ void face_l_coef(float f0, float fp1, float fp2, floa
 
 // ------------------------------------------------------------------------------- forward x
 // Whole rows in LDS, one cell per thread; the limited stage-2 flux is formed once per face.
-// KICK (the first sweep of a step): the opening gas half kick with g4 and the table's h is
+// KICK (the first sweep of a step): the opening gas half kick with g of phi and the table's h is
 // applied to each cell as it is loaded (the reverse pass applies it again, so the kicked state
 // is not stored).
 template <bool KICK, int NQ>
@@ -70,7 +70,7 @@ __global__ void __launch_bounds__(kRowThreads) sweep_x_kernel(const float* __res
                                                               float* __restrict__ qout, int n,
                                                               long long nc,
                                                               const StepScal* __restrict__ tab,
-                                                              const float4* __restrict__ g4) {
+                                                              const float* __restrict__ phi) {
   __shared__ float FR[NQ][kRowCells];
   __shared__ float FL[NQ][kRowCells];
   const long long base = static_cast<long long>(blockIdx.x) * kRowCells;
@@ -93,7 +93,8 @@ __global__ void __launch_bounds__(kRowThreads) sweep_x_kernel(const float* __res
   for (int c = 0; c < NQ; ++c) u[c] = qin[c * nc + base + j];
   if (KICK) {
     float m[3] = {u[1], u[2], u[3]};
-    kick_cell(u[0], g4[blockIdx.y * nc + base + j], sc.h, m, u[4]);
+    kick_cell(u[0], mesh_g(phi + blockIdx.y * nc, static_cast<unsigned>(base + j), log2_side(nc)),
+              sc.h, m, u[4]);
     u[1] = m[0];
     u[2] = m[1];
     u[3] = m[2];
@@ -146,13 +147,31 @@ constexpr int kAhead = 4;   // cells loaded ahead of the one being split
 // The opening gas kick applied to a loaded state in place (the first sweep of a step).  The
 // walks load g two (forward) or one (adjoint) visits before a cell is first used and kick it
 // then: kicking on load would make a visit wait for the loads of the cells ahead.
-template <int NQ>
-__device__ __forceinline__ void kick_loaded(float (&u)[NQ], const float (&g)[3], float h) {
+// (side: potentials at x - 1, x + 1 and beside the cell on the axis that is neither x nor D)
+template <int D, int NQ>
+__device__ __forceinline__ void kick_loaded(float (&u)[NQ], const float* side, float below,
+                                            float above, float h) {
+  const float gx = half_difference(side[1], side[0]), go = half_difference(side[3], side[2]);
+  const float gd = half_difference(above, below);
   float m[3] = {u[1], u[2], u[3]};
-  kick_cell(u[0], make_float4(g[0], g[1], g[2], 0.0f), h, m, u[4]);
+  kick_cell(u[0], make_float4(gx, D == 1 ? gd : go, D == 1 ? go : gd, 0.0f), h, m, u[4]);
   u[1] = m[0];
   u[2] = m[1];
   u[3] = m[2];
+}
+
+__device__ __forceinline__ float ld_byte(const char* p, unsigned off) {
+  return *reinterpret_cast<const float*>(p + off);
+}
+
+// bytes from a cell of column (x, other) to its neighbours at x - 1, x + 1, other - 1, other + 1
+template <int D>
+__device__ __forceinline__ void walk_sides(int n, int x, int other, int (&side)[4]) {
+  const int so = D == 1 ? n * n : n;
+  side[0] = 4 * (((x - 1) & (n - 1)) - x);
+  side[1] = 4 * (((x + 1) & (n - 1)) - x);
+  side[2] = 4 * (((other - 1) & (n - 1)) - other) * so;
+  side[3] = 4 * (((other + 1) & (n - 1)) - other) * so;
 }
 
 // The splits of the cells with which a pipeline is filled at every kHead-th cell of a pencil
@@ -183,7 +202,8 @@ struct WalkFwd {
   float f2[2][NQ];            // limited stage-2 face (k - 3 - j) + 1/2 in slot (i - j) & 1
   float dr[2][NQ], dl[2][NQ];  // upper slopes of face (k - 3 - j) + 1/2 in slot (i - j) & 1: the
                              // lower slopes of the next face
-  float g[4][3];              // first sweep: g of cell k + 2 - j in slot (i + 2 - j) & 3
+  float g[4][4];              // first sweep: potentials beside cell k + 2 - j, (i + 2 - j) & 3
+  float c[8];                 // and of cell k + 3 - j itself, (i + 3 - j) & 7
 };
 
 template <int NQ>
@@ -192,8 +212,10 @@ struct WalkPtr {
   float* __restrict__ o[NQ];
   unsigned base, stride;   // in bytes
   int n;
-  // opening gas kick on load (first sweep of a step): g of the sample's cells, the half kick
-  const char* g4;
+  // opening gas kick on load (first sweep of a step): potential of the sample's cells, where the
+  // four cells beside a cell of the column lie from it (bytes), the half kick
+  const char* phi;
+  int side[4];
   float h;
   // byte offset of cell k of the column (periodic)
   __device__ __forceinline__ unsigned at(int k) const {
@@ -215,14 +237,12 @@ __device__ __forceinline__ void walk_load(const WalkPtr<NQ>& p, int kk, float (&
   for (int c = 0; c < NQ; ++c) u[c] = p.ld(c, off);
 }
 
-// g of cell kk of the column (the float4 of cell i is at byte 16 i, i.e. 4 times the byte
-// offset of its float)
+// potentials beside cell kk of the column
 template <int NQ>
-__device__ __forceinline__ void walk_load_g(const WalkPtr<NQ>& p, int kk, float (&g)[3]) {
-  const float4 v = *reinterpret_cast<const float4*>(p.g4 + 4ull * p.at(kk));
-  g[0] = v.x;
-  g[1] = v.y;
-  g[2] = v.z;
+__device__ __forceinline__ void walk_load_side(const WalkPtr<NQ>& p, int kk, float (&g)[4]) {
+  const unsigned off = p.at(kk);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) g[i] = ld_byte(p.phi, off + p.side[i]);
 }
 
 template <int D, int I, int STAGE, bool HEAD, bool KICK, int NQ>
@@ -238,9 +258,10 @@ __device__ __forceinline__ void walk_fwd_visit(WalkFwd<D, NQ>& w, const WalkPtr<
   constexpr int p0 = I & 1, p1 = (I + 1) & 1;
   walk_load<NQ>(p, k + kAhead, w.u[sa]);
   if (KICK) {
-    // g two visits ahead; cell k, first used now, takes the opening kick
-    walk_load_g<NQ>(p, k + 2, w.g[(I + 2) & 3]);
-    kick_loaded(w.u[s0], w.g[I & 3], p.h);
+    // potentials two visits ahead; cell k, first used now, takes the opening kick
+    walk_load_side<NQ>(p, k + 2, w.g[(I + 2) & 3]);
+    w.c[(I + 3) & 7] = ld_byte(p.phi, p.at(k + 3));
+    kick_loaded<D>(w.u[s0], w.g[I & 3], w.c[(I + 7) & 7], w.c[(I + 1) & 7], p.h);
   }
   float l1[NQ];
   split_flux<D, NQ, q1, q1>(w.u[s0], h1, w.r1[p0], l1);
@@ -291,7 +312,7 @@ __global__ void __launch_bounds__(256) sweep_walk_kernel(const float* __restrict
                                                          float* __restrict__ qout, int n,
                                                          long long nc, int seg_len, int nseg,
                                                          const StepScal* __restrict__ tab,
-                                                         const float4* __restrict__ g4) {
+                                                         const float* __restrict__ phi) {
   int x, other, seg;
   walk_thread(n, x, other, seg);
   if (seg >= nseg) return;
@@ -307,7 +328,8 @@ __global__ void __launch_bounds__(256) sweep_walk_kernel(const float* __restrict
     p.q[c] = qin + (blockIdx.y * NQ + c) * nc;
     p.o[c] = qout + (blockIdx.y * NQ + c) * nc;
   }
-  p.g4 = KICK ? reinterpret_cast<const char*>(g4 + blockIdx.y * nc) : nullptr;
+  p.phi = KICK ? reinterpret_cast<const char*>(phi + blockIdx.y * nc) : nullptr;
+  walk_sides<D>(n, x, other, p.side);
   p.h = sc.h;
   if (!sc.active) {
     for (int i = 0; i < seg_len; ++i) {
@@ -324,8 +346,10 @@ __global__ void __launch_bounds__(256) sweep_walk_kernel(const float* __restrict
 #pragma unroll
   for (int j = 0; j < kAhead; ++j) walk_load<NQ>(p, s - 3 + j, w.u[j]);
   if (KICK) {
-    walk_load_g<NQ>(p, s - 3, w.g[0]);
-    walk_load_g<NQ>(p, s - 2, w.g[1]);
+    walk_load_side<NQ>(p, s - 3, w.g[0]);
+    walk_load_side<NQ>(p, s - 2, w.g[1]);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) w.c[(j + 7) & 7] = ld_byte(p.phi, p.at(s - 4 + j));
   }
   if (walk_head(s))
     walk_fwd_fill<D, true, KICK, NQ>(w, p, s, h1, h2, dt, hdt);
@@ -359,7 +383,7 @@ __global__ void __launch_bounds__(256) sweep_walk_kernel(const float* __restrict
 template <bool KICK, int NQ>
 __global__ void __launch_bounds__(kRowThreads) sweep_x_vjp_kernel(
     const float* __restrict__ qin, const float* __restrict__ lam_out, float* __restrict__ lam_in,
-    int n, long long nc, const StepScal* __restrict__ tab, const float4* __restrict__ g4) {
+    int n, long long nc, const StepScal* __restrict__ tab, const float* __restrict__ phi) {
   __shared__ float S[5][NQ][kRowCells];
   const long long base = static_cast<long long>(blockIdx.x) * kRowCells;
   const int j = threadIdx.x;
@@ -387,7 +411,8 @@ __global__ void __launch_bounds__(kRowThreads) sweep_x_vjp_kernel(
     }
     if (KICK) {
       float m[3] = {u[1], u[2], u[3]};
-      kick_cell(u[0], g4[blockIdx.y * nc + base + j], sc.h, m, u[4]);
+      kick_cell(u[0], mesh_g(phi + blockIdx.y * nc, static_cast<unsigned>(base + j), log2_side(nc)),
+              sc.h, m, u[4]);
       u[1] = m[0];
       u[2] = m[1];
       u[3] = m[2];
@@ -491,7 +516,7 @@ struct WalkVjp {
   float gr[4][NQ], gl[4][NQ];  // adjoints of F^R, F^L of cell k - 1 - j in slot (i - j) & 3
   float lh[2][NQ];            // lambda_h of cell k - 3 - j in slot (i - j) & 1
   float g1[2][NQ];            // G1 of face (k - 4 - j) + 1/2 in slot (i - j) & 1
-  float g[2][3];              // first sweep: g of cell k + 1 - j in slot (i + 1 - j) & 1
+  float g[2][6];              // first sweep: potentials around cell k + 1 - j, (i + 1 - j) & 1
 };
 
 // Returns x unchanged through an empty asm statement, so that the compiler cannot reuse
@@ -509,8 +534,9 @@ struct WalkVjpPtr {
   unsigned base, stride;   // in bytes
   int n;
   // adjoint of the first sweep of a step: q is the state before the opening gas kick, which
-  // every load applies again (g of the sample's cells, the half kick)
-  const char* g4;
+  // every load applies again (potential of the sample's cells, the cells beside, the half kick)
+  const char* phi;
+  int side[4];
   float h;
   __device__ __forceinline__ unsigned at(int k) const {
     return base + static_cast<unsigned>(k & (n - 1)) * stride;
@@ -521,12 +547,13 @@ struct WalkVjpPtr {
   __device__ __forceinline__ void st(int c, unsigned off, float v) const {
     *reinterpret_cast<float*>(reinterpret_cast<char*>(o[c]) + off) = v;
   }
-  // g of the cell at byte offset off (its float4 is at byte 16 off / 4)
-  __device__ __forceinline__ void load_g(unsigned off, float (&g)[3]) const {
-    const float4 v = *reinterpret_cast<const float4*>(g4 + 4ull * off);
-    g[0] = v.x;
-    g[1] = v.y;
-    g[2] = v.z;
+  // potentials beside, before and after cell k
+  __device__ __forceinline__ void load_phi(int k, float (&g)[6]) const {
+    const unsigned off = at(k);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) g[i] = ld_byte(phi, off + side[i]);
+    g[4] = ld_byte(phi, at(k - 1));
+    g[5] = ld_byte(phi, at(k + 1));
   }
 };
 
@@ -561,9 +588,9 @@ __device__ __forceinline__ void walk_vjp_visit(WalkVjp<NQ>& w, const WalkVjpPtr<
       w.u[ua][c] = WalkVjpPtr<NQ>::ld(p.q[c], offu);
       w.lm[la][c] = WalkVjpPtr<NQ>::ld(p.l[c], offl);
     }
-    if (KICK) p.load_g(p.at(k + 1), w.g[(I + 1) & 1]);
+    if (KICK) p.load_phi(k + 1, w.g[(I + 1) & 1]);
   }
-  if (KICK) kick_loaded(w.u[u0], w.g[I & 1], p.h);
+  if (KICK) kick_loaded<D>(w.u[u0], w.g[I & 1], w.g[I & 1][4], w.g[I & 1][5], p.h);
   float l1[NQ];
   split_flux<D, NQ, q1r, q1l>(w.u[u0], h1, w.r1[p0], l1);
   if (STAGE < 1) return;
@@ -648,7 +675,7 @@ __global__ void __launch_bounds__(256) sweep_walk_vjp_kernel(const float* __rest
                                                              float* __restrict__ lam_in, int n,
                                                              long long nc, int seg_len, int nseg,
                                                              const StepScal* __restrict__ tab,
-                                                             const float4* __restrict__ g4) {
+                                                             const float* __restrict__ phi) {
   int x, other, seg;
   walk_thread(n, x, other, seg);
   if (seg >= nseg) return;
@@ -665,7 +692,8 @@ __global__ void __launch_bounds__(256) sweep_walk_vjp_kernel(const float* __rest
     p.l[c] = lam_out + (blockIdx.y * NQ + c) * nc;
     p.o[c] = lam_in + (blockIdx.y * NQ + c) * nc;
   }
-  p.g4 = KICK ? reinterpret_cast<const char*>(g4 + blockIdx.y * nc) : nullptr;
+  p.phi = KICK ? reinterpret_cast<const char*>(phi + blockIdx.y * nc) : nullptr;
+  walk_sides<D>(n, x, other, p.side);
   p.h = sc.h;
   if (!sc.active) {
     for (int i = 0; i < seg_len; ++i) {
@@ -685,7 +713,7 @@ __global__ void __launch_bounds__(256) sweep_walk_vjp_kernel(const float* __rest
 #pragma unroll
     for (int c = 0; c < NQ; ++c) w.u[j][c] = WalkVjpPtr<NQ>::ld(p.q[c], off);
   }
-  if (KICK) p.load_g(p.at(s - 4), w.g[0]);
+  if (KICK) p.load_phi(s - 4, w.g[0]);
 #pragma unroll
   for (int j = 0; j < kAheadL; ++j) {
     const unsigned off = p.at(s - 4 + j);
@@ -729,14 +757,14 @@ namespace {
 
 template <int NQ>
 void sweep_nq(hipStream_t st, const float* qin, float* qout, const Batch& b, int axis,
-              const float4* g4) {
+              const float* phi) {
   const int n = b.n;
   const long long nc = b.nc();
   if (axis == 0) {
     const dim3 grid(static_cast<unsigned>(nc / kRowCells), b.S);
-    if (g4)
+    if (phi)
       hipLaunchKernelGGL((sweep_x_kernel<true, NQ>), grid, dim3(kRowThreads), 0, st, qin, qout, n,
-                         nc, b.tab, g4);
+                         nc, b.tab, phi);
     else
       hipLaunchKernelGGL((sweep_x_kernel<false, NQ>), grid, dim3(kRowThreads), 0, st, qin, qout,
                          n, nc, b.tab, nullptr);
@@ -747,12 +775,12 @@ void sweep_nq(hipStream_t st, const float* qin, float* qout, const Batch& b, int
     const dim3 grid(blocks_for(threads, 256), b.S);
 #define DH_WALK(D, KICK)                                                                     \
   hipLaunchKernelGGL((sweep_walk_kernel<D, KICK, NQ>), grid, dim3(256), 0, st, qin, qout, n, nc, \
-                     seg, nseg, b.tab, g4)
+                     seg, nseg, b.tab, phi)
     if (axis == 1) {
-      if (g4) DH_WALK(1, true);
+      if (phi) DH_WALK(1, true);
       else DH_WALK(1, false);
     } else {
-      if (g4) DH_WALK(2, true);
+      if (phi) DH_WALK(2, true);
       else DH_WALK(2, false);
     }
 #undef DH_WALK
@@ -761,14 +789,14 @@ void sweep_nq(hipStream_t st, const float* qin, float* qout, const Batch& b, int
 
 template <int NQ>
 void sweep_vjp_nq(hipStream_t st, const float* qin, const float* lam_out, float* lam_in,
-                  const Batch& b, int axis, const float4* g4) {
+                  const Batch& b, int axis, const float* phi) {
   const int n = b.n;
   const long long nc = b.nc();
   if (axis == 0) {
     const dim3 grid(static_cast<unsigned>(nc / kRowCells), b.S);
-    if (g4)
+    if (phi)
       hipLaunchKernelGGL((sweep_x_vjp_kernel<true, NQ>), grid, dim3(kRowThreads), 0, st, qin,
-                         lam_out, lam_in, n, nc, b.tab, g4);
+                         lam_out, lam_in, n, nc, b.tab, phi);
     else
       hipLaunchKernelGGL((sweep_x_vjp_kernel<false, NQ>), grid, dim3(kRowThreads), 0, st, qin,
                          lam_out, lam_in, n, nc, b.tab, nullptr);
@@ -779,12 +807,12 @@ void sweep_vjp_nq(hipStream_t st, const float* qin, const float* lam_out, float*
     const dim3 grid(blocks_for(threads, 256), b.S);
 #define DH_WALK_VJP(D, KICK)                                                                  \
   hipLaunchKernelGGL((sweep_walk_vjp_kernel<D, KICK, NQ>), grid, dim3(256), 0, st, qin, lam_out, \
-                     lam_in, n, nc, seg, nseg, b.tab, g4)
+                     lam_in, n, nc, seg, nseg, b.tab, phi)
     if (axis == 1) {
-      if (g4) DH_WALK_VJP(1, true);
+      if (phi) DH_WALK_VJP(1, true);
       else DH_WALK_VJP(1, false);
     } else {
-      if (g4) DH_WALK_VJP(2, true);
+      if (phi) DH_WALK_VJP(2, true);
       else DH_WALK_VJP(2, false);
     }
 #undef DH_WALK_VJP
@@ -794,24 +822,24 @@ void sweep_vjp_nq(hipStream_t st, const float* qin, const float* lam_out, float*
 }  // namespace
 
 void launch_sweep(hipStream_t st, const float* qin, float* qout, const Batch& b, int axis,
-                  const float4* g4) {
+                  const float* phi) {
   if (!b.tab) throw ArgError("sweep: step table required");
   if (axis == 0 && qin == qout) throw ArgError("sweep_x: in-place not supported");
   if (b.nq == 6)
-    sweep_nq<6>(st, qin, qout, b, axis, g4);
+    sweep_nq<6>(st, qin, qout, b, axis, phi);
   else
-    sweep_nq<5>(st, qin, qout, b, axis, g4);
+    sweep_nq<5>(st, qin, qout, b, axis, phi);
   DH_LAUNCH_CHECK();
 }
 
 void launch_sweep_vjp(hipStream_t st, const float* qin, const float* lam_out, float* lam_in,
-                      const Batch& b, int axis, const float4* g4) {
+                      const Batch& b, int axis, const float* phi) {
   if (!b.tab) throw ArgError("sweep adjoint: step table required");
   if (qin == lam_in || lam_out == lam_in) throw ArgError("sweep adjoint: in-place not supported");
   if (b.nq == 6)
-    sweep_vjp_nq<6>(st, qin, lam_out, lam_in, b, axis, g4);
+    sweep_vjp_nq<6>(st, qin, lam_out, lam_in, b, axis, phi);
   else
-    sweep_vjp_nq<5>(st, qin, lam_out, lam_in, b, axis, g4);
+    sweep_vjp_nq<5>(st, qin, lam_out, lam_in, b, axis, phi);
   DH_LAUNCH_CHECK();
 }
 

@@ -611,21 +611,20 @@ struct GridIdx {
   }
 };
 
-// g4[c] = (g_x, g_y, g_z, 0),  g_d = -(phi[c + e_d] - phi[c - e_d]) / 2
+// g[c] = -grad(phi) at c, for the read-outs on the particles (the cells' kernels form it from
+// phi).  12 bytes a cell: with 16 this pass took 74 us at 256^3 against 65, kick and drift 275
+// against 268.  A particle's own read-out from phi takes 32 loads, as rows or one by one, and
+// 360 to 420 us.
 __global__ void __launch_bounds__(256) grad_kernel(const float* __restrict__ phi,
-                                                   float4* __restrict__ g4, int n, int lgn,
+                                                   float3* __restrict__ g, int lgn,
                                                    const StepScal* __restrict__ tab) {
   const unsigned c = blockIdx.x * blockDim.x + threadIdx.x;
   const unsigned nc = 1u << (3 * lgn);
   if (c >= nc || !sample_active(tab, blockIdx.y)) return;
   phi += static_cast<long long>(blockIdx.y) * nc;
-  g4 += static_cast<long long>(blockIdx.y) * nc;
-  const GridIdx gi{static_cast<unsigned>(n - 1), static_cast<unsigned>(lgn)};
-  const unsigned ix = c & gi.n1, iy = (c >> lgn) & gi.n1, iz = c >> (2 * lgn);
-  const float gx = -0.5f * (phi[gi.at(ix + 1, iy, iz)] - phi[gi.at(ix - 1, iy, iz)]);
-  const float gy = -0.5f * (phi[gi.at(ix, iy + 1, iz)] - phi[gi.at(ix, iy - 1, iz)]);
-  const float gz = -0.5f * (phi[gi.at(ix, iy, iz + 1)] - phi[gi.at(ix, iy, iz - 1)]);
-  g4[c] = make_float4(gx, gy, gz, 0.0f);
+  g += static_cast<long long>(blockIdx.y) * nc;
+  const float4 v = mesh_g(phi, c, lgn);
+  g[c] = make_float3(v.x, v.y, v.z);
 }
 
 __device__ __forceinline__ long long corner(const Cic& w, int ox, int oy, int oz, int n) {
@@ -634,7 +633,7 @@ __device__ __forceinline__ long long corner(const Cic& w, int ox, int oy, int oz
 }
 
 // CIC read-out of g at a particle
-__device__ __forceinline__ void readout_g(const float4* __restrict__ g4, const Cic& w, int n,
+__device__ __forceinline__ void readout_g(const float3* __restrict__ g3, const Cic& w, int n,
                                           float out[3]) {
   out[0] = out[1] = out[2] = 0.0f;
 #pragma unroll
@@ -643,7 +642,7 @@ __device__ __forceinline__ void readout_g(const float4* __restrict__ g4, const C
     for (int oy = 0; oy < 2; ++oy)
 #pragma unroll
       for (int ox = 0; ox < 2; ++ox) {
-        const float4 g = g4[corner(w, ox, oy, oz, n)];
+        const float3 g = g3[corner(w, ox, oy, oz, n)];
         const float ww = wsel(w.w1[0], ox) * wsel(w.w1[1], oy) * wsel(w.w1[2], oz);
         out[0] = fmaf(ww, g.x, out[0]);
         out[1] = fmaf(ww, g.y, out[1]);
@@ -651,18 +650,18 @@ __device__ __forceinline__ void readout_g(const float4* __restrict__ g4, const C
       }
 }
 
-__global__ void __launch_bounds__(256) readout_g_kernel(const float4* __restrict__ g4,
+__global__ void __launch_bounds__(256) readout_g_kernel(const float3* __restrict__ g3,
                                                         const float* __restrict__ pos,
                                                         float* __restrict__ out, int n,
                                                         long long np) {
   const long long i = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= np) return;
-  g4 += blockIdx.y * np;
+  g3 += blockIdx.y * np;
   pos += blockIdx.y * 3 * np;
   out += blockIdx.y * 3 * np;
   const Cic w = cic_of(pos[i], pos[np + i], pos[2 * np + i], n);
   float g[3];
-  readout_g(g4, w, n, g);
+  readout_g(g3, w, n, g);
   out[i] = g[0];
   out[np + i] = g[1];
   out[2 * np + i] = g[2];
@@ -705,7 +704,7 @@ __device__ __forceinline__ float wrap_pos(float x, float fn) {
 // positions) is applied first: the two kicks are the separate roundings of kick_kernel
 // followed by this kernel, fused into one pass over the particles.
 // pos_in and pos may be the same array (in place): no __restrict__ on them
-__global__ void __launch_bounds__(256) kick_drift_kernel(const float4* __restrict__ g4,
+__global__ void __launch_bounds__(256) kick_drift_kernel(const float3* __restrict__ g3,
                                                          const float* pos_in, float* pos,
                                                          float* __restrict__ mom,
                                                          uint32_t* __restrict__ key,
@@ -719,7 +718,7 @@ __global__ void __launch_bounds__(256) kick_drift_kernel(const float4* __restric
   const StepScal& sc = tab[blockIdx.y];
   if (i >= np) return;
   const int smp = blockIdx.y;
-  g4 += smp * np;
+  g3 += smp * np;
   pos_in += smp * 3 * np;
   pos += smp * 3 * np;
   mom += smp * 3 * np;
@@ -745,7 +744,7 @@ __global__ void __launch_bounds__(256) kick_drift_kernel(const float4* __restric
   float x[3] = {pos_in[i], pos_in[np + i], pos_in[2 * np + i]};
   const Cic w = cic_of(x[0], x[1], x[2], n);
   float g[3];
-  readout_g(g4, w, n, g);
+  readout_g(g3, w, n, g);
   const float fn = static_cast<float>(n);
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
@@ -765,7 +764,7 @@ __global__ void __launch_bounds__(256) kick_drift_kernel(const float4* __restric
   if (count) rank[i] = atomicAdd(&count[k], 1u);
 }
 
-__global__ void __launch_bounds__(256) kick_kernel(const float4* __restrict__ g4,
+__global__ void __launch_bounds__(256) kick_kernel(const float3* __restrict__ g3,
                                                    const float* __restrict__ pos,
                                                    float* __restrict__ mom, int n, long long np,
                                                    const StepScal* __restrict__ tab) {
@@ -773,18 +772,18 @@ __global__ void __launch_bounds__(256) kick_kernel(const float4* __restrict__ g4
   const StepScal& sc = tab[blockIdx.y];
   if (i >= np || !sc.active) return;
   const float h = sc.h_close;
-  g4 += blockIdx.y * np;
+  g3 += blockIdx.y * np;
   pos += blockIdx.y * 3 * np;
   mom += blockIdx.y * 3 * np;
   const Cic w = cic_of(pos[i], pos[np + i], pos[2 * np + i], n);
   float g[3];
-  readout_g(g4, w, n, g);
+  readout_g(g3, w, n, g);
 #pragma unroll
   for (int d = 0; d < 3; ++d) mom[d * np + i] = fmaf(h, g[d], mom[d * np + i]);
 }
 
 // acc = sum_corners (dw/dx) (g_corner . lp): the kick's adjoint with respect to the position
-__device__ __forceinline__ void kick_pos_acc(const float4* __restrict__ g4, const Cic& w,
+__device__ __forceinline__ void kick_pos_acc(const float3* __restrict__ g3, const Cic& w,
                                              const float lp[3], int n, float acc[3]) {
   acc[0] = acc[1] = acc[2] = 0.0f;
 #pragma unroll
@@ -793,7 +792,7 @@ __device__ __forceinline__ void kick_pos_acc(const float4* __restrict__ g4, cons
     for (int oy = 0; oy < 2; ++oy)
 #pragma unroll
       for (int ox = 0; ox < 2; ++ox) {
-        const float4 g = g4[corner(w, ox, oy, oz, n)];
+        const float3 g = g3[corner(w, ox, oy, oz, n)];
         const float gl = g.x * lp[0] + g.y * lp[1] + g.z * lp[2];
         const float wx = wsel(w.w1[0], ox), wy = wsel(w.w1[1], oy), wz = wsel(w.w1[2], oz);
         acc[0] += (ox ? 1.0f : -1.0f) * wy * wz * gl;
@@ -803,7 +802,7 @@ __device__ __forceinline__ void kick_pos_acc(const float4* __restrict__ g4, cons
 }
 
 // lam_x += h * sum_corners (dw/dx) (g_corner . lam_p)
-__global__ void __launch_bounds__(256) kick_vjp_pos_kernel(const float4* __restrict__ g4,
+__global__ void __launch_bounds__(256) kick_vjp_pos_kernel(const float3* __restrict__ g3,
                                                            const float* __restrict__ pos,
                                                            const float* __restrict__ lam_p,
                                                            bool merged, float* __restrict__ lam_x,
@@ -813,27 +812,27 @@ __global__ void __launch_bounds__(256) kick_vjp_pos_kernel(const float4* __restr
   const StepScal& sc = tab[blockIdx.y];
   if (i >= np || !sc.active) return;
   const float h = merged ? sc.h_dm : sc.h_open;
-  g4 += blockIdx.y * np;
+  g3 += blockIdx.y * np;
   pos += blockIdx.y * 3 * np;
   lam_p += blockIdx.y * 3 * np;
   lam_x += blockIdx.y * 3 * np;
   const Cic w = cic_of(pos[i], pos[np + i], pos[2 * np + i], n);
   const float lp[3] = {lam_p[i], lam_p[np + i], lam_p[2 * np + i]};
   float acc[3];
-  kick_pos_acc(g4, w, lp, n, acc);
+  kick_pos_acc(g3, w, lp, n, acc);
 #pragma unroll
   for (int d = 0; d < 3; ++d) lam_x[d * np + i] = fmaf(h, acc[d], lam_x[d * np + i]);
 }
 
 // lam_x += mass * sum_corners lam_delta[corner] dw/dx
-// With lam_p: first, with g4, the merged dark-matter kicks' adjoint with respect to the
+// With lam_p: first, with g3, the merged dark-matter kicks' adjoint with respect to the
 // position (kick_vjp_pos_kernel, factor h_dm); last, lam_p += drift lam_x (the drift's
 // adjoint, x1 = x0 + drift p).  One pass, the roundings of the separate kernels.
 __global__ void __launch_bounds__(256) deposit_vjp_pos_kernel(const float* __restrict__ lam_delta,
                                                               const float* __restrict__ pos,
                                                               float mass, float* __restrict__ lam_x,
                                                               float* __restrict__ lam_p,
-                                                              const float4* __restrict__ g4,
+                                                              const float3* __restrict__ g3,
                                                               int n, long long np,
                                                               const StepScal* __restrict__ tab) {
   const long long i = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -842,7 +841,7 @@ __global__ void __launch_bounds__(256) deposit_vjp_pos_kernel(const float* __res
   pos += blockIdx.y * 3 * np;
   lam_x += blockIdx.y * 3 * np;
   if (lam_p) lam_p += blockIdx.y * 3 * np;
-  if (g4) g4 += blockIdx.y * np;
+  if (g3) g3 += blockIdx.y * np;
   const Cic w = cic_of(pos[i], pos[np + i], pos[2 * np + i], n);
   float lx0[3] = {lam_x[i], lam_x[np + i], lam_x[2 * np + i]};
   float lp[3] = {0.0f, 0.0f, 0.0f};
@@ -850,9 +849,9 @@ __global__ void __launch_bounds__(256) deposit_vjp_pos_kernel(const float* __res
 #pragma unroll
     for (int d = 0; d < 3; ++d) lp[d] = lam_p[d * np + i];
   }
-  if (g4) {
+  if (g3) {
     float ka[3];
-    kick_pos_acc(g4, w, lp, n, ka);
+    kick_pos_acc(g3, w, lp, n, ka);
     const float h = tab[blockIdx.y].h_dm;
 #pragma unroll
     for (int d = 0; d < 3; ++d) lx0[d] = fmaf(h, ka[d], lx0[d]);
@@ -1022,15 +1021,15 @@ void launch_deposit_vec(hipStream_t st, const Bins& bins, const float* v, bool m
   launch_columns<true>(st, bins, v, 3 * b.nc(), 0.0f, 0.0f, merged, out_accum, b);
 }
 
-void launch_grad(hipStream_t st, const float* phi, float4* g4, const Batch& b) {
-  hipLaunchKernelGGL(grad_kernel, per_sample(b.nc(), b), dim3(256), 0, st, phi, g4, b.n,
+void launch_grad(hipStream_t st, const float* phi, float3* g3, const Batch& b) {
+  hipLaunchKernelGGL(grad_kernel, per_sample(b.nc(), b), dim3(256), 0, st, phi, g3,
                      log2_ll(b.n), b.tab);
   DH_LAUNCH_CHECK();
 }
 
-void launch_readout_g(hipStream_t st, const float4* g4, const float* pos, float* out,
+void launch_readout_g(hipStream_t st, const float3* g3, const float* pos, float* out,
                       const Batch& b) {
-  hipLaunchKernelGGL(readout_g_kernel, per_sample(b.nc(), b), dim3(256), 0, st, g4, pos, out, b.n,
+  hipLaunchKernelGGL(readout_g_kernel, per_sample(b.nc(), b), dim3(256), 0, st, g3, pos, out, b.n,
                      b.nc());
   DH_LAUNCH_CHECK();
 }
@@ -1042,39 +1041,39 @@ void launch_star_readout(hipStream_t st, const float* znew, const float* pos, fl
   DH_LAUNCH_CHECK();
 }
 
-void launch_kick_drift(hipStream_t st, const float4* g4, const float* pos_in, float* pos,
+void launch_kick_drift(hipStream_t st, const float3* g3, const float* pos_in, float* pos,
                        float* mom, uint32_t* key, float* mom_copy, float* pos_copy, bool prev,
                        const Batch& b, const Bins* count_into) {
   if (!b.tab) throw ArgError("kick_drift: step table required");
   if (count_into && key != count_into->key) throw ArgError("kick_drift: keys of another sort");
   uint32_t* count = count_into ? count_into->count : nullptr;
   uint32_t* rank = count_into ? count_into->rank : nullptr;
-  hipLaunchKernelGGL(kick_drift_kernel, per_sample(b.nc(), b), dim3(256), 0, st, g4, pos_in, pos,
+  hipLaunchKernelGGL(kick_drift_kernel, per_sample(b.nc(), b), dim3(256), 0, st, g3, pos_in, pos,
                      mom, key, mom_copy, pos_copy, b.n, b.nc(), prev ? 1 : 0, b.tab, count, rank);
   DH_LAUNCH_CHECK();
 }
 
-void launch_kick(hipStream_t st, const float4* g4, const float* pos, float* mom, const Batch& b) {
+void launch_kick(hipStream_t st, const float3* g3, const float* pos, float* mom, const Batch& b) {
   if (!b.tab) throw ArgError("kick: step table required");
-  hipLaunchKernelGGL(kick_kernel, per_sample(b.nc(), b), dim3(256), 0, st, g4, pos, mom, b.n,
+  hipLaunchKernelGGL(kick_kernel, per_sample(b.nc(), b), dim3(256), 0, st, g3, pos, mom, b.n,
                      b.nc(), b.tab);
   DH_LAUNCH_CHECK();
 }
 
-void launch_kick_vjp_pos(hipStream_t st, const float4* g4, const float* pos, const float* lam_p,
+void launch_kick_vjp_pos(hipStream_t st, const float3* g3, const float* pos, const float* lam_p,
                          bool merged, float* lam_x, const Batch& b) {
   if (!b.tab) throw ArgError("kick adjoint: step table required");
-  hipLaunchKernelGGL(kick_vjp_pos_kernel, per_sample(b.nc(), b), dim3(256), 0, st, g4, pos, lam_p,
+  hipLaunchKernelGGL(kick_vjp_pos_kernel, per_sample(b.nc(), b), dim3(256), 0, st, g3, pos, lam_p,
                      merged, lam_x, b.n, b.nc(), b.tab);
   DH_LAUNCH_CHECK();
 }
 
 void launch_deposit_vjp_pos(hipStream_t st, const float* lam_delta, const float* pos, float mass,
-                            float* lam_x, float* lam_p, const float4* g4, const Batch& b) {
+                            float* lam_x, float* lam_p, const float3* g3, const Batch& b) {
   if (lam_p && !b.tab) throw ArgError("deposit adjoint: step table required for the drift");
-  if (g4 && !lam_p) throw ArgError("deposit adjoint: the kick term needs lam_p");
+  if (g3 && !lam_p) throw ArgError("deposit adjoint: the kick term needs lam_p");
   hipLaunchKernelGGL(deposit_vjp_pos_kernel, per_sample(b.nc(), b), dim3(256), 0, st, lam_delta,
-                     pos, mass, lam_x, lam_p, g4, b.n, b.nc(), b.tab);
+                     pos, mass, lam_x, lam_p, g3, b.n, b.nc(), b.tab);
   DH_LAUNCH_CHECK();
 }
 

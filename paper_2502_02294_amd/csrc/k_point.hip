@@ -97,7 +97,7 @@ __device__ __forceinline__ void kick_cell_vjp(float rho, const float m[3], const
 }
 
 __global__ void __launch_bounds__(256) gas_kick_vjp_kernel(const float* __restrict__ q,
-                                                           const float4* __restrict__ g4,
+                                                           const float* __restrict__ phi,
                                                            float* __restrict__ lam,
                                                            float* __restrict__ lam_g,
                                                            long long nc, int nq,
@@ -109,13 +109,13 @@ __global__ void __launch_bounds__(256) gas_kick_vjp_kernel(const float* __restri
   q += blockIdx.y * nq * nc;
   lam += blockIdx.y * nq * nc;
   lam_g += blockIdx.y * 3 * nc;
-  g4 += blockIdx.y * nc;
+  phi += blockIdx.y * nc;
   const float m[3] = {q[nc + c], q[2 * nc + c], q[3 * nc + c]};
   float l5[5];
 #pragma unroll
   for (int k = 0; k < 5; ++k) l5[k] = lam[k * nc + c];
   float lg[3];
-  kick_cell_vjp(q[c], m, g4[c], sc.h, l5, lg);
+  kick_cell_vjp(q[c], m, mesh_g(phi, static_cast<unsigned>(c), log2_side(nc)), sc.h, l5, lg);
 #pragma unroll
   for (int k = 0; k < 4; ++k) lam[k * nc + c] = l5[k];
 #pragma unroll
@@ -326,12 +326,12 @@ __device__ __forceinline__ void dual_close(float* q, double e_sn, float r1g) {
 // Early on the pass is bounded by the arithmetic of the estimate and the CFL speed, so what is
 // the same in every cell is converted once (CellScal) and the estimate takes bare hardware
 // logarithms; five waves per SIMD (96 registers, nothing spilled) hide the loads: 256^3
-// 241 -> 209 us (13 fields: 4.2 TB/s), 128^3 45 -> 39, 13 x 64^3 74 -> 64; six waves or eight
+// 241 -> 207 us (10 fields), 128^3 45 -> 38, 13 x 64^3 74 -> 64; six waves or eight
 // with the source term's FP64 values in scratch: 215, 231.  NQ = 6 keeps its 141 registers (at
 // 96 it spills: 64^3 13.9 -> 16.6 us).
 template <bool FULL, int NQ>
 __global__ void __launch_bounds__(kRedThreads, NQ == 5 ? 5 : 1) close_step_kernel(
-    const float* q_in, float* q, const float4* __restrict__ g4, float* __restrict__ star,
+    const float* q_in, float* q, const float* __restrict__ phi, float* __restrict__ star,
     float* __restrict__ q_kicked, double gg1, double* partial, long long nc,
     const StepScal* __restrict__ tab, float* __restrict__ znew, float* __restrict__ sn_out, int per) {
   const StepScal& sc = tab[blockIdx.y];
@@ -345,7 +345,8 @@ __global__ void __launch_bounds__(kRedThreads, NQ == 5 ? 5 : 1) close_step_kerne
   q_in += blockIdx.y * NQ * nc;
   q += blockIdx.y * NQ * nc;
   if (q_kicked) q_kicked += blockIdx.y * NQ * nc;
-  g4 += blockIdx.y * nc;
+  phi += blockIdx.y * nc;
+  const int lgn = log2_side(nc);
   if (FULL) star += blockIdx.y * nc;
   if (znew) znew += blockIdx.y * nc;
   if (sn_out) sn_out += blockIdx.y * nc;
@@ -359,7 +360,7 @@ __global__ void __launch_bounds__(kRedThreads, NQ == 5 ? 5 : 1) close_step_kerne
     float q5[NQ];
     load_q<NQ>(q_in, c, nc, q5);
     float m[3] = {q5[1], q5[2], q5[3]};
-    kick_cell(q5[0], g4[c], h, m, q5[4]);
+    kick_cell(q5[0], mesh_g(phi, static_cast<unsigned>(c), lgn), h, m, q5[4]);
     q5[1] = m[0];
     q5[2] = m[1];
     q5[3] = m[2];
@@ -473,12 +474,12 @@ __global__ void __launch_bounds__(kRedThreads) sn_inject_kernel(
 
 // Adjoint of the smoothed injection into a dual-energy state and of the end-of-step reset
 // after it (sn_inject_kernel<6>), at the state the injection pass saw: q4 (the state after the
-// sweeps) with the closing gas kick (g4, the table's h) applied as the closing pass applied it
+// sweeps) with the closing gas kick (g of phi, the table's h) applied as the closing pass applied it
 // (where the injection is smoothed the source term leaves the cell's state unchanged), plus
 // add = smooth27(sn).  lam: in, the adjoint after the reset; out, that after the closing pass's
 // source term.  lam_add: the adjoint of each cell's smoothed energy.
 __global__ void __launch_bounds__(256) inject_sync_vjp_kernel(
-    const float* __restrict__ q4, const float4* __restrict__ g4, const float* __restrict__ sn,
+    const float* __restrict__ q4, const float* __restrict__ phi, const float* __restrict__ sn,
     float* __restrict__ lam, float* __restrict__ lam_add, int n, int lgn,
     const StepScal* __restrict__ tab) {
   const unsigned c = blockIdx.x * blockDim.x + threadIdx.x;
@@ -488,14 +489,14 @@ __global__ void __launch_bounds__(256) inject_sync_vjp_kernel(
   const SourceArgs& a = sc.src;
   const long long off = static_cast<long long>(blockIdx.y) * nc;
   q4 += 6 * off;
-  g4 += off;
+  phi += off;
   sn += off;
   lam += 6 * off;
   lam_add += off;
   float q[6];
   load_q<6>(q4, c, nc, q);
   float m[3] = {q[1], q[2], q[3]};
-  kick_cell(q[0], g4[c], sc.h, m, q[4]);
+  kick_cell(q[0], mesh_g(phi, c, lgn), sc.h, m, q[4]);
   q[1] = m[0];
   q[2] = m[1];
   q[3] = m[2];
@@ -655,11 +656,11 @@ __device__ __forceinline__ void dual_close_vjp(const float* q, long long c, cons
 // every sample moves in both steps.
 // lam_inj (optional): the adjoint of the injected energy of each cell when the injection is
 // smoothed (the smoothing of the energy adjoint).
-// Bounded by its 29 fields (256^3: 400 us, 4.9 TB/s) at four waves per SIMD (128 registers; with
+// Bounded by its 26 fields (256^3: 363 us, 4.8 TB/s) at four waves per SIMD (128 registers; with
 // 139, three waves: 13 x 64^3 102 us against 88).
 template <bool OPEN, int NQ>
 __global__ void __launch_bounds__(kRedThreads, NQ == 5 ? 4 : 1) source_kick_vjp_kernel(
-    const float* __restrict__ q_kick, const float4* __restrict__ g4, float* __restrict__ lam,
+    const float* __restrict__ q_kick, const float* __restrict__ phi, float* __restrict__ lam,
     float* __restrict__ lam_g, double* partial, long long nc, const StepScal* __restrict__ tab,
     const float* __restrict__ q_open, float* __restrict__ lam_g_open,
     const StepScal* __restrict__ tab_open, const float* __restrict__ lam_inj, int per) {
@@ -671,7 +672,8 @@ __global__ void __launch_bounds__(kRedThreads, NQ == 5 ? 4 : 1) source_kick_vjp_
   const SourceArgs& a = sc.src;
   const float h = sc.h;
   q_kick += blockIdx.y * NQ * nc;
-  g4 += blockIdx.y * nc;
+  phi += blockIdx.y * nc;
+  const int lgn = log2_side(nc);
   lam += blockIdx.y * NQ * nc;
   lam_g += blockIdx.y * 3 * nc;
   if (lam_inj) lam_inj += blockIdx.y * nc;
@@ -690,7 +692,7 @@ __global__ void __launch_bounds__(kRedThreads, NQ == 5 ? 4 : 1) source_kick_vjp_
     float q5[NQ], l5[NQ];
     load_q<NQ>(q_kick, c, nc, q5);
     load_q<NQ>(lam, c, nc, l5);
-    const float4 gv = g4[c];
+    const float4 gv = mesh_g(phi, static_cast<unsigned>(c), lgn);
     if (OPEN) {
       const float mo[3] = {q_open[nc + c], q_open[2 * nc + c], q_open[3 * nc + c]};
       float lgo[3];
@@ -838,7 +840,7 @@ __device__ __forceinline__ float closure_logit_estimate(float o0, float o1, cons
 // pass).
 template <int NQ>
 __global__ void __launch_bounds__(kRedThreads) close_step_mlp_kernel(
-    const float* q_in, float* q, const float4* __restrict__ g4, float* __restrict__ star,
+    const float* q_in, float* q, const float* __restrict__ phi, float* __restrict__ star,
     float* __restrict__ q_kicked, double gg1, double* partial, long long nc,
     const StepScal* __restrict__ tab, float* __restrict__ znew, float* __restrict__ sn_out, int per) {
   const StepScal& sc = tab[blockIdx.y];
@@ -853,7 +855,8 @@ __global__ void __launch_bounds__(kRedThreads) close_step_mlp_kernel(
   if (q_kicked) q_kicked += blockIdx.y * NQ * nc;
   const CellScal cs = cell_scalars(a, gg1);
   const float g1m = static_cast<float>(1.0 - a.gamma);
-  g4 += blockIdx.y * nc;
+  phi += blockIdx.y * nc;
+  const int lgn = log2_side(nc);
   star += blockIdx.y * nc;
   if (znew) znew += blockIdx.y * nc;
   if (sn_out) sn_out += blockIdx.y * nc;
@@ -875,7 +878,7 @@ __global__ void __launch_bounds__(kRedThreads) close_step_mlp_kernel(
     if (valid) {
       load_q<NQ>(q_in, c, nc, q5);
       float m[3] = {q5[1], q5[2], q5[3]};
-      kick_cell(q5[0], g4[c], h, m, q5[4]);
+      kick_cell(q5[0], mesh_g(phi, static_cast<unsigned>(c), lgn), h, m, q5[4]);
       q5[1] = m[0];
       q5[2] = m[1];
       q5[3] = m[2];
@@ -1501,16 +1504,16 @@ int cfl_blocks(int n) {
 }
 int source_vjp_blocks(int n) { return cfl_blocks(n); }
 
-void launch_gas_kick_vjp(hipStream_t st, const float* q_before, const float4* g4, float* lam_q,
+void launch_gas_kick_vjp(hipStream_t st, const float* q_before, const float* phi, float* lam_q,
                          float* lam_g, const Batch& b) {
   if (!b.tab) throw ArgError("gas kick adjoint: step table required");
   hipLaunchKernelGGL(gas_kick_vjp_kernel, dim3(blocks_for(b.nc(), 256), b.S), dim3(256), 0, st,
-                     q_before, g4, lam_q, lam_g, b.nc(), b.nq, b.tab);
+                     q_before, phi, lam_q, lam_g, b.nc(), b.nq, b.tab);
   DH_LAUNCH_CHECK();
 }
 
 // The closure kernels are chosen per launch: every sample of a batch has the same closure.
-void launch_close_step(hipStream_t st, const float* q_in, float* q, const float4* g4,
+void launch_close_step(hipStream_t st, const float* q_in, float* q, const float* phi,
                        float* star, float* q_kicked, double gamma, double* block_max,
                        const Batch& b, bool closure, float* znew, float* sn_out) {
   if (!b.tab) throw ArgError("closing pass: step table required");
@@ -1523,13 +1526,13 @@ void launch_close_step(hipStream_t st, const float* q_in, float* q, const float4
   const dim3 grid(cfl_blocks(b.n), b.S);
   const double gg1 = gamma * (gamma - 1.0);
 #define DH_CLOSE(FULL, NQ)                                                                      \
-  hipLaunchKernelGGL((close_step_kernel<FULL, NQ>), grid, dim3(kRedThreads), 0, st, q_in, q, g4, \
+  hipLaunchKernelGGL((close_step_kernel<FULL, NQ>), grid, dim3(kRedThreads), 0, st, q_in, q, phi, \
                      star, q_kicked, gg1, block_max, b.nc(), b.tab, znew, sn_out, per)
   if (closure && b.nq == 6)
-    hipLaunchKernelGGL(close_step_mlp_kernel<6>, grid, dim3(kRedThreads), 0, st, q_in, q, g4, star,
+    hipLaunchKernelGGL(close_step_mlp_kernel<6>, grid, dim3(kRedThreads), 0, st, q_in, q, phi, star,
                        q_kicked, gg1, block_max, b.nc(), b.tab, znew, sn_out, per);
   else if (closure)
-    hipLaunchKernelGGL(close_step_mlp_kernel<5>, grid, dim3(kRedThreads), 0, st, q_in, q, g4, star,
+    hipLaunchKernelGGL(close_step_mlp_kernel<5>, grid, dim3(kRedThreads), 0, st, q_in, q, phi, star,
                        q_kicked, gg1, block_max, b.nc(), b.tab, znew, sn_out, per);
   else if (b.nq == 6) {
     if (star) DH_CLOSE(true, 6);
@@ -1562,12 +1565,12 @@ void launch_sn_inject(hipStream_t st, const float* sn, float* q, double gamma, d
   DH_LAUNCH_CHECK();
 }
 
-void launch_inject_sync_vjp(hipStream_t st, const float* q4, const float4* g4, const float* sn,
+void launch_inject_sync_vjp(hipStream_t st, const float* q4, const float* phi, const float* sn,
                             float* lam, float* lam_add, const Batch& b) {
   if (!b.tab) throw ArgError("injection adjoint: step table required");
   if (b.nq != 6) throw ArgError("injection adjoint: dual-energy state only");
   hipLaunchKernelGGL(inject_sync_vjp_kernel, dim3(blocks_for(b.nc(), 256), b.S), dim3(256), 0, st,
-                     q4, g4, sn, lam, lam_add, b.n, log2_int(b.n), b.tab);
+                     q4, phi, sn, lam, lam_add, b.n, log2_int(b.n), b.tab);
   DH_LAUNCH_CHECK();
 }
 
@@ -1596,7 +1599,7 @@ void launch_source_vjp(hipStream_t st, const float* q_before, float* lam_q, doub
   DH_LAUNCH_CHECK();
 }
 
-void launch_source_kick_vjp(hipStream_t st, const float* q_kick, const float4* g4,
+void launch_source_kick_vjp(hipStream_t st, const float* q_kick, const float* phi,
                             float* lam_q, float* lam_g, double* partials, const Batch& b,
                             const float* q_open, float* lam_g_open, const StepScal* tab_open,
                             const float* lam_inj) {
@@ -1606,7 +1609,7 @@ void launch_source_kick_vjp(hipStream_t st, const float* q_kick, const float4* g
   const dim3 grid(source_vjp_blocks(b.n), b.S);
 #define DH_SKV(OPEN, NQ)                                                                      \
   hipLaunchKernelGGL((source_kick_vjp_kernel<OPEN, NQ>), grid, dim3(kRedThreads), 0, st, q_kick, \
-                     g4, lam_q, lam_g, partials, b.nc(), b.tab, q_open, lam_g_open, tab_open,    \
+                     phi, lam_q, lam_g, partials, b.nc(), b.tab, q_open, lam_g_open, tab_open,    \
                      lam_inj, cells_per_thread(b.n))
   if (b.nq == 6) {
     if (q_open) DH_SKV(true, 6);
