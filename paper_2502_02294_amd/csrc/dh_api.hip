@@ -788,7 +788,7 @@ void reset_clock(dh_sim* s) {
 
 // The spectral operator op (kOpIcDisp, kOpIcHess, ...) of the initial conditions with the
 // handle's linear spectrum at a_init
-dh::IcOp ic_op(const dh_sim* s, int op, int axis, int axis2 = 0, double scale = 1.0) {
+dh::IcOp ic_op(const dh_sim* s, int op, int axis = 0, int axis2 = 0, double scale = 1.0) {
   const int n = s->n;
   const double ai = s->cfg.a_init;
   const double d = s->cosmo.growth(ai);
@@ -826,13 +826,12 @@ void initial_conditions(dh_sim* s, const float* d_white) {
   const long long nc = s->nc;
   const double ai = s->cfg.a_init;
   const Batch all = batch(s, nullptr);
+  const Batch triples{n, 3 * s->S, nullptr, s->nq};   // the components of [S][3] fields
   dh::fft_forward_xy(s->st, d_white, s->spec2, s->tw, all);
-  dh::fft_zpass_forward(s->st, s->spec2, s->spec2, s->tw, all);
-  for (int j = 0; j < 3; ++j) {
-    dh::fft_zpass_ic(s->st, s->spec2, s->spec, s->tw, ic_op(s, dh::kOpIcDisp, j), false, true,
-                     false, all);
-    dh::fft_inverse_yx(s->st, s->spec, s->psi + j * nc, s->tw, 1.0f, all, 3 * nc);
-  }
+  // (the second-order displacement also takes the full spectrum)
+  dh::fft_zpass_disp(s->st, s->spec2, s->cfg.lpt == 2 ? s->spec2 : nullptr, s->spec, s->tw,
+                     ic_op(s, dh::kOpIcDisp), all);
+  dh::fft_inverse_yx(s->st, s->spec, s->psi, s->tw, 1.0f, triples);
   const float* vel = s->psi;
   if (s->cfg.lpt == 2) {
     // second derivatives of the linear potential, the source delta2 and its displacement
@@ -1365,12 +1364,9 @@ void ic_vjp(dh_sim* s, float* d_grad_white) {
     }
   }
   // psi_j = IFFT(i k_j T(k)/k^2 FFT(w)) -> lambda_w = sum_j IFFT(-i k_j T/k^2 FFT(lambda_psi_j))
-  for (int j = 0; j < 3; ++j) {
-    dh::fft_forward_xy(st, s->lpsi + j * nc, s->spec, s->tw, all, 3 * nc);
-    dh::fft_zpass_ic(st, s->spec, s->spec2, s->tw, ic_op(s, dh::kOpIcDispT, j), true, false,
-                     acc || j > 0, all);
-  }
-  dh::fft_zpass_inverse(st, s->spec2, s->tw, all);
+  dh::fft_forward_xy(st, s->lpsi, s->spec, s->tw, Batch{n, 3 * s->S, nullptr, s->nq});
+  dh::fft_zpass_disp_vjp(st, s->spec, acc ? s->spec2 : nullptr, s->spec2, s->tw,
+                         ic_op(s, dh::kOpIcDisp), all);
   dh::fft_inverse_yx(st, s->spec2, d_grad_white, s->tw, 1.0f, all);
 }
 
@@ -1500,7 +1496,7 @@ int dh_create(const dh_config* cfg, dh_sim** out) {
     s->cic = s->alloc<float>(nc);
     s->psi = s->alloc<float>(3 * nc);
     s->fscratch = s->alloc<float>(3 * np);
-    s->spec = s->alloc<float2>(s->nck * S);
+    s->spec = s->alloc<float2>(3 * s->nck * S);   // [S][3] in the initial conditions
     s->spec2 = s->alloc<float2>(s->nck * S);
     s->tw = s->alloc<float2>(n / 2);
     s->bins.key = s->alloc<uint32_t>(np);

@@ -134,7 +134,7 @@ void launch_grad_vjp2(hipStream_t st, const float* lam_g0, const float* lam_g, f
 
 // ---- FFT and spectral operators (k_fft.hip)
 enum SpecOp {
-  kOpGreen = 0, kOpIcDisp = 1, kOpIcDispT = 2, kOpIcHess = 3, kOpZa = 4, kOpZaT = 5
+  kOpGreen = 0, kOpIcDisp = 1, kOpIcHess = 2, kOpZa = 3, kOpZaT = 4
 };
 // An initial-condition operator of the z pass: op, axes, the spectrum (amplitude
 // A D^2 / V_cell, n_s, Omega_m h, n / box, transfer function) and a scale for kOpZa(T)
@@ -161,6 +161,13 @@ void fft_zpass_inverse(hipStream_t st, float2* spec, const float2* tw, const Bat
 void fft_zpass_ic(hipStream_t st, const float2* in, float2* out, const float2* tw,
                   const IcOp& op, bool forward_first, bool inverse_after, bool accumulate,
                   const Batch& b);
+// z pass of the Zel'dovich displacement of white noise: forward, the operators of the three axes,
+// inverse, into out[S][3]; full (or null): the full spectrum of in (may be in)
+void fft_zpass_disp(hipStream_t st, const float2* in, float2* full, float2* out, const float2* tw,
+                    const IcOp& op, const Batch& b);
+// its adjoint: in[S][3] -> out[S], with the spectrum sum[S] (or null; may be out) added
+void fft_zpass_disp_vjp(hipStream_t st, const float2* in, const float2* sum, float2* out,
+                        const float2* tw, const IcOp& op, const Batch& b);
 
 // ---- observables of Sec. 3 (k_observe.hip)
 // per-block sums of w |X|^2 by bin of the rounded |m| (bins 1..nbins) of a half spectrum

@@ -30,6 +30,12 @@ namespace {
 constexpr int kFftThreads = 256;
 constexpr int kMaxR = 16;
 
+// hides how x was formed from the compiler: it is rounded before any sum it enters
+__device__ __forceinline__ float opaque(float x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
 __device__ __forceinline__ float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
 __device__ __forceinline__ float2 csub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
 __device__ __forceinline__ float2 cmul(float2 a, float2 b) {
@@ -363,7 +369,7 @@ __global__ void __launch_bounds__((Plane<N1, N2>::threads)) plane_inverse_kernel
 
 // ---------------------------------------------------------------------------- line passes
 struct OpArgs {
-  int op;          // -1 none, kOpGreen, kOpIcDisp, kOpIcDispT, kOpIcHess, kOpZa, kOpZaT
+  int op;          // -1 none, kOpGreen, kOpIcHess, kOpZa, kOpZaT
   float green;     // -(3 Om / 2a) / N^3
   int axis, axis2;
   float sqrt_amp;  // sqrt(A D^2 / V_cell)
@@ -405,47 +411,43 @@ __device__ __forceinline__ float sqrt_shape(const OpArgs& o, float kp) {
 
 __device__ __forceinline__ int signed_freq(int k, int n) { return k <= n / 2 ? k : k - n; }
 
-// OPK: 0 none, 1 Green's function, 2 initial-condition displacement (o.op says which sign)
+// sqrt(P(k)) of mode k2 (rad/cell), and what it takes of the white-noise normalisation
+__device__ __forceinline__ float mode_spectrum(const OpArgs& o, float k2) {
+  return o.sqrt_amp * sqrt_shape(o, sqrtf(k2) * o.kphys);
+}
+
+__device__ __forceinline__ float mode_k2(int fx, int fy, int fz, int n) {
+  const float c = 6.283185307179586f / static_cast<float>(n);
+  const float ax = c * fx, ay = c * fy, az = c * fz;
+  return ax * ax + ay * ay + az * az;
+}
+
+// OPK: 0 none, 1 Green's function, 2 the other operators (o.op)
 template <int OPK>
 __device__ __forceinline__ float2 apply_op(const OpArgs& o, int kx, int ky, int kz, int n,
                                            float2 v) {
   const int fx = kx, fy = signed_freq(ky, n), fz = signed_freq(kz, n);
   if (OPK == 0) return v;
+  const float k2 = mode_k2(fx, fy, fz, n);
+  if (k2 == 0.0f) return make_float2(0.0f, 0.0f);
   if (OPK == 1) {
-    const float c = 6.283185307179586f / static_cast<float>(n);
-    const float ax = c * fx, ay = c * fy, az = c * fz;
-    const float k2 = ax * ax + ay * ay + az * az;
-    if (k2 == 0.0f) return make_float2(0.0f, 0.0f);
     const float f = o.green / k2;
     return make_float2(v.x * f, v.y * f);
   }
   // initial-condition operators (derivative factors from deriv_k):
-  //   kOpIcDisp  i k_axis sqrt(P(k)) / k^2 / N^3 (kOpIcDispT: its conjugate), the Zel'dovich
-  //              displacement of white noise;
   //   kOpIcHess  k_axis k_axis2 sqrt(P(k)) / k^2 / N^3 (real): second derivative of the
   //              linear potential (its own transpose);
   //   kOpZa      i k_axis / k^2 times inv_n3 (kOpZaT: its conjugate), the displacement of a
   //              given density, scaled
-  const float c = 6.283185307179586f / static_cast<float>(n);
-  const float ax = c * fx, ay = c * fy, az = c * fz;
-  const float k2 = ax * ax + ay * ay + az * az;
-  if (k2 == 0.0f) return make_float2(0.0f, 0.0f);
   const float kj = deriv_k(o.axis, fx, fy, fz, n);
   if (o.op == kOpZa || o.op == kOpZaT) {
     const float f = kj / k2 * o.inv_n3;
     const float ff = o.op == kOpZa ? f : -f;
     return make_float2(-v.y * ff, v.x * ff);
   }
-  const float kp = sqrtf(k2) * o.kphys;
-  const float spec = o.sqrt_amp * sqrt_shape(o, kp);
-  if (o.op == kOpIcHess) {
-    const float f = kj * deriv_k(o.axis2, fx, fy, fz, n) * spec / k2 * o.inv_n3;
-    return make_float2(v.x * f, v.y * f);
-  }
-  const float f = kj * spec / k2 * o.inv_n3;
-  const float ff = o.op == kOpIcDisp ? f : -f;
-  // multiply by i * ff
-  return make_float2(-v.y * ff, v.x * ff);
+  const float f =
+      kj * deriv_k(o.axis2, fx, fy, fz, n) * mode_spectrum(o, k2) / k2 * o.inv_n3;
+  return make_float2(v.x * f, v.y * f);
 }
 
 // Workgroups go to the 8 XCDs (each with its own L2) round robin.  Consecutive line groups
@@ -525,6 +527,150 @@ __global__ void __launch_bounds__(kFftThreads) pencil_kernel(const float2* in, f
       out[g] = w;
     }
   }
+}
+
+// Zel'dovich displacement of white noise, i k_j sqrt(P(k)) / k^2 / N^3 for the three axes j, on
+// the z pass: in (spectrum along x and y) forward along z, times the operator of each axis,
+// inverse, into out[S][3].  full (optional, may be in): the spectrum of all three axes' input.
+// What bounds a pass per axis is the spectrum's power and logarithm at every mode (95 us at
+// 256^3 against 25 for a plain pass, after a forward pass of its own), so they are taken once:
+// 310 -> 139 us at 256^3, 87 -> 32 at 128^3, 28 -> 12 at 16^3.
+template <int N1, int N2>
+__global__ void __launch_bounds__(kFftThreads) ic_disp_kernel(const float2* in, float2* full,
+                                                              float2* __restrict__ out,
+                                                              const float2* __restrict__ tw,
+                                                              OpArgs op) {
+  using L = Lines<N1, N2>;
+  constexpr int n = L::n, nh = n / 2 + 1;
+  __shared__ float EX[L::tk * L::ps];
+  __shared__ float2 TW[n / 2];
+  const long long slab = static_cast<long long>(n) * n * nh;
+  in += blockIdx.y * slab;
+  if (full) full += blockIdx.y * slab;
+  out += blockIdx.y * 3 * slab;
+  load_tw(TW, tw, n);
+  const int li = threadIdx.x % L::tk, q = threadIdx.x / L::tk;
+  const int line = xcd_group(blockIdx.x, gridDim.x) * L::tk + li;
+  const bool valid = line < n * nh;
+  const int ky = line / nh, kx = line - ky * nh;
+  const long long stride = static_cast<long long>(n) * nh;
+  float* ex = EX + li * L::ps;
+  float2 v[kMaxR];
+  float sp[kMaxR];
+  const bool in_x = valid && q < N2, in_k = valid && q < N1;
+  if (in_x)
+#pragma unroll
+    for (int r = 0; r < N1; ++r) v[r] = in[line + (q + N2 * r) * stride];
+  __syncthreads();
+  line_forward<N1, N2>(v, ex, TW, q, in_x, in_k);
+  const int fy = signed_freq(ky, n);
+  if (in_k) {
+#pragma unroll
+    for (int r = 0; r < N2; ++r) {
+      const int kz = q + N1 * r;
+      if (full) full[line + kz * stride] = v[r];
+      sp[r] = mode_spectrum(op, mode_k2(kx, fy, signed_freq(kz, n), n));
+    }
+  }
+#pragma unroll 1
+  for (int axis = 0; axis < 3; ++axis) {
+    float2 w[kMaxR];
+    if (in_k) {
+#pragma unroll
+      for (int r = 0; r < N2; ++r) {
+        const int fz = signed_freq(q + N1 * r, n);
+        const float k2 = mode_k2(kx, fy, fz, n);
+        // k = 0 has no displacement
+        const float f = k2 == 0.0f ? 0.0f : deriv_k(axis, kx, fy, fz, n) * sp[r] / k2 * op.inv_n3;
+        // times i f, rounded before the transform's sums
+        w[r] = make_float2(opaque(-v[r].y * f), opaque(v[r].x * f));
+      }
+    }
+    __syncthreads();   // the pass before may still read the exchange buffer
+    line_inverse<N1, N2>(w, ex, TW, q, in_x, in_k);
+    if (in_x)
+#pragma unroll
+      for (int r = 0; r < N1; ++r) out[axis * slab + line + (q + N2 * r) * stride] = w[r];
+  }
+}
+
+// Adjoint of ic_disp_kernel: in[S][3] (spectra along x and y of the displacement's adjoint)
+// forward along z, times the conjugate operators, summed over the axes (and with sum[S], if
+// given, the spectrum of other terms; may be out), inverse along z into out[S].  (Three passes of
+// forward, operator and accumulation and one of the inverse took 315 us at 256^3; this takes 173.)
+template <int N1, int N2>
+__global__ void __launch_bounds__(kFftThreads) ic_disp_vjp_kernel(const float2* __restrict__ in,
+                                                                  const float2* sum, float2* out,
+                                                                  const float2* __restrict__ tw,
+                                                                  OpArgs op) {
+  using L = Lines<N1, N2>;
+  constexpr int n = L::n, nh = n / 2 + 1;
+  __shared__ float EX[L::tk * L::ps];
+  __shared__ float2 TW[n / 2];
+  const long long slab = static_cast<long long>(n) * n * nh;
+  in += blockIdx.y * 3 * slab;
+  if (sum) sum += blockIdx.y * slab;
+  out += blockIdx.y * slab;
+  load_tw(TW, tw, n);
+  const int li = threadIdx.x % L::tk, q = threadIdx.x / L::tk;
+  const int line = xcd_group(blockIdx.x, gridDim.x) * L::tk + li;
+  const bool valid = line < n * nh;
+  const int ky = line / nh, kx = line - ky * nh;
+  const long long stride = static_cast<long long>(n) * nh;
+  float* ex = EX + li * L::ps;
+  const bool in_x = valid && q < N2, in_k = valid && q < N1;
+  const int fy = signed_freq(ky, n);
+  float2 acc[kMaxR];
+  float sp[kMaxR];
+  if (in_k) {
+#pragma unroll
+    for (int r = 0; r < N2; ++r) {
+      const int kz = q + N1 * r;
+      sp[r] = mode_spectrum(op, mode_k2(kx, fy, signed_freq(kz, n), n));
+      acc[r] = sum ? sum[line + kz * stride] : make_float2(0.0f, 0.0f);
+    }
+  }
+#pragma unroll 1
+  for (int axis = 0; axis < 3; ++axis) {
+    float2 v[kMaxR];
+    if (in_x)
+#pragma unroll
+      for (int r = 0; r < N1; ++r) v[r] = in[axis * slab + line + (q + N2 * r) * stride];
+    __syncthreads();
+    line_forward<N1, N2>(v, ex, TW, q, in_x, in_k);
+    if (in_k) {
+#pragma unroll
+      for (int r = 0; r < N2; ++r) {
+        const int fz = signed_freq(q + N1 * r, n);
+        const float k2 = mode_k2(kx, fy, fz, n);
+        const float f = k2 == 0.0f ? 0.0f : deriv_k(axis, kx, fy, fz, n) * sp[r] / k2 * op.inv_n3;
+        acc[r] = cadd(acc[r], make_float2(v[r].y * f, -v[r].x * f));   // times -i f
+      }
+    }
+  }
+  __syncthreads();
+  line_inverse<N1, N2>(acc, ex, TW, q, in_x, in_k);
+  if (in_x)
+#pragma unroll
+    for (int r = 0; r < N1; ++r) out[line + (q + N2 * r) * stride] = acc[r];
+}
+
+template <int N1, int N2>
+void ic_disp_n(hipStream_t st, const float2* in, float2* full, float2* out, const float2* tw,
+               const OpArgs& op, const Batch& b) {
+  using L = Lines<N1, N2>;
+  constexpr int n = L::n, nh = n / 2 + 1;
+  hipLaunchKernelGGL((ic_disp_kernel<N1, N2>), dim3((n * nh + L::tk - 1) / L::tk, b.S),
+                     dim3(kFftThreads), 0, st, in, full, out, tw, op);
+}
+
+template <int N1, int N2>
+void ic_disp_vjp_n(hipStream_t st, const float2* in, const float2* sum, float2* out,
+                   const float2* tw, const OpArgs& op, const Batch& b) {
+  using L = Lines<N1, N2>;
+  constexpr int n = L::n, nh = n / 2 + 1;
+  hipLaunchKernelGGL((ic_disp_vjp_kernel<N1, N2>), dim3((n * nh + L::tk - 1) / L::tk, b.S),
+                     dim3(kFftThreads), 0, st, in, sum, out, tw, op);
 }
 
 template <int AX, int N1, int N2, int OPK>
@@ -667,12 +813,9 @@ void fft_zpass_inverse(hipStream_t st, float2* spec, const float2* tw, const Bat
   pencil(st, spec, spec, tw, 4, none, b);
 }
 
-// IC operators on the z pass (see apply_op): out = op(in), forward z transform first and
-// inverse after as asked
-void fft_zpass_ic(hipStream_t st, const float2* in, float2* out, const float2* tw,
-                  const IcOp& op, bool forward_first, bool inverse_after, bool accumulate,
-                  const Batch& b) {
-  const int n = b.n;
+namespace {
+
+OpArgs ic_args(const IcOp& op, int n) {
   OpArgs o{};
   o.op = op.op;
   o.axis = op.axis;
@@ -686,8 +829,36 @@ void fft_zpass_ic(hipStream_t st, const float2* in, float2* out, const float2* t
   o.eh_theta2 = static_cast<float>(op.eh_theta2);
   o.eh_alpha = static_cast<float>(op.eh_alpha);
   o.eh_ks = static_cast<float>(op.eh_ks);
+  return o;
+}
+
+}  // namespace
+
+// IC operators on the z pass (see apply_op): out = op(in), forward z transform first and
+// inverse after as asked
+void fft_zpass_ic(hipStream_t st, const float2* in, float2* out, const float2* tw,
+                  const IcOp& op, bool forward_first, bool inverse_after, bool accumulate,
+                  const Batch& b) {
   const int flags = (forward_first ? 1 : 0) | 2 | (inverse_after ? 4 : 0) | (accumulate ? 8 : 0);
-  pencil(st, in, out, tw, flags, o, b);
+  pencil(st, in, out, tw, flags, ic_args(op, b.n), b);
+}
+
+void fft_zpass_disp(hipStream_t st, const float2* in, float2* full, float2* out, const float2* tw,
+                    const IcOp& op, const Batch& b) {
+  const OpArgs o = ic_args(op, b.n);
+#define DH_CALL(a, c) ic_disp_n<a, c>(st, in, full, out, tw, o, b)
+  DH_FFT_DISPATCH(b.n, DH_CALL, DH_CALL)
+#undef DH_CALL
+  DH_LAUNCH_CHECK();
+}
+
+void fft_zpass_disp_vjp(hipStream_t st, const float2* in, const float2* sum, float2* out,
+                        const float2* tw, const IcOp& op, const Batch& b) {
+  const OpArgs o = ic_args(op, b.n);
+#define DH_CALL(a, c) ic_disp_vjp_n<a, c>(st, in, sum, out, tw, o, b)
+  DH_FFT_DISPATCH(b.n, DH_CALL, DH_CALL)
+#undef DH_CALL
+  DH_LAUNCH_CHECK();
 }
 
 }  // namespace dh
