@@ -1262,12 +1262,11 @@ void step_vjp(dh_sim* s, const TapeStep& T, bool defer_open) {
     dh::launch_grad_vjp(st, s->lg, s->lphi, s->lphi2, b);
   // Poisson (symmetric operator) and deposit at x1
   poisson(s, s->lphi2, s->ldelta, b);
-  dh::launch_axpy(st, s->lq, s->ldelta, 1.0f, nc, s->nq * nc, nc, false, b);
   // with the kicks' term at x1 (g_{n+1}) and the drift
   // x1 = x0 + p_half dt / a_h^2: lambda_p += (dt / a_h^2) lambda_x
   dh::launch_grad(st, T.phi1, s->g3b, b);
   dh::launch_deposit_vjp_pos(st, s->ldelta, T.x1, static_cast<float>(s->m_dm), s->lx, s->lp,
-                             s->g3b, b);
+                             s->g3b, s->lq, s->nq * nc, b);
   // sweeps in reverse; the first sweep's input is Q0 after the opening gas kick with phi_n
   for (int k = 2; k >= 0; --k) {
     {
@@ -1313,7 +1312,6 @@ void ic_vjp(dh_sim* s, float* d_grad_white) {
   const Batch b0 = batch(s, state_table(s));
   // phi_0 = Poisson(rho_gas + m_dm CIC(x) - 1)
   poisson(s, s->lphi, s->ldelta, b0);
-  dh::launch_axpy(st, s->lq, s->ldelta, 1.0f, nc, s->nq * nc, nc, false, all);
   // positions of the initial particles are recomputed from psi (the momenta, written to
   // scratch, are not needed)
   const double vfac = ai * ai * s->cosmo.E(ai) * s->cosmo.growth_rate(ai);
@@ -1321,7 +1319,7 @@ void ic_vjp(dh_sim* s, float* d_grad_white) {
   const float* vel = lpt2 ? s->lptv : s->psi;
   dh::launch_ic_particles(st, s->psi, vel, s->pos, s->fscratch, static_cast<float>(vfac), all);
   dh::launch_deposit_vjp_pos(st, s->ldelta, s->pos, static_cast<float>(s->m_dm), s->lx, nullptr,
-                             nullptr, all);
+                             nullptr, s->lq, s->nq * nc, all);
   // gas: rho = f_b CIC(x), m = rho p(q), Et = a^2 rho (e_init + |p/a|^2/2); with first-order
   // displacements the velocity displacement is psi itself and its adjoint goes to lpsi, with
   // second-order ones it has its own adjoint (lvel, in fscratch)
@@ -1331,7 +1329,7 @@ void ic_vjp(dh_sim* s, float* d_grad_white) {
   dh::launch_ic_gas_vjp(st, s->cic, vel, s->lq, static_cast<float>(s->f_b),
                         static_cast<float>(vfac), static_cast<float>(ai),
                         static_cast<float>(s->e_init), s->cfg.gamma, s->lcic, lvel, all);
-  dh::launch_deposit_vjp_pos(st, s->lcic, s->pos, 1.0f, s->lx, nullptr, nullptr, all);
+  dh::launch_deposit_vjp_pos(st, s->lcic, s->pos, 1.0f, s->lx, nullptr, nullptr, nullptr, 0, all);
   // x = q + psi, p = vfac vel
   dh::launch_axpy(st, s->lpsi, s->lx, 1.0f, 3 * nc, 3 * nc, 3 * nc, false, all);
   dh::launch_axpy(st, lvel, s->lp, static_cast<float>(vfac), 3 * nc, 3 * nc, 3 * nc, false, all);

@@ -116,10 +116,11 @@ void launch_kick_vjp_pos(hipStream_t st, const float3* g3, const float* pos,
                          const float* lam_p, bool merged, float* lam_x, const Batch& b);
 // adjoint of the deposit wrt positions: lam_x += mass sum_c lam_delta_c dw_c/dx; with lam_p
 // (table required), first (with g3) the merged kicks' term of launch_kick_vjp_pos and last
-// the drift's adjoint lam_p += drift lam_x
+// the drift's adjoint lam_p += drift lam_x; with lam_rho (sample s at lam_rho + s rho_stride),
+// lam_rho += lam_delta
 void launch_deposit_vjp_pos(hipStream_t st, const float* lam_delta, const float* pos,
                             float mass, float* lam_x, float* lam_p, const float3* g3,
-                            const Batch& b);
+                            float* lam_rho, long long rho_stride, const Batch& b);
 // y[s] += a x[s] over `count` values per sample (strides ys, xs); a times the table's drift
 // factor if by_drift
 void launch_axpy(hipStream_t st, float* y, const float* x, float a, long long count,

@@ -827,19 +827,24 @@ __global__ void __launch_bounds__(256) kick_vjp_pos_kernel(const float3* __restr
 // lam_x += mass * sum_corners lam_delta[corner] dw/dx
 // With lam_p: first, with g3, the merged dark-matter kicks' adjoint with respect to the
 // position (kick_vjp_pos_kernel, factor h_dm); last, lam_p += drift lam_x (the drift's
-// adjoint, x1 = x0 + drift p).  One pass, the roundings of the separate kernels.
+// adjoint, x1 = x0 + drift p).  With lam_rho (sample s at lam_rho + s rho_stride): lam_rho +=
+// lam_delta on the cells, as many as particles, while the pass reads lam_delta anyway (a pass of
+// its own took 40 us at 256^3).  One pass, the roundings of the separate kernels.
 __global__ void __launch_bounds__(256) deposit_vjp_pos_kernel(const float* __restrict__ lam_delta,
                                                               const float* __restrict__ pos,
                                                               float mass, float* __restrict__ lam_x,
                                                               float* __restrict__ lam_p,
                                                               const float3* __restrict__ g3,
-                                                              int n, long long np,
+                                                              float* __restrict__ lam_rho,
+                                                              long long rho_stride, int n,
+                                                              long long np,
                                                               const StepScal* __restrict__ tab) {
   const long long i = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= np || !sample_active(tab, blockIdx.y)) return;
   lam_delta += blockIdx.y * np;
   pos += blockIdx.y * 3 * np;
   lam_x += blockIdx.y * 3 * np;
+  if (lam_rho) lam_rho[blockIdx.y * rho_stride + i] += lam_delta[i];
   if (lam_p) lam_p += blockIdx.y * 3 * np;
   if (g3) g3 += blockIdx.y * np;
   const Cic w = cic_of(pos[i], pos[np + i], pos[2 * np + i], n);
@@ -1069,11 +1074,12 @@ void launch_kick_vjp_pos(hipStream_t st, const float3* g3, const float* pos, con
 }
 
 void launch_deposit_vjp_pos(hipStream_t st, const float* lam_delta, const float* pos, float mass,
-                            float* lam_x, float* lam_p, const float3* g3, const Batch& b) {
+                            float* lam_x, float* lam_p, const float3* g3, float* lam_rho,
+                            long long rho_stride, const Batch& b) {
   if (lam_p && !b.tab) throw ArgError("deposit adjoint: step table required for the drift");
   if (g3 && !lam_p) throw ArgError("deposit adjoint: the kick term needs lam_p");
   hipLaunchKernelGGL(deposit_vjp_pos_kernel, per_sample(b.nc(), b), dim3(256), 0, st, lam_delta,
-                     pos, mass, lam_x, lam_p, g3, b.n, b.nc(), b.tab);
+                     pos, mass, lam_x, lam_p, g3, lam_rho, rho_stride, b.n, b.nc(), b.tab);
   DH_LAUNCH_CHECK();
 }
 
