@@ -324,7 +324,7 @@ void launch_mlp_reduce_grad(hipStream_t st, const float* partial, int nparts,
                             const double* loss_part, double loss_scale, double* grad,
                             double* loss_out);
 void launch_mlp_adam(hipStream_t st, const float* partial, int nparts, const double* loss_part,
-                     double loss_scale, float* theta, float* m, float* v, const AdamArgs& a,
-                     double* loss_hist);
+                     double loss_scale, float* theta, float* m, float* v, uint4* packed,
+                     const AdamArgs& a, double* loss_hist);
 
 }  // namespace dh

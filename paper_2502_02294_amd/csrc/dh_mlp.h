@@ -206,14 +206,24 @@ __device__ __forceinline__ void backward(const uint4* fr, const Act<NCT> (&sd)[3
   }
 }
 
-// Copies the first nfrag packed fragments and the biases from global memory into LDS.
-// Block-wide; the caller synchronises before use.
-__device__ __forceinline__ void load_packed(const uint4* __restrict__ packed, int nfrag,
-                                            uint4* fr_lds, float* bias_lds) {
-  const int nv = nfrag * 64;
-  for (int i = threadIdx.x; i < nv; i += blockDim.x) fr_lds[i] = packed[i];
-  const float* b = reinterpret_cast<const float*>(packed + kFrAll * 64);
-  for (int i = threadIdx.x; i < kBias; i += blockDim.x) bias_lds[i] = b[i];
+// Copies the first NFRAG packed fragments and the biases from global memory into LDS, by a block
+// of THREADS threads; the caller synchronises before use.  The loads of a thread are all on their
+// way before the first is stored: one after the other they took up to half a training step's
+// gradient kernel.
+template <int NFRAG, int THREADS>
+__device__ __forceinline__ void load_packed(const uint4* __restrict__ packed, uint4* fr_lds,
+                                            float* bias_lds) {
+  constexpr int nv = NFRAG * 64, per = (nv + THREADS - 1) / THREADS;
+  static_assert(kBias <= THREADS, "one bias a thread");
+  const int t = threadIdx.x;
+  uint4 v[per];
+#pragma unroll
+  for (int k = 0; k < per; ++k) v[k] = packed[min(t + k * THREADS, nv - 1)];
+  const float b = reinterpret_cast<const float*>(packed + kFrAll * 64)[min(t, kBias - 1)];
+#pragma unroll
+  for (int k = 0; k < per; ++k)
+    if (t + k * THREADS < nv) fr_lds[t + k * THREADS] = v[k];
+  if (t < kBias) bias_lds[t] = b;
 }
 
 // Training targets of a cell state (FP64): o0 = ln(eps_sf / t_ff) with t_ff H0 =

@@ -863,7 +863,7 @@ __global__ void __launch_bounds__(kRedThreads) close_step_mlp_kernel(
   __shared__ uint4 fr[mlp::kFrFwd * 64];
   __shared__ __attribute__((aligned(16))) float bias[mlp::kBias];
   __shared__ __attribute__((aligned(16))) float stage[kRedThreads / 64][64][kStage];
-  mlp::load_packed(a.mlp, mlp::kFrFwd, fr, bias);
+  mlp::load_packed<mlp::kFrFwd, kRedThreads>(a.mlp, fr, bias);
   __syncthreads();   // the weights; from here on every wave works on its own cells
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int g = lane >> 4, cl = lane & 15;
@@ -970,7 +970,7 @@ __global__ void __launch_bounds__(kRedThreads, 2) source_vjp_mlp_kernel(
   __shared__ uint4 fr[mlp::kFrAll * 64];
   __shared__ __attribute__((aligned(16))) float bias[mlp::kBias];
   __shared__ __attribute__((aligned(16))) float stage[kRedThreads / 64][64][kStage];
-  mlp::load_packed(a.mlp, mlp::kFrAll, fr, bias);
+  mlp::load_packed<mlp::kFrAll, kRedThreads>(a.mlp, fr, bias);
   __syncthreads();   // the weights; from here on every wave works on its own cells
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int g = lane >> 4, cl = lane & 15;

@@ -316,8 +316,8 @@ int dh_mlp_train(dh_mlp* s, const float* d_x, const float* d_y, int64_t count,
       a.corr2 = static_cast<float>(1.0 / (1.0 - b2t));
       a.step = k;
       dh::launch_mlp_adam(s->st, s->partial, parts, s->loss_part,
-                          1.0 / static_cast<double>(o.batch), s->theta, s->m, s->v, a, s->hist);
-      dh::launch_mlp_pack(s->st, s->theta, s->packed);
+                          1.0 / static_cast<double>(o.batch), s->theta, s->m, s->v,
+                          s->packed, a, s->hist);
     }
     if (h_loss && o.steps > 0)
       DH_HIP(hipMemcpyAsync(h_loss, s->hist, o.steps * sizeof(double), hipMemcpyDeviceToHost,
