@@ -75,7 +75,7 @@ struct Bins {          // counting sort of particles by CIC base cell
   float3* sw1;         // [S np] upper CIC weights of the particles in bin order
 };
 size_t scan_block_count(long long nbins);
-// entries of Bins::large for `total` particles (bins of more than 256 particles)
+// entries of Bins::large for `total` particles (bins of more than a wave sorts)
 long long large_bin_capacity(long long total);
 void launch_keys(hipStream_t st, const float* pos, uint32_t* key, const Batch& b);
 // aux += CIC read-out of znew at each particle (pos: the positions at the end of the step;

@@ -18,6 +18,7 @@ namespace {
 
 constexpr int kScanThreads = 1024;
 constexpr int kLargeSortBlocks = 512;   // two blocks of 64 KB of LDS per CU
+constexpr int kLargeSortThreads = 1024;
 constexpr int kScanTile = kScanThreads * 4;   // one 16-byte vector of counts a thread
 
 __device__ __forceinline__ int wrapi(int j, int n) { return j & (n - 1); }
@@ -169,10 +170,12 @@ __global__ void scatter_kernel(const uint32_t* __restrict__ key, const uint32_t*
 // clustered state a lane alone sorted up to 32 ids through global memory (128^3 run to
 // a = 0.29: 54 + 21 us a step on average).  Runs longer than kWaveIds go in several parts;
 // bins of more than kWaveBin ids (dense halos gather thousands of particles in a cell) go to
-// a list that bin_sort_large_kernel sorts one workgroup per bin.  (Moving the positions along
+// a list that bin_sort_large_kernel sorts one workgroup of 1024 threads per bin.  (In that run the
+// two kernels take 44 + 15 us a step with bins of up to 256 left to the waves and 256 threads,
+// 44 + 10 with 1024, 36 + 11 with bins of up to 128 and 32 + 14 with 64.)  (Moving the positions along
 // with the ids in the scatter was slower: the scattered 16-byte writes cost more than the
 // gather's scattered reads.)
-constexpr uint32_t kWaveBin = 256;
+constexpr uint32_t kWaveBin = 128;
 constexpr uint32_t kWaveIds = 512;
 constexpr int kLdsSort = 16384;   // ids a workgroup sorts in LDS (64 KB)
 
@@ -280,7 +283,7 @@ __global__ void __launch_bounds__(256) bin_sort_gather_kernel(const uint32_t* __
       if (k <= 64)
         wave_rank_sort<1>(s, k, lane);
       else
-        wave_rank_sort<4>(s, k, lane);
+        wave_rank_sort<2>(s, k, lane);
     }
     wave_sync();
     for (uint32_t i = lane; i < total; i += 64) {
@@ -316,7 +319,7 @@ __device__ void bitonic_ascending(uint32_t k, uint32_t p, Get get, Put put) {
   }
 }
 
-__global__ void __launch_bounds__(256) bin_sort_large_kernel(const uint32_t* __restrict__ start,
+__global__ void __launch_bounds__(kLargeSortThreads) bin_sort_large_kernel(const uint32_t* __restrict__ start,
                                                              uint32_t* sorted,
                                                              const uint32_t* __restrict__ large,
                                                              const float* __restrict__ pos,
@@ -979,7 +982,7 @@ void launch_sort(hipStream_t st, const Bins& bins, const float* pos, const Batch
                      st, bins.start, bins.sorted, pos, bins.sw1, lnp, bins.count, bins.large,
                      keep_ids);
   DH_LAUNCH_CHECK();
-  hipLaunchKernelGGL(bin_sort_large_kernel, dim3(kLargeSortBlocks), dim3(256), 0, st, bins.start,
+  hipLaunchKernelGGL(bin_sort_large_kernel, dim3(kLargeSortBlocks), dim3(kLargeSortThreads), 0, st, bins.start,
                      bins.sorted, bins.large, pos, bins.sw1, lnp);
   DH_LAUNCH_CHECK();
 }

@@ -50,6 +50,7 @@ def _fill(n, sizes, seed):
 
 CASES = {
     "lane": ([8, 9, 7, 2] * 40, 1e-5),
+    "edge": ([128, 129, 127, 8, 130] * 6, 1e-5),
     "wave": ([64, 65, 256, 255, 63, 9] * 6, 1e-5),
     "neighbours": ([200] * 120, 1e-5),
     "workgroup": ([257, 300, 5000, 256], 1e-5),
