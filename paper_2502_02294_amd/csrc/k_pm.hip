@@ -74,11 +74,27 @@ __global__ void keys_kernel(const float* __restrict__ pos, uint32_t* __restrict_
   key[blockIdx.y * np + i] = bin_of(c, n, blockIdx.y, np);
 }
 
+// Counts a particle of bin k and returns its arrival rank there.  Neighbouring particles that fall
+// into one bin (in clustered states) are counted together: the first of a run of lanes adds the
+// run's length (128^3 run to a = 0.29: kick and drift 54.6 -> 45.6 us a step; before clustering as
+// with an atomic each).  All 64 lanes of the wave call it.
+__device__ __forceinline__ uint32_t count_in_bin(uint32_t* count, uint32_t k) {
+  const int lane = threadIdx.x & 63;
+  const uint32_t below = __shfl_up(k, 1, 64);
+  const uint64_t heads = __ballot(lane == 0 || k != below);
+  const int head = 63 - __builtin_clzll(heads & (~0ULL >> (63 - lane)));
+  const uint64_t after = heads >> lane >> 1;
+  uint32_t base = 0;
+  if (head == lane)
+    base = atomicAdd(&count[k], after ? __builtin_ctzll(after) + 1u : 64u - lane);
+  return __shfl(base, head, 64) + (lane - head);
+}
+
 __global__ void hist_kernel(const uint32_t* __restrict__ key, uint32_t* count,
                             uint32_t* __restrict__ rank, long long np) {
   const long long i = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= np) return;
-  rank[i] = atomicAdd(&count[key[i]], 1u);
+  if (i >= np) return;   // (np is a multiple of the block)
+  rank[i] = count_in_bin(count, key[i]);
 }
 
 // Scans of the bin counts: 32-bit integer sums, so the grouping does not change a result.
@@ -731,7 +747,7 @@ __global__ void __launch_bounds__(256) kick_drift_kernel(const float3* __restric
   if (count) rank += smp * np;
   if (!sc.active) {
     // the sort's histogram counts the sample's particles under the keys they have
-    if (count) rank[i] = atomicAdd(&count[key[i]], 1u);
+    if (count) rank[i] = count_in_bin(count, key[i]);
     // a sample that sits the step out keeps its particles; the copies (the tape of the
     // reverse pass, which sorts them again) receive them unchanged
 #pragma unroll
@@ -764,7 +780,7 @@ __global__ void __launch_bounds__(256) kick_drift_kernel(const float3* __restric
   const uint32_t k = bin_of(w2, n, smp, np);
   key[i] = k;
   // the sort's histogram (count zeroed beforehand): the arrival rank of the particle in its bin
-  if (count) rank[i] = atomicAdd(&count[k], 1u);
+  if (count) rank[i] = count_in_bin(count, k);
 }
 
 __global__ void __launch_bounds__(256) kick_kernel(const float3* __restrict__ g3,

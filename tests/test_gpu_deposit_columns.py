@@ -18,9 +18,9 @@ pytestmark = pytest.mark.gpu
 SIZES = [0, 1, 2, 3, 16, 17, 64, 65]
 
 
-def _seams(n, seed):
+def _seams(n, seed, runs):
     """n^3 particles: bins of the sizes above at the seams (and their neighbours), the rest of
-    the particles anywhere."""
+    the particles anywhere; in random order or (runs) a bin's particles one after the other."""
     r = np.random.default_rng(seed)
     edge = np.array([0, 1, 3, 4, 15, n - 1])
     cells = np.stack(np.meshgrid(edge, edge, edge, indexing="ij")).reshape(3, -1)
@@ -31,15 +31,16 @@ def _seams(n, seed):
     cell = np.concatenate([cell, r.integers(0, n, (3, rest))], axis=1)
     pos = (cell + 0.5 + r.uniform(0.0, 0.999, cell.shape)).astype(np.float32)
     pos = np.where(pos >= n, pos - n, pos).astype(np.float32)
-    return pos[:, r.permutation(n ** 3)]
+    return pos if runs else pos[:, r.permutation(n ** 3)]
 
 
-@pytest.mark.parametrize("n", [16, 32, 64, 128])
-def test_deposit_at_the_seams(n):
+@pytest.mark.parametrize("n,runs", [(16, False), (32, False), (32, True), (64, False), (128, False),
+                                    (128, True)])
+def test_deposit_at_the_seams(n, runs):
     import paper_2502_02294_amd as dhp
-    print(f"deposit seams: n {n}", flush=True)
+    print(f"deposit seams: n {n}, runs {runs}", flush=True)
     s = dhp.Sim(dhp.default_config(n=n))
-    pos = _seams(n, 7 * n)
+    pos = _seams(n, 7 * n, runs)
     zero = torch.zeros(n, n, n, dtype=torch.float32, device="cuda")
     d = s.stage_deposit(zero, to_gpu(pos)).double().cpu().numpy().reshape(-1)
     ref = (1.0 - 0.05 / 0.3) * _cic(pos, n)
