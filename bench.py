@@ -28,29 +28,27 @@ FP32_VECTOR_PEAK_TFLOPS = 157.3      # MI355X published FP32 vector peak
 SWEEP_FLOPS_PER_CELL = 236           # FP32 operations of one sweep per cell (FMA = 2)
 SWEEP_BYTES_PER_CELL = 40            # read Q, write Q
 SWEEP_VJP_BYTES_PER_CELL = 60        # read Q, read lambda_out, write lambda_in
-SWEEP_VJP_KICK_BYTES_PER_CELL = 16   # the first of a step's three also reads g4 (the kick)
+SWEEP_VJP_KICK_BYTES_PER_CELL = 4    # the first of a step's three also reads phi (the kick)
 # Algorithmic HBM bytes per cell (one particle per cell) of one step, recounted from the
 # kernels a step launches: every array a kernel must read or write, once.
 FWD_BYTES = [
-    ("kick+drift: x, p read and written, key written, g4 read", 68),
-    ("first sweep with the opening gas kick: Q read and written, g4 read", 56),
+    ("kick+drift: x, p read and written, key written, g read", 64),
+    ("first sweep with the opening gas kick: Q read and written, phi read", 44),
     ("second and third sweeps: Q read and written", 80),
-    ("sort: histogram 8, scan 8, scatter 12, bin sort 8, gather of x 32", 68),
-    ("deposit: bin starts, sorted x, rho_gas read, delta written", 28),
+    ("sort: histogram 8, scan 12, scatter 12, bin sort and gather of the weights 36", 68),
+    ("deposit: bin starts, sorted weights, rho_gas read, delta written", 24),
     ("FFT Poisson: r2c, y, z with Green's function, y, c2r passes", 64),
-    ("gradient: phi read, g4 written", 20),
-    ("closing pass: Q read and written, g4 read, star read and written", 64),
+    ("gradient: phi read, g written", 16),
+    ("closing pass: Q read and written, phi read, star read and written", 52),
 ]
 REV_BYTES = [
-    ("source, closing-kick and next opening-kick adjoints", 120),
-    ("gather of lambda_p into bin order", 32),
-    ("vector deposit of the kick adjoint", 60),
+    ("source, closing-kick and next opening-kick adjoints", 108),
+    ("vector deposit of the kick adjoint", 56),
     ("gradient adjoint (two fields)", 28),
     ("FFT Poisson of the potential adjoint", 64),
-    ("density adjoint added to lambda_rho", 12),
-    ("position adjoint of kicks, deposit and drift", 80),
-    ("three sweep adjoints (the first re-applies the opening kick: g4 read)", 196),
-    ("gradient of the step's start potential", 20),
+    ("position adjoint of kicks, deposit and drift; density adjoint", 84),
+    ("three sweep adjoints (the first re-applies the opening kick: phi read)", 184),
+    ("gradient of the step's end potential", 16),
 ]
 MODEL_FWD_BYTES = 340                # the byte model the >= 50% target is stated in
 MODEL_FWD_BWD_BYTES = 1180
@@ -472,8 +470,8 @@ def main():
         f"recomputed {t_fb_rc * 1e3:.1f} ms")
 
     # dominant kernel of the forward + reverse step: the sweep adjoint (three launches per
-    # step, about a fifth of the step), 60 algorithmic bytes per cell and launch (76 for the
-    # first, which reads g4 to re-apply the opening kick); beside it
+    # step, about a fifth of the step), 60 algorithmic bytes per cell and launch (64 for the
+    # first, which reads phi to re-apply the opening kick); beside it
     # the forward sweeps, 40 bytes and 236 FP32 operations per cell and launch.  Their
     # launches inside one more forward + loss + reverse pass of the same steps are timed by
     # the library with HIP events on the stream it launches them on.
