@@ -209,14 +209,17 @@ __device__ __forceinline__ void split_flux(const float* q, const HydroK& h, floa
 }
 
 // Vector-Jacobian product of the split fluxes at q: given the adjoints gR = dL/dF^R and
-// gL = dL/dF^L (NQ each), returns dL/dq = (dF^R/dq)^T gR + (dF^L/dq)^T gL
-//   = 1/2 [ c s + (dc/dq)(q . s) + (dF/dq)^T d ],  s = gR + gL, d = gR - gL.
+// gL = dL/dF^L (NQ each), returns twice dL/dq = (dF^R/dq)^T gR + (dF^L/dq)^T gL
+//   = 1/2 [ c s + (dc/dq)(q . s) + (dF/dq)^T d ],  s = gR + gL, d = gR - gL
+// (the callers' sums take the exact half along).
 // Derivatives are those of the floored EOS (zero through e where the floor is active), of
 // the branch of the dual-energy selection that the state takes, and of |U_d| with
-// sign(0) = 0.
+// sign(0) = 0.  Every FMA is spelled out and none left to the compiler, so that a cell's
+// adjoint is rounded alike in every visit of a walk, wherever its segment begins.
 template <int D, int NQ = 5, bool ETOT = false>
 __device__ __forceinline__ void split_flux_vjp(const float* q, const HydroK& h, const float* s,
                                                const float* dv, float* out) {
+#pragma clang fp contract(off)
   const float rho = q[0];
   const float ir = rcp_approx(rho);
   const float iar = h.ia * ir;
@@ -235,7 +238,8 @@ __device__ __forceinline__ void split_flux_vjp(const float* q, const HydroK& h, 
   // masked, so the function has no branches
   const float live = eraw < h.efloor ? 0.0f : 1.0f;
   const float e = fmaxf(eraw, h.efloor);
-  const float p = h.gm1 * rho * e;
+  const float pe = h.gm1 * rho;
+  const float p = pe * e;
   const float cs = sqrt_approx(h.gg1 * e);
   const float ud = u[D];
   const float md = q[1 + D];
@@ -245,7 +249,7 @@ __device__ __forceinline__ void split_flux_vjp(const float* q, const HydroK& h, 
   // derivatives of e (zero when floored); the entropy's branch: e = S rho^(gamma-2) / a^2
   const float lt = live * tot;
   float er = lt * (ke - e) * ir;
-  if (NQ == 6) er += live * (1.0f - tot) * h.gm2 * e * ir;
+  if (NQ == 6) er = fmaf(live * (1.0f - tot) * h.gm2 * e, ir, er);
   const float liar = -lt * iar;
   float em[3];
 #pragma unroll
@@ -253,45 +257,50 @@ __device__ __forceinline__ void split_flux_vjp(const float* q, const HydroK& h, 
   const float eE = lt * h.ia2 * ir;
   const float eS = NQ == 6 ? live * (1.0f - tot) * h.ia2 * rs : 0.0f;
   // pressure derivatives
-  const float pr = h.gm1 * (e + rho * er);
+  const float pr = h.gm1 * fmaf(rho, er, e);
   float pm[3];
 #pragma unroll
-  for (int k = 0; k < 3; ++k) pm[k] = h.gm1 * rho * em[k];
-  const float pE = h.gm1 * rho * eE;
+  for (int k = 0; k < 3; ++k) pm[k] = pe * em[k];
+  const float pE = pe * eE;
   // freezing-speed derivatives
   const float cse = live > 0.0f ? 0.5f * h.gg1 * rcp_approx(cs) : 0.0f;   // cs may be 0 if floored
-  const float cr = h.ia * (-fabsf(ud) * ir + cse * er);
+  const float cr = h.ia * fmaf(-fabsf(ud), ir, cse * er);
   float cm[3];
 #pragma unroll
-  for (int k = 0; k < 3; ++k) cm[k] = h.ia * ((k == D ? sgn * iar : 0.0f) + cse * em[k]);
+  for (int k = 0; k < 3; ++k)
+    cm[k] = h.ia * (k == D ? fmaf(sgn, iar, cse * em[k]) : cse * em[k]);
   const float cE = h.ia * cse * eE;
 
-  float qs = q[0] * s[0] + q[1] * s[1] + q[2] * s[2] + q[3] * s[3] + q[4] * s[4];
-  if (NQ == 6) qs += q[5] * s[5];
+  float qs = fmaf(q[0], s[0], q[1] * s[1]);
+#pragma unroll
+  for (int k = 2; k < NQ; ++k) qs = fmaf(q[k], s[k], qs);
   // (dF/dq)^T dv
-  const float H = (q[4] * h.ia2 + p) * ir;
-  const float vu = dv[1] * u[0] + dv[2] * u[1] + dv[3] * u[2];
-  const float W = dv[1 + D] + dv[4] * h.a * ud;
+  const float H = fmaf(q[4], h.ia2, p) * ir;
+  const float vu = fmaf(dv[3], u[2], fmaf(dv[1], u[0], dv[2] * u[1]));
+  const float va = dv[4] * h.a;
+  const float W = fmaf(va, ud, dv[1 + D]);
   float jt[5];
-  jt[0] = -ud * vu + pr * W - dv[4] * h.a * ud * H;
-  float diag = dv[0] * h.ia2 + h.ia * vu + dv[4] * H;
+  jt[0] = fmaf(-(va * ud), H, fmaf(-ud, vu, pr * W));
+  float diag = fmaf(dv[4], H, fmaf(dv[0], h.ia2, h.ia * vu));
   if (NQ == 6) {
     // F_S = S U_d / a
     const float fs = dv[5] * q[5] * h.ia;
-    jt[0] -= fs * ud * ir;
-    diag += fs * iar;
+    jt[0] = fmaf(-(fs * ud), ir, jt[0]);
+    diag = fmaf(fs, iar, diag);
   }
+  const float uda = ud * h.ia;
 #pragma unroll
-  for (int k = 0; k < 3; ++k) jt[1 + k] = (k == D ? diag : 0.0f) + ud * h.ia * dv[1 + k] + pm[k] * W;
-  jt[4] = pE * W + dv[4] * h.a * ud * h.ia2;
+  for (int k = 0; k < 3; ++k)
+    jt[1 + k] = fmaf(pm[k], W, k == D ? fmaf(uda, dv[1 + k], diag) : uda * dv[1 + k]);
+  jt[4] = fmaf(pE, W, va * ud * h.ia2);
 
   const float dc[5] = {cr, cm[0], cm[1], cm[2], cE};
 #pragma unroll
-  for (int k = 0; k < 5; ++k) out[k] = 0.5f * (c * s[k] + dc[k] * qs + jt[k]);
+  for (int k = 0; k < 5; ++k) out[k] = fmaf(c, s[k], dc[k] * qs) + jt[k];
   if (NQ == 6) {
-    const float pS = h.gm1 * rho * eS;
+    const float pS = pe * eS;
     const float cS = h.ia * cse * eS;
-    out[5] = 0.5f * (c * s[5] + cS * qs + pS * W + dv[5] * ud * h.ia);
+    out[5] = fmaf(dv[5], uda, fmaf(pS, W, fmaf(c, s[5], cS * qs)));
   }
 }
 

@@ -43,6 +43,7 @@ __device__ __forceinline__ void copy_block(const float* __restrict__ in, float* 
 // (F_{m+1} - F_m)/2) with respect to F^R at m-1, m, m+1
 __device__ __forceinline__ void face_r_coef(float fm1, float f0, float fp1, float& cm1, float& c0,
                                             float& cp1) {
+#pragma clang fp contract(off)
   float da, db;
   van_leer_half_d(f0 - fm1, fp1 - f0, da, db);
   cm1 = -da;
@@ -53,6 +54,7 @@ __device__ __forceinline__ void face_r_coef(float fm1, float f0, float fp1, floa
 // (F_{m+2} - F_{m+1})/2) with respect to F^L at m, m+1, m+2
 __device__ __forceinline__ void face_l_coef(float f0, float fp1, float fp2, float& c0, float& cp1,
                                             float& cp2) {
+#pragma clang fp contract(off)
   float da, db;
   van_leer_half_d(fp1 - f0, fp2 - fp1, da, db);
   c0 = da;
@@ -473,7 +475,10 @@ __global__ void __launch_bounds__(kRowThreads) sweep_x_vjp_kernel(
     }
     split_flux_vjp<0, NQ, true>(qh, h2, sv, dv, gr);
 #pragma unroll
-    for (int c = 0; c < NQ; ++c) S[0][c][j] = gr[c];
+    for (int c = 0; c < NQ; ++c) {
+      gr[c] *= 0.5f;
+      S[0][c][j] = gr[c];
+    }
   }
   __syncthreads();
   {  // 5. stage-1 transpose
@@ -487,7 +492,7 @@ __global__ void __launch_bounds__(kRowThreads) sweep_x_vjp_kernel(
     }
     split_flux_vjp<0, NQ, true>(u, h1, sv, dv, out);
 #pragma unroll
-    for (int c = 0; c < NQ; ++c) lam_in[c * nc + base + j] = lm[c] + gr[c] + out[c];
+    for (int c = 0; c < NQ; ++c) lam_in[c * nc + base + j] = fmaf(0.5f, out[c], lm[c] + gr[c]);
   }
 }
 
@@ -514,10 +519,14 @@ struct WalkVjp {
   float uh[4][NQ];            // Uh of cell k - 1 - j in slot (i - j) & 3
   float r2[4][NQ], l2[4][NQ];  // stage-2 split of cell k - 1 - j in slot (i - j) & 3
   float gr[4][NQ], gl[4][NQ];  // adjoints of F^R, F^L of cell k - 1 - j in slot (i - j) & 3
-  float lh[2][NQ];            // lambda_h of cell k - 3 - j in slot (i - j) & 1
+  float lh[2][NQ];            // twice lambda_h of cell k - 3 - j in slot (i - j) & 1
   float g1[2][NQ];            // G1 of face (k - 4 - j) + 1/2 in slot (i - j) & 1
   float g[2][6];              // first sweep: potentials around cell k + 1 - j, (i + 1 - j) & 1
 };
+
+// F^R + (-F^L) of a face.  Both are exact halves, so it is the same bits also where the compiler
+// takes one half into an FMA.
+__device__ __forceinline__ float face_flux(float r, float l) { return r - l; }
 
 // Returns x unchanged through an empty asm statement, so that the compiler cannot reuse
 // values it derived from x visits earlier (it would keep them in registers that long).
@@ -558,12 +567,15 @@ struct WalkVjpPtr {
 };
 
 
-// STAGE: 0 split only, 1 + F1, 2 + half step and stage-2 split, 3 + first faces (every
-// adjoint assigned), 4 + faces, 5 + lambda_h, 6 + G1, 7 + output
+// STAGE: 0 split only, 1 + F1, 2 + half step and stage-2 split, 3 + first faces, 4 + faces,
+// 5 + lambda_h, 6 + G1, 7 + output.  No FMA is left to the compiler, which would form them
+// differently in the visits that fill a segment's pipeline: a cell's adjoint is the same bits
+// however a launch cuts the pencils, and so a sample's gradient alone and in a batch.
 template <int D, int I, int STAGE, bool HEAD, bool KICK, int NQ>
 __device__ __forceinline__ void walk_vjp_visit(WalkVjp<NQ>& w, const WalkVjpPtr<NQ>& p, int k,
                                                const HydroK& h1, const HydroK& h2, float dt,
                                                float hdt) {
+#pragma clang fp contract(off)
   // rounding of the stage-1 splits where a head fills its pipeline (see kHead)
   constexpr bool fill = HEAD && STAGE < 7;
   constexpr int q1r = !fill                               ? kFluxRounded
@@ -595,7 +607,7 @@ __device__ __forceinline__ void walk_vjp_visit(WalkVjp<NQ>& w, const WalkVjpPtr<
   split_flux<D, NQ, q1r, q1l>(w.u[u0], h1, w.r1[p0], l1);
   if (STAGE < 1) return;
 #pragma unroll
-  for (int c = 0; c < NQ; ++c) w.f1[p0][c] = w.r1[p1][c] - l1[c];
+  for (int c = 0; c < NQ; ++c) w.f1[p0][c] = face_flux(w.r1[p1][c], l1[c]);
   if (STAGE < 2) return;
 #pragma unroll
   for (int c = 0; c < NQ; ++c) w.uh[t0][c] = fmaf(-hdt, w.f1[p0][c] - w.f1[p1][c], w.u[u1][c]);
@@ -610,16 +622,13 @@ __device__ __forceinline__ void walk_vjp_visit(WalkVjp<NQ>& w, const WalkVjpPtr<
     float b0, b1, b2;
     face_l_coef(w.l2[t2][c], w.l2[t1][c], w.l2[t0][c], b0, b1, b2);
     const float gL = dt * (w.lm[l3s][c] - w.lm[l2s][c]);
-    if (STAGE == 3) {
-      w.gr[t2][c] = gR * a0;
-      w.gr[t1][c] = gR * a1;
-      w.gl[t2][c] = gL * b0;
-      w.gl[t1][c] = gL * b1;
-    } else {
-      w.gr[t2][c] += gR * a0;
-      w.gr[t1][c] += gR * a1;
-      w.gl[t2][c] += gL * b0;
-      w.gl[t1][c] += gL * b1;
+    // (in the first faces of a segment t1 and t2 are cells before it, whose sums lack terms and
+    // are not used)
+    if (STAGE > 3) {
+      w.gr[t2][c] = fmaf(gR, a0, w.gr[t2][c]);
+      w.gr[t1][c] = fmaf(gR, a1, w.gr[t1][c]);
+      w.gl[t2][c] = fmaf(gL, b0, w.gl[t2][c]);
+      w.gl[t1][c] = fmaf(gL, b1, w.gl[t1][c]);
     }
     w.gr[t0][c] = gR * a2;
     w.gl[t0][c] = gL * b2;
@@ -637,7 +646,7 @@ __device__ __forceinline__ void walk_vjp_visit(WalkVjp<NQ>& w, const WalkVjpPtr<
   }
   if (STAGE < 6) return;
 #pragma unroll
-  for (int c = 0; c < NQ; ++c) w.g1[p0][c] = -hdt * (w.lh[p1][c] - w.lh[p0][c]);   // face k-4+1/2
+  for (int c = 0; c < NQ; ++c) w.g1[p0][c] = -0.5f * hdt * (w.lh[p1][c] - w.lh[p0][c]);   // face k-4+1/2
   if (STAGE < 7) return;
   {  // lambda of cell k-4
     float sv[NQ], dv[NQ], out[NQ], q[NQ];
@@ -650,7 +659,8 @@ __device__ __forceinline__ void walk_vjp_visit(WalkVjp<NQ>& w, const WalkVjpPtr<
     split_flux_vjp<D, NQ>(q, h1, sv, dv, out);
     const unsigned off = p.at(k - 4);
 #pragma unroll
-    for (int c = 0; c < NQ; ++c) p.st(c, off, w.lm[u4][c] + w.lh[p1][c] + out[c]);
+    for (int c = 0; c < NQ; ++c)
+      p.st(c, off, fmaf(0.5f, out[c], fmaf(0.5f, w.lh[p1][c], w.lm[u4][c])));
   }
 }
 
