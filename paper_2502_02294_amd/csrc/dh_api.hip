@@ -301,9 +301,20 @@ dh::HydroK hydro_at(const dh_sim* s, double a) {
 
 void sync(dh_sim* s) { DH_HIP(hipStreamSynchronize(s->st)); }
 
+// A call that takes tables for uploaded, or waits for the device, cannot be part of a captured
+// graph: what it enqueues would be recorded, not run.
+void refuse_capture(dh_sim* s) {
+  hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s->st, &c) != hipSuccess)
+    (void)hipGetLastError();   // another stream's capture; the launches say what they allow
+  else if (c != hipStreamCaptureStatusNone)
+    throw HipError("the stream is being captured");
+}
+
 // Small uploads from ordinary host memory, on the stream; staged through pinned memory (which
 // must be free again first) where they exceed a launch's arguments.
 void upload(dh_sim* s, void* dst, const void* src, size_t bytes) {
+  refuse_capture(s);
   if (dh::launch_upload(s->st, dst, src, bytes)) return;
   sync(s);
   std::memcpy(s->hstage, src, bytes);
@@ -317,6 +328,7 @@ void upload(dh_sim* s, void* dst, const void* src, size_t bytes) {
 // finished when this returns.
 void reduce_to_host(dh_sim* s, const double* in, int count, int stride, int nvec, bool max,
                     double* out) {
+  refuse_capture(s);
   const uint64_t seq = ++s->host_seq;
   dh::launch_reduce_to_host(s->st, in, count, stride, nvec, max, s->host_out, seq);
   for (int v = 0; v < nvec; ++v) {
@@ -1974,6 +1986,7 @@ int dh_backward(dh_sim* s, const float* d_grad_rho, float* d_grad_white, double*
                      1.0 / s->f_b, s->e_floor, s->t_per_e, s->cfg.gamma, nullptr, s->lq,
                      batch(s, nullptr));
     } else {
+      refuse_capture(s);
       const int nb = dh::cfl_blocks(s->n);
       dh::launch_loss_vjp(s->st, s->q, s->loss_target, s->prm.A, s->prm.beta,
                           static_cast<float>(1.0 / s->f_b), s->lq, s->red, batch(s, nullptr));
