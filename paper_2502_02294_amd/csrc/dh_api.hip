@@ -254,7 +254,7 @@ int fail(dh_sim* s, int code, const std::string& msg) {
 }
 
 template <typename F>
-int guarded(dh_sim* s, F&& f) {
+int run_guarded(dh_sim* s, F&& f) {
   try {
     return f();
   } catch (const ArgError& e) {
@@ -266,6 +266,19 @@ int guarded(dh_sim* s, F&& f) {
   } catch (const std::exception& e) {
     return fail(s, DH_E_HIP, e.what());
   }
+}
+
+template <typename F>
+int guarded(dh_sim* s, F&& f) {
+  const int rc = run_guarded(s, f);
+  // a histogram that a failed call left: cleared here, or, where that fails too, by the next one
+  if (s->bins.counting) {
+    try {
+      dh::clear_counts(s->st, s->bins);
+    } catch (const std::exception&) {
+    }
+  }
+  return rc;
 }
 
 // Records an event pair around the launches made during its lifetime when the handle times
@@ -1512,6 +1525,7 @@ int dh_create(const dh_config* cfg, dh_sim** out) {
     s->bins.key = s->alloc<uint32_t>(np);
     s->bins.rank = s->alloc<uint32_t>(np);
     s->bins.count = s->alloc<uint32_t>(nc);
+    s->bins.size = nc;
     s->bins.start = s->alloc<uint32_t>(nc + 1);
     s->bins.sorted = s->alloc<uint32_t>(np);
     s->bins.block_sums = s->alloc<uint32_t>(static_cast<long long>(dh::scan_block_count(nc)));

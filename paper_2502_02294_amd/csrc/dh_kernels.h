@@ -73,7 +73,11 @@ struct Bins {          // counting sort of particles by CIC base cell
   uint32_t* block_sums;  // [scan blocks]
   uint32_t* large;     // [1 + large_bin_capacity(total)]: count, then bins of many particles
   float3* sw1;         // [S np] upper CIC weights of the particles in bin order
+  long long size;      // S nc
+  bool counting;       // a histogram was begun and no sort has taken it (and cleared count) yet
 };
+// count is zero afterwards (a call that failed between histogram and sort leaves it otherwise)
+void clear_counts(hipStream_t st, Bins& bins);
 size_t scan_block_count(long long nbins);
 // entries of Bins::large for `total` particles (bins of more than a wave sorts)
 long long large_bin_capacity(long long total);
@@ -85,8 +89,8 @@ void launch_star_readout(hipStream_t st, const float* znew, const float* pos, fl
 // sort by bins.key (already computed for pos) and gather the particles' weights into bin order;
 // counted: the histogram was made by launch_kick_drift (count_into); keep_ids: the ids, too,
 // are wanted in bin order (bins.sorted, for launch_deposit_vec)
-void launch_sort(hipStream_t st, const Bins& bins, const float* pos, const Batch& b,
-                 bool counted, bool keep_ids);
+void launch_sort(hipStream_t st, Bins& bins, const float* pos, const Batch& b, bool counted,
+                 bool keep_ids);
 // out = rho_gas + m_dm * CIC(sorted positions) + offset; rho_gas (sample s at
 // rho_gas + s * rho_stride: 5 n^3 for the density row of Q) may be null (then 0)
 void launch_deposit(hipStream_t st, const Bins& bins, const float* rho_gas,
@@ -107,7 +111,7 @@ void launch_readout_g(hipStream_t st, const float3* g3, const float* pos, float*
 // launch_sort(..., counted = true) (arrival ranks)
 void launch_kick_drift(hipStream_t st, const float3* g3, const float* pos_in, float* pos,
                        float* mom, uint32_t* key, float* mom_copy, float* pos_copy, bool prev,
-                       const Batch& b, const Bins* count_into = nullptr);
+                       const Batch& b, Bins* count_into = nullptr);
 // closing kick p += h_close g(x)
 void launch_kick(hipStream_t st, const float3* g3, const float* pos, float* mom, const Batch& b);
 // adjoint of p' = p + k g(x) with respect to x: lam_x += k sum_c dw/dx (g_c . lam_p'), with

@@ -969,11 +969,19 @@ void launch_keys(hipStream_t st, const float* pos, uint32_t* key, const Batch& b
   DH_LAUNCH_CHECK();
 }
 
-void launch_sort(hipStream_t st, const Bins& bins, const float* pos, const Batch& b,
-                 bool counted, bool keep_ids) {
+void clear_counts(hipStream_t st, Bins& bins) {
+  if (!bins.counting) return;
+  launch_fill(st, reinterpret_cast<float*>(bins.count), 0.0f, bins.size);
+  bins.counting = false;
+}
+
+void launch_sort(hipStream_t st, Bins& bins, const float* pos, const Batch& b, bool counted,
+                 bool keep_ids) {
   const long long nbins = b.nc() * b.S, total = nbins;
   const int lnp = log2_ll(b.nc());
   if (!counted) {
+    clear_counts(st, bins);
+    bins.counting = true;
     hipLaunchKernelGGL(hist_kernel, dim3(blocks_for(total, 256)), dim3(256), 0, st, bins.key,
                        bins.count, bins.rank, total);
     DH_LAUNCH_CHECK();
@@ -998,6 +1006,7 @@ void launch_sort(hipStream_t st, const Bins& bins, const float* pos, const Batch
                      st, bins.start, bins.sorted, pos, bins.sw1, lnp, bins.count, bins.large,
                      keep_ids);
   DH_LAUNCH_CHECK();
+  bins.counting = false;
   hipLaunchKernelGGL(bin_sort_large_kernel, dim3(kLargeSortBlocks), dim3(kLargeSortThreads), 0, st, bins.start,
                      bins.sorted, bins.large, pos, bins.sw1, lnp);
   DH_LAUNCH_CHECK();
@@ -1067,11 +1076,15 @@ void launch_star_readout(hipStream_t st, const float* znew, const float* pos, fl
 
 void launch_kick_drift(hipStream_t st, const float3* g3, const float* pos_in, float* pos,
                        float* mom, uint32_t* key, float* mom_copy, float* pos_copy, bool prev,
-                       const Batch& b, const Bins* count_into) {
+                       const Batch& b, Bins* count_into) {
   if (!b.tab) throw ArgError("kick_drift: step table required");
   if (count_into && key != count_into->key) throw ArgError("kick_drift: keys of another sort");
   uint32_t* count = count_into ? count_into->count : nullptr;
   uint32_t* rank = count_into ? count_into->rank : nullptr;
+  if (count_into) {
+    clear_counts(st, *count_into);
+    count_into->counting = true;
+  }
   hipLaunchKernelGGL(kick_drift_kernel, per_sample(b.nc(), b), dim3(256), 0, st, g3, pos_in, pos,
                      mom, key, mom_copy, pos_copy, b.n, b.nc(), prev ? 1 : 0, b.tab, count, rank);
   DH_LAUNCH_CHECK();

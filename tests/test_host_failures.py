@@ -1,0 +1,76 @@
+"""What a handle does after a call has failed half-way, on a stand-in for the HIP runtime
+(tests/hip_stub.cpp, preloaded into a child process): kernels do nothing, chosen runtime calls
+fail, and the stand-in keeps watch over what the library asks of it.  No GPU needed."""
+
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+LIB = os.path.join(ROOT, "paper_2502_02294_amd", "libdiffhydro.so")
+
+PRELUDE = """
+import ctypes, importlib.util, sys
+spec = importlib.util.spec_from_file_location("binding", sys.argv[1])
+b = importlib.util.module_from_spec(spec)
+spec.loader.exec_module(b)
+lib, stub = b.lib(), ctypes.CDLL(None)
+stub.stub_log.restype = ctypes.c_char_p
+def create(**kw):
+    c = b.Config()
+    lib.dh_config_default(ctypes.byref(c))
+    c.n, c.box = 16, 2.5
+    for k, v in kw.items():
+        setattr(c, k, v)
+    h = ctypes.c_void_p()
+    assert lib.dh_create(ctypes.byref(c), ctypes.byref(h)) == 0
+    return h
+def buf(count):
+    return ctypes.cast((ctypes.c_float * count)(*[0.5] * count), ctypes.c_void_p)
+N = ctypes.c_int32()
+"""
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    if not os.path.exists(LIB):
+        from paper_2502_02294_amd import build_lib
+        build_lib.build(verbose=False)
+    so = tmp_path_factory.mktemp("stub") / "hip_stub.so"
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC",
+                    os.path.join(HERE, "hip_stub.cpp"), "-o", str(so)], check=True)
+    return str(so)
+
+
+def run(stub, code, *args):
+    env = dict(os.environ)
+    env["LD_PRELOAD"] = ":".join(p for p in (stub, env.get("LD_PRELOAD")) if p)
+    binding = os.path.join(ROOT, "paper_2502_02294_amd", "_lib.py")
+    r = subprocess.run([sys.executable, "-c", PRELUDE + code, binding, *map(str, args)], env=env,
+                       capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-2000:]
+
+
+@pytest.mark.parametrize("kernel", ["kick_drift_kernel", "sweep_x_kernel", "scan_kernel",
+                                    "scatter_kernel", "bin_sort_gather_kernel",
+                                    "bin_sort_large_kernel", "deposit_kernel"])
+def test_bin_counts_are_clear_after_a_failed_step(stub, kernel):
+    """A step counts the particles' bins in the drift and clears the counts in the sort; a
+    histogram on counts that a failed call left behind would index past the particles."""
+    run(stub, """
+h = create()
+pos, rho, out = buf(3 * 16**3), buf(16**3), buf(16**3)
+assert lib.dh_init_from_seed(h, 1) == 0
+for again in (lambda: lib.dh_run_steps(h, 1, ctypes.byref(N)),
+              lambda: lib.dh_stage_deposit(h, rho, pos, out),
+              lambda: lib.dh_init_from_seed(h, 2)):
+    stub.stub_fail_kernel(sys.argv[2].encode())
+    assert lib.dh_run_steps(h, 1, ctypes.byref(N)) == -3
+    assert again() == 0
+    assert lib.dh_init_from_seed(h, 1) == 0
+    assert lib.dh_run_steps(h, 2, ctypes.byref(N)) == 0
+    assert stub.stub_dirty_counts() == 0, sys.argv[2]
+""", kernel)
