@@ -233,10 +233,18 @@ struct dh_sim {
   template <typename T>
   T* alloc(long long count) {
     void* p = nullptr;
-    if (hipMalloc(&p, static_cast<size_t>(count) * sizeof(T)) != hipSuccess)
+    if (hipMalloc(&p, static_cast<size_t>(count) * sizeof(T)) != hipSuccess) {
+      (void)hipGetLastError();   // reported here, not again by a later launch's check
       throw std::bad_alloc();
+    }
     allocs.push_back(p);
     return static_cast<T*>(p);
+  }
+  // for buffers made when they are first needed: what an earlier call that failed half-way has
+  // made is kept, what it has not is made now
+  template <typename T>
+  void ensure(T*& p, long long count) {
+    if (!p) p = alloc<T>(count);
   }
   void release(void* p) {
     if (!p) return;
@@ -421,37 +429,54 @@ StepScal entry_of(const dh_sim* s, int smp, const Plan& p, int step) {
   return e;
 }
 
-// Grows the table store to hold `slots` steps (keeping the tables written so far).
+template <typename T>
+T* alloc_pinned(size_t count) {
+  void* p = nullptr;
+  const hipError_t e = hipHostMalloc(&p, count * sizeof(T), hipHostMallocDefault);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    throw HipError(std::string("pinned memory: ") + hipGetErrorString(e));
+  }
+  return static_cast<T*>(p);
+}
+
+// Grows the table store to hold `slots` steps (keeping the tables written so far).  The old
+// store stays until the new one is whole.
 void ensure_tab_slots(dh_sim* s, int slots) {
   if (slots <= s->tab_cap) return;
   const int cap = std::max(slots, 2 * s->tab_cap + 64);
+  const size_t count = static_cast<size_t>(cap) * s->S;
   sync(s);
-  StepScal* d = s->alloc<StepScal>(static_cast<long long>(cap) * s->S);
-  double* sl = s->alloc<double>(static_cast<long long>(cap) * s->S);
-  void* hp = nullptr;
-  DH_HIP(hipHostMalloc(&hp, static_cast<size_t>(cap) * s->S * sizeof(StepScal),
-                       hipHostMallocDefault));
-  StepScal* h = static_cast<StepScal*>(hp);
-  if (s->host_log) (void)hipHostFree(s->host_log);
-  s->host_log = nullptr;
-  DH_HIP(hipHostMalloc(&hp, static_cast<size_t>(cap) * s->S * sizeof(double),
-                       hipHostMallocDefault));
-  s->host_log = static_cast<double*>(hp);
-  if (s->tabs) {
-    const size_t bytes = static_cast<size_t>(s->tab_cap) * s->S * sizeof(StepScal);
-    DH_HIP(hipMemcpy(d, s->tabs, bytes, hipMemcpyDeviceToDevice));
-    DH_HIP(hipMemcpy(sl, s->speed_log, static_cast<size_t>(s->tab_cap) * s->S * sizeof(double),
-                     hipMemcpyDeviceToDevice));
-    std::memcpy(h, s->htabs, bytes);
-    s->release(s->tabs);
-    s->release(s->speed_log);
-    (void)hipHostFree(s->htabs);
+  StepScal *d = nullptr, *h = nullptr;
+  double *sl = nullptr, *hl = nullptr;
+  try {
+    d = s->alloc<StepScal>(static_cast<long long>(count));
+    sl = s->alloc<double>(static_cast<long long>(count));
+    h = alloc_pinned<StepScal>(count);
+    hl = alloc_pinned<double>(count);
+    s->replayed.resize(count, 0.0);
+    if (s->tabs) {
+      const size_t had = static_cast<size_t>(s->tab_cap) * s->S;
+      DH_HIP(hipMemcpy(d, s->tabs, had * sizeof(StepScal), hipMemcpyDeviceToDevice));
+      DH_HIP(hipMemcpy(sl, s->speed_log, had * sizeof(double), hipMemcpyDeviceToDevice));
+      std::memcpy(h, s->htabs, had * sizeof(StepScal));
+    }
+  } catch (...) {
+    s->release(d);
+    s->release(sl);
+    if (h) (void)hipHostFree(h);
+    if (hl) (void)hipHostFree(hl);
+    throw;
   }
-  s->tabs = d;
-  s->speed_log = sl;
-  s->replayed.resize(static_cast<size_t>(cap) * s->S, 0.0);
-  s->htabs = h;
+  std::swap(s->tabs, d);
+  std::swap(s->speed_log, sl);
+  std::swap(s->htabs, h);
+  std::swap(s->host_log, hl);
   s->tab_cap = cap;
+  s->release(d);
+  s->release(sl);
+  if (h) (void)hipHostFree(h);
+  if (hl) (void)hipHostFree(hl);
 }
 
 // Writes the table of a planned step into its slot (host mirror and device).  Each slot
@@ -940,6 +965,7 @@ void power_spectrum(dh_sim* s, int nbins, std::vector<double>& pk) {
   if (s->pk_part_bins < nbins) {
     if (s->pk_part) s->release(s->pk_part);
     s->pk_part = nullptr;
+    s->pk_part_bins = 0;
     s->pk_part = s->alloc<double>(static_cast<long long>(S) * nbins * nblk);
     s->pk_part_bins = nbins;
   }
@@ -969,7 +995,7 @@ void power_spectrum(dh_sim* s, int nbins, std::vector<double>& pk) {
 void power_loss_vjp(dh_sim* s) {
   const Batch b = batch(s, nullptr);
   const int nbins = s->pk_loss_bins;
-  if (!s->d_pk_g) s->d_pk_g = s->alloc<float>(static_cast<long long>(s->S) * (s->n / 2));
+  s->ensure(s->d_pk_g, static_cast<long long>(s->S) * (s->n / 2));
   DH_HIP(hipMemcpyAsync(s->d_pk_g, s->pk_g.data(), s->pk_g.size() * sizeof(float),
                         hipMemcpyHostToDevice, s->st));
   density_spectrum(s, b);
@@ -1137,16 +1163,19 @@ bool try_alloc_tape_entry(dh_sim* s, TapeStep& t) {
   }
 }
 
+void ensure_ckpt(dh_sim* s, Ckpt& c) {
+  const long long S = s->S;
+  s->ensure(c.q, s->nq * s->nc * S);
+  s->ensure(c.pos, 3 * s->np * S);
+  s->ensure(c.mom, 3 * s->np * S);
+  s->ensure(c.star, s->nc * S);
+  s->ensure(c.phi, s->nc * S);
+}
+
 void save_ckpt(dh_sim* s, Ckpt& c) {
   const long long S = s->S;
   flush_kick(s);
-  if (!c.q) {
-    c.q = s->alloc<float>(s->nq * s->nc * S);
-    c.pos = s->alloc<float>(3 * s->np * S);
-    c.mom = s->alloc<float>(3 * s->np * S);
-    c.star = s->alloc<float>(s->nc * S);
-    c.phi = s->alloc<float>(s->nc * S);
-  }
+  ensure_ckpt(s, c);
   copy_d2d(s, c.q, s->q, s->nq * s->nc * S);
   copy_d2d(s, c.pos, s->pos, 3 * s->np * S);
   copy_d2d(s, c.mom, s->mom, 3 * s->np * S);
@@ -1178,14 +1207,7 @@ void load_ckpt(dh_sim* s, const Ckpt& c) {
 void stash_state(dh_sim* s) {
   flush_kick(s);
   Ckpt& c = s->keep;
-  const long long S = s->S;
-  if (!c.q) {
-    c.q = s->alloc<float>(s->nq * s->nc * S);
-    c.pos = s->alloc<float>(3 * s->np * S);
-    c.mom = s->alloc<float>(3 * s->np * S);
-    c.star = s->alloc<float>(s->nc * S);
-    c.phi = s->alloc<float>(s->nc * S);
-  }
+  ensure_ckpt(s, c);
   std::swap(s->q, c.q);
   std::swap(s->pos, c.pos);
   std::swap(s->mom, c.mom);
@@ -1924,7 +1946,7 @@ int dh_loss(dh_sim* s, const float* d_target, double* loss_out) {
                             static_cast<float>(1.0 / s->f_b), s->red, batch(s, nullptr));
     reduce_to_host(s, s->red, nb, nb, s->S, false, loss_out);
     for (int i = 0; i < s->S; ++i) loss_out[i] /= static_cast<double>(s->nc);
-    if (!s->loss_target) s->loss_target = s->alloc<float>(s->nc * s->S);
+    s->ensure(s->loss_target, s->nc * s->S);
     copy_d2d(s, s->loss_target, d_target, s->nc * s->S);
     s->have_loss = s->have_forward;
     s->loss_kind = dh_sim::kLossFlux;
@@ -1942,30 +1964,26 @@ int dh_backward(dh_sim* s, const float* d_grad_rho, float* d_grad_white, double*
     const int nsteps = s->fwd_steps;
     s->open_pending = false;
     const int K = s->cfg.ckpt_every;
-    if (!s->lq) {
-      s->lq = s->alloc<float>(s->nq * nc * S);
-      s->lq2 = s->alloc<float>(s->nq * nc * S);
-      s->lx = s->alloc<float>(3 * np * S);
-      s->lp = s->alloc<float>(3 * np * S);
-      s->lphi = s->alloc<float>(nc * S);
-      s->lphi2 = s->alloc<float>(nc * S);
-      s->lg = s->alloc<float>(3 * nc * S);
-      s->lg2 = s->alloc<float>(3 * nc * S);
-      s->ldelta = s->alloc<float>(nc * S);
-      s->lpsi = s->alloc<float>(3 * nc * S);
-      s->lcic = s->alloc<float>(nc * S);
-    }
+    s->ensure(s->lq, s->nq * nc * S);
+    s->ensure(s->lq2, s->nq * nc * S);
+    s->ensure(s->lx, 3 * np * S);
+    s->ensure(s->lp, 3 * np * S);
+    s->ensure(s->lphi, nc * S);
+    s->ensure(s->lphi2, nc * S);
+    s->ensure(s->lg, 3 * nc * S);
+    s->ensure(s->lg2, 3 * nc * S);
+    s->ensure(s->ldelta, nc * S);
+    s->ensure(s->lpsi, 3 * nc * S);
+    s->ensure(s->lcic, nc * S);
     if (s->param_cap < nsteps + 2) {
-      if (s->param_steps) s->release(s->param_steps);
-      s->param_steps = nullptr;
-      s->param_cap = nsteps + 2;
-      s->param_steps = s->alloc<double>(2LL * S * s->param_cap);
+      s->release(s->param_steps);
       if (s->host_params) (void)hipHostFree(s->host_params);
-      s->host_params = nullptr;
-      void* hp = nullptr;
-      DH_HIP(hipHostMalloc(&hp, 2 * static_cast<size_t>(S) * (s->param_cap + 1) * sizeof(double),
-                           hipHostMallocDefault));
-      s->host_params = static_cast<double*>(hp);
+      s->param_steps = s->host_params = nullptr;
+      s->param_cap = 0;
+      const int cap = nsteps + 2;
+      s->param_steps = s->alloc<double>(2LL * S * cap);
+      s->host_params = alloc_pinned<double>(2 * static_cast<size_t>(S) * (cap + 1));
+      s->param_cap = cap;
     }
     // dark-matter kick factors of the reverse pass: the step's closing kick plus the same
     // sample's next opening kick (0 after its last step)
@@ -2013,7 +2031,10 @@ int dh_backward(dh_sim* s, const float* d_grad_rho, float* d_grad_white, double*
     const size_t want = s->taped < nsteps ? static_cast<size_t>(std::min(K, nsteps)) : 0;
     while (s->tape.size() < want) {
       s->tape.push_back(TapeStep{});
-      alloc_tape_entry(s, s->tape.back());
+      if (!try_alloc_tape_entry(s, s->tape.back())) {
+        s->tape.pop_back();
+        throw std::bad_alloc();
+      }
     }
     // set the forward's final state aside to restore it afterwards
     stash_state(s);
@@ -2153,12 +2174,10 @@ int dh_fli_loss(dh_sim* s, const float* d_data, const float* d_noise_var, const 
   return guarded(s, [&]() -> int {
     const int S = s->S;
     const long long nc = s->nc;
-    if (!s->fli_data) {
-      s->fli_data = s->alloc<float>(nc * S);
-      s->fli_nvar = s->alloc<float>(nc * S);
-      s->fli_white = s->alloc<float>(nc * S);
-      s->fli_part = s->alloc<double>(static_cast<long long>(dh::fli_blocks(nc)) * S);
-    }
+    s->ensure(s->fli_data, nc * S);
+    s->ensure(s->fli_nvar, nc * S);
+    s->ensure(s->fli_white, nc * S);
+    s->ensure(s->fli_part, static_cast<long long>(dh::fli_blocks(nc)) * S);
     copy_d2d(s, s->fli_data, d_data, nc * S);
     copy_d2d(s, s->fli_nvar, d_noise_var, nc * S);
     copy_d2d(s, s->fli_white, d_white, nc * S);

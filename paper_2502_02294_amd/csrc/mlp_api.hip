@@ -41,8 +41,10 @@ struct dh_mlp {
   template <typename T>
   T* alloc(long long count) {
     void* p = nullptr;
-    if (hipMalloc(&p, static_cast<size_t>(count) * sizeof(T)) != hipSuccess)
+    if (hipMalloc(&p, static_cast<size_t>(count) * sizeof(T)) != hipSuccess) {
+      (void)hipGetLastError();   // reported here, not again by a later launch's check
       throw std::bad_alloc();
+    }
     allocs.push_back(p);
     return static_cast<T*>(p);
   }

@@ -172,7 +172,8 @@ int hipLaunchKernel(const void* f, Dim3 grid, Dim3, void** args, size_t, void*) 
       for (long long i = 0; i < n; ++i) std::memcpy(p + 4 * i, &v, 4);
     }
   }
-  if (is("reduce_kernel") && bad(pointer(3))) ++null_writes;   // in, count, stride, out
+  if ((is("reduce_kernel") || is("reduce_to_host_kernel")) && (bad(pointer(0)) || bad(pointer(3))))
+    ++null_writes;   // in, count, stride, out
   if (is("reduce_to_host_kernel") && !hold_values) {           // in, count, stride, out, seq
     char* out = pointer(3);
     const uint64_t seq = *static_cast<uint64_t*>(args[4]);

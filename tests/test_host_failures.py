@@ -74,3 +74,48 @@ for again in (lambda: lib.dh_run_steps(h, 1, ctypes.byref(N)),
     assert lib.dh_run_steps(h, 2, ctypes.byref(N)) == 0
     assert stub.stub_dirty_counts() == 0, sys.argv[2]
 """, kernel)
+
+
+@pytest.mark.parametrize("kind", ["malloc", "host_malloc"])
+@pytest.mark.parametrize("call", ["backward", "forward", "fli_loss", "power_loss"])
+def test_a_call_whose_allocation_failed_can_be_made_again(stub, kind, call):
+    """Every allocation of a call fails in turn; the call reports it, and made again it works on
+    whole buffers: nothing is launched on, or copied through, one that was never allocated."""
+    run(stub, """
+kind, call = sys.argv[2], sys.argv[3]
+white, out, a, c = buf(16**3), buf(16**3), buf(16**3), buf(16**3)
+loss, par = (ctypes.c_double * 1)(), (ctypes.c_double * 4)()
+pk, sig = (ctypes.c_double * 8)(*[1.0] * 8), (ctypes.c_double * 8)(*[1.0] * 8)
+fail = getattr(stub, "stub_fail_" + kind)
+fails = 0
+for k in range(200):
+    h = create(ckpt_every=3)
+    lib.dh_set_store_limit(h, 3)     # taped steps, checkpoints and recomputed steps
+    sched = (ctypes.c_double * 80)(*[1e-4] * 80)
+    def forward(steps):
+        assert lib.dh_set_schedule(h, sched, steps) == 0
+        return lib.dh_forward(h, white, 1.0, ctypes.byref(N))
+    if call != "forward":
+        assert forward(7) == 0
+        assert lib.dh_loss(h, a, loss) == 0
+    f = {"backward": lambda: lib.dh_backward(h, None, out, par),
+         "forward": lambda: forward(70),
+         "fli_loss": lambda: lib.dh_fli_loss(h, a, c, white, loss),
+         "power_loss": lambda: lib.dh_power_loss(h, 8, pk, sig, loss)}[call]
+    fail(k)
+    rc = f()
+    fail(-1)
+    if rc == 0:
+        break
+    assert rc in (-2, -3), rc
+    fails += 1
+    assert f() == 0, (k, lib.dh_last_error(h))
+    if call != "backward":
+        assert call == "forward" or lib.dh_backward(h, None, out, par) == 0
+    else:   # a later, longer run grows the same buffers
+        assert forward(70) == 0 and lib.dh_loss(h, a, loss) == 0
+        assert f() == 0
+    assert stub.stub_null_writes() == 0, k
+    assert lib.dh_destroy(h) == 0
+assert k < 199 and (fails > 0 or kind == "host_malloc" or call == "power_loss"), (k, fails)
+""", kind, call)
