@@ -15,6 +15,7 @@
 // adjoint kernels need (the tape of that segment), then applies the adjoint of each step
 // in reverse order, and finally the adjoint of the initial conditions.
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstring>
 #include <memory>
@@ -345,27 +346,31 @@ void upload(dh_sim* s, void* dst, const void* src, size_t bytes) {
 // out[v] = reduction over in[v * stride + 0..count), v < nvec <= 2 S + 16, returned to the host.  The
 // kernel writes the values into pinned memory and the host watches for them, which returns a
 // few us after the kernel, where a copy and a wait for the stream take some 20 us more (a CFL
-// step needs its speed before the next one can be planned).  Everything enqueued before has
-// finished when this returns.
+// step needs its speed before the next one can be planned).  It watches for at most kWatch, longer
+// than a step takes (256^3: 2.5 ms), and leaves longer waits, behind a queued run, to the runtime,
+// which sleeps and reports the stream's errors.  Everything enqueued before has finished when this
+// returns; if it fails, out is as it was.
+constexpr std::chrono::milliseconds kWatch{5};
 void reduce_to_host(dh_sim* s, const double* in, int count, int stride, int nvec, bool max,
                     double* out) {
   refuse_capture(s);
   const uint64_t seq = ++s->host_seq;
   dh::launch_reduce_to_host(s->st, in, count, stride, nvec, max, s->host_out, seq);
+  const auto arrived = [&](int v) {
+    return __atomic_load_n(&s->host_out[v].seq, __ATOMIC_ACQUIRE) == seq;
+  };
+  const auto until = std::chrono::steady_clock::now() + kWatch;
+  bool watching = true;
   for (int v = 0; v < nvec; ++v) {
-    const dh::HostValue* h = s->host_out + v;
-    for (int spin = 1; __atomic_load_n(&h->seq, __ATOMIC_ACQUIRE) != seq; ++spin) {
-      if (spin % (1 << 16) != 0) continue;
-      // still not there: has the stream failed, or drained without it?
-      const hipError_t e = hipStreamQuery(s->st);
-      (void)hipGetLastError();
-      if (e == hipErrorNotReady) continue;
-      if (e != hipSuccess) throw HipError(std::string("reduction: ") + hipGetErrorString(e));
-      if (__atomic_load_n(&h->seq, __ATOMIC_ACQUIRE) != seq)
-        throw HipError("reduction: the device's value did not arrive");
+    for (int spin = 1; !arrived(v) && watching; ++spin) {
+      __builtin_ia32_pause();
+      if (spin % 256 == 0) watching = std::chrono::steady_clock::now() < until;
     }
-    out[v] = h->value;
+    if (arrived(v)) continue;
+    sync(s);
+    if (!arrived(v)) throw HipError("reduction: the device's value did not arrive");
   }
+  for (int v = 0; v < nvec; ++v) out[v] = s->host_out[v].value;
 }
 
 Batch batch(const dh_sim* s, const StepScal* tab) { return Batch{s->n, s->S, tab, s->nq}; }

@@ -1,12 +1,13 @@
 // A HIP runtime for host-logic tests on a machine without a GPU: device memory is host memory,
 // copies are memcpy, kernels do nothing (a value handed to the waiting host arrives, unless held
-// back) and every launch is logged by name.  Failures of chosen calls are injected.
+// back or late) and every launch is logged by name.  Failures of chosen calls are injected.
+#include <chrono>
 #include <cstdint>
 #include <cstdlib>
 #include <cstring>
 #include <map>
 #include <string>
-#include <vector>
+#include <thread>
 
 namespace {
 struct Dim3 {
@@ -21,7 +22,8 @@ int last_error = 0;
 // calls until one fails, < 0: none
 int fail_malloc = -1, fail_host_malloc = -1;
 std::string fail_kernel;   // a launch whose name contains it fails, once
-int hold_values = 0;
+int hold_values = 0, late_ms = 0;
+std::chrono::steady_clock::time_point done;   // when the stream's work has ended
 int syncs = 0, null_writes = 0;
 int dirty_counts = 0;   // histograms begun on counts that were not clear
 Dim3 cfg_grid, cfg_block;
@@ -38,6 +40,7 @@ void stub_fail_malloc(int n) { fail_malloc = n; }
 void stub_fail_host_malloc(int n) { fail_host_malloc = n; }
 void stub_fail_kernel(const char* name) { fail_kernel = name; }
 void stub_hold_values(int on) { hold_values = on; }
+void stub_late_values(int ms) { late_ms = ms; }
 int stub_syncs() { return syncs; }
 int stub_null_writes() { return null_writes; }
 int stub_dirty_counts() { return dirty_counts; }
@@ -91,10 +94,11 @@ int hipGetLastError() {
 const char* hipGetErrorString(int e) { return e ? "injected" : "no error"; }
 int hipStreamSynchronize(void*) {
   ++syncs;
+  std::this_thread::sleep_until(done);
   return 0;
 }
 int hipDeviceSynchronize() { return 0; }
-int hipStreamQuery(void*) { return 0; }
+int hipStreamQuery(void*) { return std::chrono::steady_clock::now() < done ? 600 : 0; }
 int hipStreamIsCapturing(void*, int* c) {
   *c = 0;
   return 0;
@@ -177,11 +181,19 @@ int hipLaunchKernel(const void* f, Dim3 grid, Dim3, void** args, size_t, void*) 
   if (is("reduce_to_host_kernel") && !hold_values) {           // in, count, stride, out, seq
     char* out = pointer(3);
     const uint64_t seq = *static_cast<uint64_t*>(args[4]);
-    for (uint32_t v = 0; v < grid.x; ++v) {
-      const double one = 1.0;
-      std::memcpy(out + 16 * v, &one, 8);
-      std::memcpy(out + 16 * v + 8, &seq, 8);
-    }
+    done = std::chrono::steady_clock::now() + std::chrono::milliseconds(late_ms);
+    const auto arrive = [out, seq, n = grid.x] {
+      std::this_thread::sleep_until(done - std::chrono::milliseconds(20));
+      for (uint32_t v = 0; v < n; ++v) {
+        const double one = 1.0;
+        std::memcpy(out + 16 * v, &one, 8);
+        __atomic_store_n(reinterpret_cast<uint64_t*>(out + 16 * v + 8), seq, __ATOMIC_RELEASE);
+      }
+    };
+    if (late_ms)
+      std::thread(arrive).detach();
+    else
+      arrive();
   }
   return 0;
 }

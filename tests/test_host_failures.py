@@ -119,3 +119,33 @@ for k in range(200):
     assert lib.dh_destroy(h) == 0
 assert k < 199 and (fails > 0 or kind == "host_malloc" or call == "power_loss"), (k, fails)
 """, kind, call)
+
+
+def test_a_long_wait_does_not_hold_the_processor(stub):
+    """Values handed to the host are watched for a short while; behind work that takes longer
+    (a replayed forward is queued as a whole) the wait is the runtime's."""
+    run(stub, """
+import time
+h = create()
+loss, a = (ctypes.c_double * 1)(), buf(16**3)
+assert lib.dh_init_from_seed(h, 1) == 0
+stub.stub_late_values(500)
+wall, cpu = time.perf_counter(), time.process_time()
+assert lib.dh_loss(h, a, loss) == 0
+wall, cpu = time.perf_counter() - wall, time.process_time() - cpu
+assert loss[0] * 16**3 == 1.0
+assert wall > 0.45 and cpu < 0.2, (wall, cpu)
+""")
+
+
+def test_a_value_that_does_not_arrive_is_an_error(stub):
+    run(stub, """
+h = create()
+loss, a = (ctypes.c_double * 1)(7.0), buf(16**3)
+assert lib.dh_init_from_seed(h, 1) == 0
+stub.stub_hold_values(1)
+assert lib.dh_loss(h, a, loss) == -3
+assert loss[0] == 7.0
+stub.stub_hold_values(0)
+assert lib.dh_loss(h, a, loss) == 0 and loss[0] * 16**3 == 1.0
+""")
