@@ -146,35 +146,32 @@ __device__ __forceinline__ double starform_uniform(long long c, const SourceArgs
 // its argument is below -110.  logit u of the 24-bit uniforms is at most
 // log((1 - 2^-25) / 2^-25) < 17.33, so a cell whose estimate stays below -110 with that
 // bound needs no uniform at all.  The estimate uses the hardware exp2/log2/rcp/sqrt (absolute
-// error of the logit near 1e-6, against the margin of tau between -110 and -109); it is +inf
+// error of the logit near 1e-6, up to 1e-4 from one_minus_exp_neg, against the margin of tau
+// between -110 and -109, and of 7 tau to where FP32 holds anything); it is +inf
 // (no screening) where the float32 probability nears underflow.
 constexpr float kMaxLogitU = 17.5f;
 
 __device__ __forceinline__ float fast_exp(float x) { return __expf(x); }
 __device__ __forceinline__ float fast_log(float x) { return __logf(x); }
-// log x of a normal x for the estimates (one hardware log2; __logf adds a dozen instructions
-// for denormal x and the last bit)
-__device__ __forceinline__ float log_estimate(float x) {
-  return 0.69314718f * __builtin_amdgcn_logf(x);
-}
 // 1 - exp(-x) for x >= 0, relative error below 1e-4
 __device__ __forceinline__ float one_minus_exp_neg(float x) {
   return x < 1e-3f ? x * (1.0f - 0.5f * x) : 1.0f - fast_exp(-x);
 }
 __device__ __forceinline__ float fast_log_sigmoid(float y) {
-  return fminf(y, 0.0f) - log_estimate(1.0f + fast_exp(-fabsf(y)));
+  return fminf(y, 0.0f) - fast_log(1.0f + fast_exp(-fabsf(y)));
 }
 // log p - log(1 - p) from log p
 __device__ __forceinline__ float fast_logit_of_log(float logp) {
-  return logp - log_estimate(1.0f - fast_exp(logp));
+  return logp - fast_log(1.0f - fast_exp(logp));
 }
 
-__device__ __forceinline__ bool screened_out(float logit_pi, float logit_u, float inv_tau) {
-  return (logit_pi + logit_u) * inv_tau < -110.0f;
+// (screen: -110 tau)
+__device__ __forceinline__ bool screened_out(float logit_pi, float logit_u, float screen) {
+  return logit_pi + logit_u < screen;
 }
 __device__ __forceinline__ float logit_u_of(double u) {
   const float uf = static_cast<float>(u);
-  return log_estimate(uf) - log_estimate(1.0f - uf);
+  return fast_log(uf) - fast_log(1.0f - uf);
 }
 
 // a scalar that is the same in the whole wave, kept in a scalar register
@@ -187,14 +184,14 @@ __device__ __forceinline__ float uniform_f(double x) {
 // step's FP64 scalars, converted once a thread before its cells.
 struct CellScal {
   float ia, efloor, gm2, gg1;
-  float t_per_e, inv_rho_mean, c_x, delta_c, k_rho, t_c, k_t, inv_tau;
+  float t_per_e, inv_rho_mean, c_x, delta_c, k_rho, t_c, k_t, screen;
   int mode;
 };
 __device__ __forceinline__ CellScal cell_scalars(const SourceArgs& a, double gg1) {
   return {uniform_f(1.0 / a.a), uniform_f(a.efloor),       uniform_f(a.gamma - 2.0),
           uniform_f(gg1),       uniform_f(a.t_per_e),      uniform_f(a.inv_rho_mean),
           uniform_f(a.c_x),     uniform_f(a.delta_c),      uniform_f(a.k_rho),
-          uniform_f(a.t_c),     uniform_f(a.k_t),          uniform_f(a.inv_tau),
+          uniform_f(a.t_c),     uniform_f(a.k_t),          uniform_f(-110.0 * a.tau),
           a.mode};
 }
 
@@ -215,7 +212,7 @@ __device__ __forceinline__ float draw_logit_estimate(const float* q5, const Cell
   if (!(psf > 1e-30f)) return INFINITY;
   const float y1 = (delta - a.delta_c) * a.k_rho;
   const float y2 = (a.t_c - temp) * a.k_t;
-  return fast_logit_of_log(log_estimate(psf) + fast_log_sigmoid(y1) + fast_log_sigmoid(y2));
+  return fast_logit_of_log(fast_log(psf) + fast_log_sigmoid(y1) + fast_log_sigmoid(y2));
 }
 
 // sigmoid(y) and log sigmoid(y) from one exponential: t = exp(-|y|),
@@ -324,11 +321,11 @@ __device__ __forceinline__ void dual_close(float* q, double e_sn, float r1g) {
 // NQ = 6 (dual energy): the entropy also takes the injected energy, then the end-of-step
 // reset (dual_close); with the smoothed injection both follow in the injection pass.
 // Early on the pass is bounded by the arithmetic of the estimate and the CFL speed, so what is
-// the same in every cell is converted once (CellScal) and the estimate takes bare hardware
-// logarithms; five waves per SIMD (96 registers, nothing spilled) hide the loads: 256^3
-// 241 -> 207 us (10 fields), 128^3 45 -> 38, 13 x 64^3 74 -> 64; six waves or eight
-// with the source term's FP64 values in scratch: 215, 231.  NQ = 6 keeps its 141 registers (at
-// 96 it spills: 64^3 13.9 -> 16.6 us).
+// the same in every cell is converted once (CellScal); five waves per SIMD (96 registers,
+// nothing spilled) hide the loads: 256^3 241 -> 213 us (10 fields), 128^3 45 -> 40, 13 x 64^3
+// 74 -> 67; six waves or eight with the source term's FP64 values in scratch are slower.  (Bare
+// v_log_f32 times ln 2 in the estimate instead of __logf: 207, 38, 64, but a less accurate
+// estimate.)  NQ = 6 keeps its 141 registers (at 96 it spills: 64^3 13.9 -> 16.6 us).
 template <bool FULL, int NQ>
 __global__ void __launch_bounds__(kRedThreads, NQ == 5 ? 5 : 1) close_step_kernel(
     const float* q_in, float* q, const float* __restrict__ phi, float* __restrict__ star,
@@ -371,9 +368,9 @@ __global__ void __launch_bounds__(kRedThreads, NQ == 5 ? 5 : 1) close_step_kerne
     const float lg = cs.mode != 0 ? draw_logit_estimate<NQ>(q5, cs) : 0.0f;
     float zc = 0.0f, inj = 0.0f;
     double e_add = 0.0;   // energy injected into this cell
-    if (cs.mode != 0 && !screened_out(lg, kMaxLogitU, cs.inv_tau)) {
+    if (cs.mode != 0 && !screened_out(lg, kMaxLogitU, cs.screen)) {
       const double u = starform_uniform(c, a);
-      if (!screened_out(lg, logit_u_of(u), cs.inv_tau)) {
+      if (!screened_out(lg, logit_u_of(u), cs.screen)) {
         const SrcCell s = source_eval<NQ>(q5, u, a);
         if (s.z != 0.0) {
           const double e_sn = a.a * a.a * s.rho * s.z * a.e0_code;
@@ -553,9 +550,9 @@ __device__ __forceinline__ void source_cell_vjp(const float* q5, long long c,
                                                 const SourceArgs& a, const CellScal& cs, float* l5,
                                                 double li, double acc[2]) {
   const float lg = draw_logit_estimate<NQ>(q5, cs);
-  if (screened_out(lg, kMaxLogitU, cs.inv_tau)) return;
+  if (screened_out(lg, kMaxLogitU, cs.screen)) return;
   const double u = starform_uniform(c, a);
-  if (screened_out(lg, logit_u_of(u), cs.inv_tau)) return;
+  if (screened_out(lg, logit_u_of(u), cs.screen)) return;
   const SrcCell s = source_eval<NQ>(q5, u, a);
   const double le = l5[4];
   const double K = a.a * a.a * a.e0_code;
@@ -606,9 +603,9 @@ __device__ __forceinline__ void dual_close_vjp(const float* q, long long c, cons
   double e_sn = 0.0;
   if (cs.mode != 0) {
     const float lg = draw_logit_estimate<6>(q, cs);
-    if (!screened_out(lg, kMaxLogitU, cs.inv_tau)) {
+    if (!screened_out(lg, kMaxLogitU, cs.screen)) {
       const double u = starform_uniform(c, a);
-      if (!screened_out(lg, logit_u_of(u), cs.inv_tau)) {
+      if (!screened_out(lg, logit_u_of(u), cs.screen)) {
         const SrcCell s = source_eval<6>(q, u, a);
         if (s.z != 0.0) e_sn = a.a * a.a * s.rho * s.z * a.e0_code;
       }
@@ -907,10 +904,10 @@ __global__ void __launch_bounds__(kRedThreads) close_step_mlp_kernel(
     if (valid) {
       const float o0 = stage[wave][lane][5], o1 = stage[wave][lane][6];
       const float lg = closure_logit_estimate(o0, o1, a);
-      const double u = screened_out(lg, kMaxLogitU, cs.inv_tau) ? 0.5 : starform_uniform(c, a);
+      const double u = screened_out(lg, kMaxLogitU, cs.screen) ? 0.5 : starform_uniform(c, a);
       float zc = 0.0f, inj = 0.0f;
       double e_add = 0.0;   // energy injected into this cell
-      if (!screened_out(lg, kMaxLogitU, cs.inv_tau) && !screened_out(lg, logit_u_of(u), cs.inv_tau)) {
+      if (!screened_out(lg, kMaxLogitU, cs.screen) && !screened_out(lg, logit_u_of(u), cs.screen)) {
         const ClosureDraw d = closure_draw(o0, o1, u, a);
         if (d.z != 0.0) {
           const double e_sn = a.a * a.a * static_cast<double>(q5[0]) * d.z * a.e0_code;
@@ -1017,8 +1014,8 @@ __global__ void __launch_bounds__(kRedThreads, 2) source_vjp_mlp_kernel(
         if (valid) {
           const float o0 = stage[wave][lane][5], o1 = stage[wave][lane][6];
           const float lg = closure_logit_estimate(o0, o1, a);
-          const double u = screened_out(lg, kMaxLogitU, cs.inv_tau) ? 0.5 : starform_uniform(c, a);
-          const bool drawn = !screened_out(lg, kMaxLogitU, cs.inv_tau) && !screened_out(lg, logit_u_of(u), cs.inv_tau);
+          const double u = screened_out(lg, kMaxLogitU, cs.screen) ? 0.5 : starform_uniform(c, a);
+          const bool drawn = !screened_out(lg, kMaxLogitU, cs.screen) && !screened_out(lg, logit_u_of(u), cs.screen);
           ClosureDraw d{};
           if (drawn) {
             d = closure_draw(o0, o1, u, a);
