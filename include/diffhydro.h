@@ -320,7 +320,9 @@ int dh_conservation_noalloc(const float* d_q, const float* d_mom, int32_t n, int
  *  sweep_vjp: lam_in = (d sweep / d q_in)^T lam_out at q_in.
  *  poisson:  phi = solution of lap(phi) = (3 Om / 2a) delta (Green's function -1/k^2).
  *  deposit:  delta = rho_gas + m_dm CIC(pos) - 1 (cell-sorted, deterministic).
- *  readout:  out[3][np] = CIC interpolation of the central-difference g = -grad(phi).  */
+ *  readout:  out[3][np] = CIC interpolation of the central-difference g = -grad(phi).
+ *  deposit_vec: out[3][n^3] += CIC deposit of the particles' vectors vec[3][np], the adjoint
+ *            of reading a mesh vector out at pos (the reverse pass's deposit).  */
 int dh_stage_sweep(dh_sim* sim, const float* d_q_in, float* d_q_out, int32_t axis, double dt,
                    double a_stage1, double a_stage2);
 int dh_stage_sweep_vjp(dh_sim* sim, const float* d_q_in, const float* d_lam_out,
@@ -329,6 +331,7 @@ int dh_stage_sweep_vjp(dh_sim* sim, const float* d_q_in, const float* d_lam_out,
 int dh_stage_poisson(dh_sim* sim, const float* d_delta, float* d_phi, double a);
 int dh_stage_deposit(dh_sim* sim, const float* d_rho_gas, const float* d_pos, float* d_delta);
 int dh_stage_readout(dh_sim* sim, const float* d_phi, const float* d_pos, float* d_g);
+int dh_stage_deposit_vec(dh_sim* sim, const float* d_pos, const float* d_vec, float* d_out);
 
 /* Message of the last failed call on sim; with sim NULL, of the last failed handle-free
  * call (dh_conservation_noalloc) on this thread. */

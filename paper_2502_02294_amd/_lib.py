@@ -108,6 +108,7 @@ _SIGNATURES = {
     "dh_stage_poisson": (I, [P, P, P, D]),
     "dh_stage_deposit": (I, [P, P, P, P]),
     "dh_stage_readout": (I, [P, P, P, P]),
+    "dh_stage_deposit_vec": (I, [P, P, P, P]),
     "dh_last_error": (ctypes.c_char_p, [P]),
     "dh_strerror": (ctypes.c_char_p, [ctypes.c_int]),
     "dh_set_closure": (I, [P, P]),

@@ -2296,6 +2296,19 @@ int dh_stage_readout(dh_sim* s, const float* d_phi, const float* d_pos, float* d
   });
 }
 
+int dh_stage_deposit_vec(dh_sim* s, const float* d_pos, const float* d_vec, float* d_out) {
+  if (!s || !d_pos || !d_vec || !d_out) return DH_E_INVAL;
+  return guarded(s, [&]() -> int {
+    StepScal e{};
+    e.active = 1;
+    e.h_open = 1.0f;
+    const Batch one{s->n, 1, stage_table(s, e), s->nq};
+    sort_particles(s, d_pos, one, true);
+    dh::launch_deposit_vec(s->st, s->bins, d_vec, false, d_out, one);
+    return DH_OK;
+  });
+}
+
 // handle-free calls (dh_conservation_noalloc) keep their last message per thread
 const char* dh_last_error(const dh_sim* s) {
   return s ? s->err.c_str() : dh_noalloc_last_error_message();

@@ -354,6 +354,14 @@ class Sim:
                                            _ptr(pos, numel=3 * self.nc), _ptr(out)))
         return out
 
+    def stage_deposit_vec(self, pos, vec, out):
+        """out [3, n, n, n] += the CIC deposit of the particles' vectors vec [3, n^3]."""
+        self._stream()
+        self._check(lib().dh_stage_deposit_vec(self._h, _ptr(pos, numel=3 * self.nc),
+                                               _ptr(vec, numel=3 * self.nc),
+                                               _ptr(out, numel=3 * self.nc)))
+        return out
+
 
 def conservation_noalloc(q, mom, n, m_dm, out, batch=1):
     """dh_conservation_noalloc: the FP64 sums of Sim.conservation over caller tensors q
