@@ -38,9 +38,12 @@ __device__ __forceinline__ int mode_radius(int kx, int ky, int kz, int n) {
 // partial[(s nbins + b) nblk + block] = sum over the block's modes of bin b of w |X|^2.  Every
 // bin's thread looks at the block's modes one after the other, which is what bounds the pass, so a
 // bin gets as many threads as there are for 2^lgb >= nbins bins, each over a strided share of the
-// modes, added in order, and small boxes take fewer modes a block (per = 2 up to 64^3, 8 above,
-// where the partials of more blocks cost more): 64^3 in 20 bins 125 -> 7.6 us, one thread a bin
-// and 8 modes a thread before.
+// modes, added in order (64^3 in 20 bins 125 -> 7.6 us, one thread a bin and 8 modes a thread
+// before).  Fewer modes a block shorten the scan: 2 a thread against 8 take, in 8 and in n/2 bins,
+// 4.8 and 4.7 us against 10.2 and 10.1 at 16^3, 5.3 and 7.9 against 10.6 and 21.0 at 64^3, 8.9 and
+// 22.9 against 11.7 and 38.2 at 128^3; at 256^3, where every block's reduction counts, 39.5 and
+// 199 against 36.2 and 222: 2 up to 128^3, 8 there (the sum over the blocks takes 3 to 6 us with
+// either).
 __global__ void __launch_bounds__(kPkThreads) pk_bin_kernel(const float2* __restrict__ spec,
                                                              int n, int nbins, int lgb, int per,
                                                              long long nck,
@@ -212,7 +215,7 @@ __global__ void __launch_bounds__(256) fli_obs_kernel(const float* __restrict__ 
 
 }  // namespace
 
-static int pk_per(int n) { return n <= 64 ? 2 : kPkPer; }
+static int pk_per(int n) { return n <= 128 ? 2 : kPkPer; }
 
 int pk_blocks(int n) {
   const long long nck = static_cast<long long>(n) * n * (n / 2 + 1);
