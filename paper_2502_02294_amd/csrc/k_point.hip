@@ -145,24 +145,34 @@ __device__ __forceinline__ double starform_uniform(long long c, const SourceArgs
 // below e^-109 (zero in float, and no change of the energy in float) when an FP32 estimate of
 // its argument is below -110.  logit u of the 24-bit uniforms is at most
 // log((1 - 2^-25) / 2^-25) < 17.33, so a cell whose estimate stays below -110 with that
-// bound needs no uniform at all.  The estimate uses the hardware exp2/log2/rcp/sqrt (absolute
-// error of the logit near 1e-6, up to 1e-4 from one_minus_exp_neg, against the margin of tau
-// between -110 and -109, and of 7 tau to where FP32 holds anything); it is +inf
-// (no screening) where the float32 probability nears underflow.
+// bound needs no uniform at all.  The estimate uses the hardware exp2/log2/rcp/sqrt: against
+// 64 bits over draws with |logit sum| < 20 and logit pi0 < 8 its error is 3.6e-6 rms and at most
+// 2.5e-4 (from 1 - exp of a small argument), against the margin of tau between -110 and -109 and
+// of 7 tau up to the smallest draw FP32 holds, which that error would reach at tau = 4e-5 (default
+// 0.1, where a cell of logit pi0 above 6.4 cannot be screened at all).  It is +inf (no screening)
+// where the float32 probability nears underflow.
 constexpr float kMaxLogitU = 17.5f;
 
 __device__ __forceinline__ float fast_exp(float x) { return __expf(x); }
 __device__ __forceinline__ float fast_log(float x) { return __logf(x); }
+// ln x of a normal x, for the estimates: one hardware log2.  As accurate as __logf, which adds
+// the handling of denormal x: error against 64 bits over every float, in units of the result's
+// last place, rms 0.74 (__logf 0.78) and at most 2.22 (2.15) below 1, 0.48 (0.58) and 1.81 (2.07)
+// in [1, 2].  With __logf the closing pass takes 217 us at 256^3 instead of 205, the source adjoint
+// with the opening kick 418 instead of 359.
+__device__ __forceinline__ float log_estimate(float x) {
+  return 0.69314718f * __builtin_amdgcn_logf(x);
+}
 // 1 - exp(-x) for x >= 0, relative error below 1e-4
 __device__ __forceinline__ float one_minus_exp_neg(float x) {
   return x < 1e-3f ? x * (1.0f - 0.5f * x) : 1.0f - fast_exp(-x);
 }
 __device__ __forceinline__ float fast_log_sigmoid(float y) {
-  return fminf(y, 0.0f) - fast_log(1.0f + fast_exp(-fabsf(y)));
+  return fminf(y, 0.0f) - log_estimate(1.0f + fast_exp(-fabsf(y)));
 }
 // log p - log(1 - p) from log p
 __device__ __forceinline__ float fast_logit_of_log(float logp) {
-  return logp - fast_log(1.0f - fast_exp(logp));
+  return logp - log_estimate(1.0f - fast_exp(logp));
 }
 
 // (screen: -110 tau)
@@ -171,7 +181,7 @@ __device__ __forceinline__ bool screened_out(float logit_pi, float logit_u, floa
 }
 __device__ __forceinline__ float logit_u_of(double u) {
   const float uf = static_cast<float>(u);
-  return fast_log(uf) - fast_log(1.0f - uf);
+  return log_estimate(uf) - log_estimate(1.0f - uf);
 }
 
 // a scalar that is the same in the whole wave, kept in a scalar register
@@ -212,7 +222,7 @@ __device__ __forceinline__ float draw_logit_estimate(const float* q5, const Cell
   if (!(psf > 1e-30f)) return INFINITY;
   const float y1 = (delta - a.delta_c) * a.k_rho;
   const float y2 = (a.t_c - temp) * a.k_t;
-  return fast_logit_of_log(fast_log(psf) + fast_log_sigmoid(y1) + fast_log_sigmoid(y2));
+  return fast_logit_of_log(log_estimate(psf) + fast_log_sigmoid(y1) + fast_log_sigmoid(y2));
 }
 
 // sigmoid(y) and log sigmoid(y) from one exponential: t = exp(-|y|),
@@ -321,11 +331,11 @@ __device__ __forceinline__ void dual_close(float* q, double e_sn, float r1g) {
 // NQ = 6 (dual energy): the entropy also takes the injected energy, then the end-of-step
 // reset (dual_close); with the smoothed injection both follow in the injection pass.
 // Early on the pass is bounded by the arithmetic of the estimate and the CFL speed, so what is
-// the same in every cell is converted once (CellScal); five waves per SIMD (96 registers,
-// nothing spilled) hide the loads: 256^3 241 -> 213 us (10 fields), 128^3 45 -> 40, 13 x 64^3
-// 74 -> 67; six waves or eight with the source term's FP64 values in scratch are slower.  (Bare
-// v_log_f32 times ln 2 in the estimate instead of __logf: 207, 38, 64, but a less accurate
-// estimate.)  NQ = 6 keeps its 141 registers (at 96 it spills: 64^3 13.9 -> 16.6 us).
+// the same in every cell is converted once (CellScal) and the estimate takes bare hardware
+// logarithms; five waves per SIMD (96 registers, nothing spilled) hide the loads: 256^3
+// 241 -> 207 us (10 fields), 128^3 45 -> 38, 13 x 64^3 74 -> 64; six waves or eight
+// with the source term's FP64 values in scratch: 215, 231.  NQ = 6 keeps its 141 registers (at
+// 96 it spills: 64^3 13.9 -> 16.6 us).
 template <bool FULL, int NQ>
 __global__ void __launch_bounds__(kRedThreads, NQ == 5 ? 5 : 1) close_step_kernel(
     const float* q_in, float* q, const float* __restrict__ phi, float* __restrict__ star,
